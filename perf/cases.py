@@ -305,3 +305,66 @@ def tolerance(case):
         # the refreshed densities measured 2.7e-8; a rotated key may round to the neighbouring bf16 number
         return {"rel": 1e-5, "max": 8e-3, "differ": 2.5e-3}
     return {"rel": 4e-6, "max": 3e-5, "differ": 2.5e-3}     # attention: measured 9.6e-7, 6.7e-6
+
+
+# ---- the outputs in 64 bits -------------------------------------------------------------------------------------------------
+def _exact_density(X, sigma, rows=None):
+    """Kernel sums of the given rows (all by default) of one head over all its keys, in 64 bits."""
+    x = X.double()
+    x = x - x.mean(dim=0)
+    y = x if rows is None else x[rows]
+    n = x.square().sum(1)
+    out = torch.empty(y.shape[0], dtype=torch.float64, device=X.device)
+    step = max(1, (1 << 27) // x.shape[0])
+    for a in range(0, y.shape[0], step):
+        e = (y[a:a + step] @ x.t().contiguous()).mul_(2.0).sub_(n[None]).sub_(y[a:a + step].square().sum(1)[:, None])
+        out[a:a + step] = e.clamp_(max=0.0).mul_(0.5 / sigma ** 2).exp_().sum(1)
+    return out
+
+
+def _exact_attend(Q, Ks, Vs):
+    N, Hq, d = Q.shape
+    g = Hq // Ks.shape[0]
+    out = torch.empty((N, Hq, d), dtype=torch.float64, device=Q.device)
+    for q in range(Hq):
+        z = (Q[:, q].double() @ Ks[q // g].double().t().contiguous()) / math.sqrt(d)
+        out[:, q] = torch.softmax(z, dim=1) @ Vs[q // g].double()
+    return out
+
+
+def exact(case, seed):
+    kind, H, d = case["kind"], case["H"], case["d"]
+    if kind == "select" or (kind in ("density", "pass") and H * case["L"] ** 2 > 2 ** 38):
+        return None                                         # picks have no value in 64 bits; the largest sweeps take too long
+    st = prepare(case, seed)
+    if kind in ("density", "pass"):
+        rho = torch.stack([_exact_density(st["K"][h], st["sigma"][h]) for h in range(H)]) / case["L"]
+        return rho if kind == "density" else [rho, None, None, None, None]
+    if kind == "agents":
+        if case["form"] == "synapse":
+            return [_exact_attend(st["Q"], st["Ks"], st["Vs"])]
+        at = st["idx"].long()[:, :, None].expand(-1, -1, d)
+        Ks, Vs = st["K"].gather(1, at), st["V"].gather(1, at)
+        O = _exact_attend(st["Q"], Ks, Vs)
+        return O if case["form"] == "indexed" else [O, Ks.double(), Vs.double()]
+    if kind == "upkeep":
+        m, L = case["m"], case["L"]
+        h, T = st["h"].double(), st["T"].double()
+        score = (T @ h) / (h.norm() * T.norm(dim=1))
+        ang = st["pos"].double()[:, None] * ROPE_BASE ** (-2.0 / d * torch.arange(d // 2, device="cuda", dtype=torch.float64))
+        x0, x1 = st["Knew"].double().split(d // 2, dim=2)
+        Kr = torch.cat([x0 * ang.cos() - x1 * ang.sin(), x1 * ang.cos() + x0 * ang.sin()], dim=2)
+        Kc = st["Kc"]
+        Kc[:, L - m:] = Kr.to(Kc.dtype)
+        rho = torch.empty((H, L), dtype=torch.float64, device="cuda")
+        for i in range(H):
+            x, s = Kc[i].double(), st["sigma"][i]
+            w = torch.stack([torch.exp((x - x[L - m + r]).square().sum(1) * (-0.5 / s ** 2)) for r in range(m)])
+            rho[i, :L - m] = st["rho_old"][i].double() * (L - m) + w[:, :L - m].sum(0)
+            rho[i, L - m:] = w.sum(1)
+        return [score, None, None, None, rho / L]
+    g, G = case["g"], case["G"]
+    A = torch.zeros((G, case["L"]), dtype=torch.float64, device="cuda")
+    for q in range(H * g):
+        A[q // (H * g // G)] += torch.softmax(st["K"][q // g].double() @ st["Q"][q].double() / math.sqrt(d), dim=0)
+    return (1.0 / A.clamp(min=1e-30)).repeat_interleave(H // G, dim=0)
