@@ -95,8 +95,8 @@ ws_status ws_synapse_density(const void *K, ws_dtype dt, int H, int L, int d,
  * NULL, the H estimates (host array). */
 ws_status ws_synapse_density_check(const void *workspace, int H, ws_stream stream, int *flagged, float *err_est);
 
-/* Which sweep ws_synapse_density runs for these sizes: 1 = the symmetric sweep (every unordered pair once),
- * 0 = the full sweep.  For reports and profiles. */
+/* Which sweep ws_synapse_density runs for these sizes: 1 = a symmetric sweep (every unordered pair once), 0 = sizes it
+ * does not take.  For reports and profiles. */
 int ws_synapse_density_is_symmetric(ws_dtype dt, int L, int d);
 
 /*

@@ -29,83 +29,49 @@
 // offsets that cannot be removed exactly).  For sigma -> 0 only the self term survives, and that one
 // is exact by construction.
 //
-// Work split: one workgroup (4 waves) owns RT*32 rows whose MFMA A-fragments stay in
-// registers for the whole sweep; the 4 waves stride over the 32-column tiles of the head and
-// read B-fragments straight from global memory/L2 in MFMA operand layout (each lane a 16-byte
-// piece of one key row), one tile ahead of use.  No LDS, no barrier inside the sweep.
+// Every unordered pair is evaluated once (the kernel matrix is symmetric) by one of two sweeps: density_sym for bf16
+// heads of at least four blocks of 256 keys, density_sym_small for fp32 keys and for shorter heads.
 #include "ws_internal.h"
+
+#include <type_traits>
 
 namespace ws {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 
-// ------------------------------------------------------------------------------------------
-// Element traits: how a 32 x KSTEP operand fragment is fetched and multiplied.
-// Lane l of a wave supplies row (l % 32) of the tile and the k-slice selected by (l / 32).
-// Both operands of K K^T are fetched with the same pattern, so the result does not depend on
-// how the hardware orders the k-slots inside an instruction.
-// ------------------------------------------------------------------------------------------
-struct Bf16Tr {
-    typedef uint16_t Elem;
-    typedef bf16x8_t Frag;
-    static constexpr int KSTEP = 16;  // v_mfma_f32_32x32x16_bf16
-    static constexpr int NEXT = 1;    // one extra k-step carries both norm terms
-    static __device__ __forceinline__ Frag load(const Elem *row, int kk, int hb)
-    {
-        return *reinterpret_cast<const Frag *>(row + kk * 16 + hb * 8);
-    }
-    // record = 8 bf16: {m1,m2,m3,m4, 1,1,1,1},  m1+..+m4 = -n/2
-    static __device__ __forceinline__ Frag ext_a(uint4 rec, int hb, int)
-    {
-        if (hb) rec = make_uint4(0, 0, 0, 0);
-        return __builtin_bit_cast(Frag, rec);
-    }
-    static __device__ __forceinline__ Frag ext_b(uint4 rec, int hb, int)
-    {
-        uint4 r = hb ? make_uint4(0, 0, 0, 0) : make_uint4(rec.z, rec.w, rec.x, rec.y);
-        return __builtin_bit_cast(Frag, r);
-    }
-    static __device__ __forceinline__ f32x16_t mfma(Frag a, Frag b, f32x16_t c)
-    {
-        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-    }
-    static __device__ __forceinline__ double widen(Elem e)
-    {
-        return (double)__uint_as_float((uint32_t)e << 16);
-    }
-};
+typedef __attribute__((ext_vector_type(8))) float f32x8_t;
+typedef f32x8_t __attribute__((aligned(16))) f32x8_16_t;     // as rows in memory are aligned
 
-struct F32Tr {
-    typedef float Elem;
-    typedef float Frag;
-    static constexpr int KSTEP = 2;  // v_mfma_f32_32x32x2_f32
-    static constexpr int NEXT = 2;   // hi and lo part of -n/2, one k-step each
-    static __device__ __forceinline__ Frag load(const Elem *row, int kk, int hb) { return row[kk * 2 + hb]; }
-    // record = 4 floats: {hi, lo, 0, 0},  hi + lo = -n/2
-    static __device__ __forceinline__ Frag ext_a(uint4 rec, int hb, int e)
-    {
-        return hb ? 1.0f : __uint_as_float(e ? rec.y : rec.x);
+// Lane l of a wave supplies row (l % 32) of a 32-row tile and the k-slice selected by (l / 32).  Both operands of K K^T
+// are fetched with the same pattern, so the result does not depend on how the hardware orders the k-slots inside an
+// instruction.
+__device__ __forceinline__ bf16x8_t load_frag(const uint16_t *row, int kk, int hb)
+{
+    return *reinterpret_cast<const bf16x8_t *>(row + kk * 16 + hb * 8);
+}
+
+// A float is the exact sum of three bf16 numbers (3 x 8 significant bits): p[0] + p[1] + p[2].  A NaN or an infinity
+// leaves a NaN in the later pieces.
+__device__ __forceinline__ void split3(f32x8_t x, bf16x8_t (&p)[3])
+{
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        p[i] = __builtin_convertvector(x, bf16x8_t);
+        x -= __builtin_convertvector(p[i], f32x8_t);
     }
-    static __device__ __forceinline__ Frag ext_b(uint4 rec, int hb, int e)
-    {
-        return hb ? __uint_as_float(e ? rec.y : rec.x) : 1.0f;
-    }
-    static __device__ __forceinline__ f32x16_t mfma(Frag a, Frag b, f32x16_t c)
-    {
-        return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
-    }
-    static __device__ __forceinline__ double widen(Elem e) { return (double)e; }
-};
+}
 
 // ------------------------------------------------------------------------------------------
 // Prepass.
-//   density_stats   (bf16)  per head, coordinate and chunk of rows: minimum, maximum, smallest non-zero magnitude
-//   density_decide          per head: the reference point c (zero where k - c would not be exact), which copy of the
-//                           head the sweep reads, the exponent scale; clears the flag
-//   density_prep            per key: k - c written to the copy (heads that move), |k - c|^2 in fp64 and its side
-//                           record; per block of 256 keys the sum of the squared norms
-//   density_estimate        per head: 2^-23 mean|k - c|^2 / sigma^2, and the flag
+//   density_stats  (bf16)  per head, coordinate and chunk of rows: minimum, maximum, smallest non-zero magnitude, first
+//                          on a sample, then, only for heads with a coordinate that might be moved, on all rows
+//   density_prep           the head's reference point c (zero where k - c would not be exact), which copy of the head the
+//                          sweep reads, the exponent scale; per key: k - c written to the copy (heads that move), |k - c|^2
+//                          in fp64 and its side record; per block of 256 keys the sum of the squared norms; clears the flag
+//   density_finish         rho from the accumulator cells; per head 2^-23 mean|k - c|^2 / sigma^2, and the flag
+// The reference point is worked out by every workgroup that needs it (24 KB of L2 reads, only in heads that may move)
+// rather than by kernels of their own: between two short kernels the chip idles for longer than that takes.
 // ------------------------------------------------------------------------------------------
 struct ScaleChunk {
     float s[256];
@@ -119,28 +85,68 @@ struct PrepWs {
     float *est;             // [H] estimated relative error of one kernel term
     float *scale;           // [H] log2(e) / sigma^2
     const void **kbase;     // [H] the rows the sweep reads: the caller's, or the translated copy
-    int *cand;              // [H] some coordinate of the head may be moved (after the sample pass); moved (after the full one)
-    float *cvec;            // [H][D] reference point
-    float *stat;            // [H][kStatChunks][3][D] min, max, smallest non-zero magnitude (bf16 keys only)
+    int *cand;              // [H] some coordinate of the head may be moved, going by the sample (bf16 keys only)
+    float *stat;            // [H][kStatChunks][3][D] min, max, smallest non-zero magnitude of the sample (bf16 keys only)
+    float *full;            // the same of all rows, for the heads with cand set
     double *nsum;           // [H][Lpad/256] sum of squared norms per block of keys
     uint4 *ext;             // [H][Lpad] side records
     void *Kc;               // [H][L][D] translated copy (bf16 keys only)
-    unsigned long long *acc;   // [H][Lpad] kernel sums in fixed point (symmetric sweep only, else NULL): cleared here
+    unsigned long long *acc;   // [H][Lpad] kernel sums in fixed point: started here at the self term
 };
 
 // Two passes.  Pass 0 looks at the first eighth of every chunk of rows.  More keys only widen a coordinate's range
 // and refine its grid, so a coordinate that fails the exactness test on the sample is taken to fail it on the whole
 // head (a rule on the safe side: it decides only whether a head is moved, never a value): heads without a candidate
 // coordinate are settled by the sample, and pass 1, which reads the rest and merges, skips them.
+// 2^(floor(log2 v) - 7): the spacing of bf16 numbers around |v| (v finite, normal, non-zero)
+__device__ __forceinline__ float bf16_ulp(float v)
+{
+    const uint32_t e = (__float_as_uint(v) >> 23) & 0xFFu;
+    return e > 7u ? __uint_as_float((e - 7u) << 23) : 0.0f;
+}
+
+// the reference point of coordinate j, from the statistics of the head's chunks; 0: the coordinate stays
+template <int D>
+__device__ __forceinline__ float reference_point(const float *__restrict__ stat /* the head's */, int j)
+{
+    float mn = __builtin_inff(), mx = -__builtin_inff(), ma = __builtin_inff();
+#pragma unroll
+    for (int ch = 0; ch < kStatChunks; ++ch) {
+        const float *st = stat + (size_t)ch * 3 * D;
+        mn = fminf(mn, st[j]);
+        mx = fmaxf(mx, st[D + j]);
+        ma = fminf(ma, st[2 * D + j]);
+    }
+    float c = 0.0f;
+    if (mx >= mn && ma < __builtin_inff()) {          // finite, not all zero
+        const float mid = __uint_as_float(bf16_rne(0.5f * mn + 0.5f * mx) << 16);
+        if (mid != 0.0f && fabsf(mid) < __builtin_inff()) {
+            // every key of the coordinate and c are multiples of g (the finer of their bf16 spacings); k - c is a
+            // bf16 number when |k - c| <= 256 g.  g must be a normal number well inside the range.
+            const float g = fminf(bf16_ulp(ma), bf16_ulp(mid));
+            const float X = fmaxf(mx - mid, mid - mn) * 1.000001f;
+            if (g >= 7.0e-31f && X <= 256.0f * g) c = mid;
+        }
+    }
+    return c;
+}
+
 template <int D>
 __global__ void __launch_bounds__(256)
-density_stats(const uint16_t *__restrict__ K, float *__restrict__ stat, int L, int pass, const int *__restrict__ cand)
+density_stats(const uint16_t *__restrict__ K, float *__restrict__ stat, float *__restrict__ full, int L, int pass,
+              int *__restrict__ cand)
 {
     constexpr int CH = D / 8;            // 16-byte pieces per row
     constexpr int RPS = 256 / CH;        // rows per sweep of the block
     __shared__ float red[3][RPS][D + 1];
     const int h = blockIdx.y, chunk = blockIdx.x;
-    if (pass == 1 && !cand[h]) return;
+    if (pass == 1) {
+        float c = 0.0f;
+        if (threadIdx.x < D) c = reference_point<D>(stat + (size_t)h * kStatChunks * 3 * D, threadIdx.x);
+        const int may = __syncthreads_or(c != 0.0f);
+        if (chunk == 0 && threadIdx.x == 0) cand[h] = may;
+        if (!may) return;
+    }
     const int per = (L + kStatChunks - 1) / kStatChunks;
     const int cut = chunk * per + (per + 7) / 8;
     const int lo = pass == 0 ? chunk * per : min(L, cut);
@@ -177,72 +183,43 @@ density_stats(const uint16_t *__restrict__ K, float *__restrict__ stat, int L, i
         const int which = c / D, j = c % D;
         float v = red[which][0][j];
         for (int r = 1; r < RPS; ++r) v = (which == 1) ? fmaxf(v, red[which][r][j]) : fminf(v, red[which][r][j]);
-        float *dst = stat + (((size_t)h * kStatChunks + chunk) * 3 + which) * D + j;
-        if (pass == 1) v = (which == 1) ? fmaxf(v, *dst) : fminf(v, *dst);
-        *dst = v;
+        const size_t at = (((size_t)h * kStatChunks + chunk) * 3 + which) * D + j;
+        if (pass == 1) full[at] = (which == 1) ? fmaxf(v, stat[at]) : fminf(v, stat[at]);
+        else stat[at] = v;
     }
 }
 
-// 2^(floor(log2 v) - 7): the spacing of bf16 numbers around |v| (v finite, normal, non-zero)
-__device__ __forceinline__ float bf16_ulp(float v)
+// sc: the exponent scales of the launch's heads
+template <bool kBf16, int D>
+__global__ void __launch_bounds__(256)
+density_prep(const void *__restrict__ K, PrepWs w, ScaleChunk sc, int head0, int L, int Lpad)
 {
-    const uint32_t e = (__float_as_uint(v) >> 23) & 0xFFu;
-    return e > 7u ? __uint_as_float((e - 7u) << 23) : 0.0f;
-}
-
-template <int D>
-__global__ void __launch_bounds__(D)
-density_decide(PrepWs w, const void *K, size_t head_bytes, ScaleChunk sc, int head0, int centre)
-{
-    const int h = head0 + blockIdx.x, j = threadIdx.x;
-    float c = 0.0f;
-    if (centre) {
-        float mn = __builtin_inff(), mx = -__builtin_inff(), ma = __builtin_inff();
-        for (int ch = 0; ch < kStatChunks; ++ch) {
-            const float *st = w.stat + ((size_t)h * kStatChunks + ch) * 3 * D;
-            mn = fminf(mn, st[j]);
-            mx = fmaxf(mx, st[D + j]);
-            ma = fminf(ma, st[2 * D + j]);
-        }
-        if (mx >= mn && ma < __builtin_inff()) {          // finite, not all zero
-            const float mid = __uint_as_float(bf16_rne(0.5f * mn + 0.5f * mx) << 16);
-            if (mid != 0.0f && fabsf(mid) < __builtin_inff()) {
-                // every key of the coordinate and c are multiples of g (the finer of their bf16 spacings); k - c is a
-                // bf16 number when |k - c| <= 256 g.  g must be a normal number well inside the range.
-                const float g = fminf(bf16_ulp(ma), bf16_ulp(mid));
-                const float X = fmaxf(mx - mid, mid - mn) * 1.000001f;
-                if (g >= 7.0e-31f && X <= 256.0f * g) c = mid;
-            }
+    typedef typename std::conditional<kBf16, uint16_t, float>::type Elem;
+    __shared__ double part[256];
+    __shared__ float cv[kBf16 ? D : 1];
+    const int h = head0 + blockIdx.y;
+    const int j = blockIdx.x * 256 + threadIdx.x;
+    const Elem *Kh = reinterpret_cast<const Elem *>(K) + (size_t)h * L * D;
+    Elem *Kch = reinterpret_cast<Elem *>(w.Kc) + (size_t)h * L * D;
+    bool moved = false;
+    if constexpr (kBf16) {
+        if (w.cand[h]) {
+            float c = 0.0f;
+            if (threadIdx.x < D) cv[threadIdx.x] = c = reference_point<D>(w.full + (size_t)h * kStatChunks * 3 * D, threadIdx.x);
+            moved = __syncthreads_or(c != 0.0f);
         }
     }
-    w.cvec[(size_t)h * D + j] = c;
-    const int moved = __syncthreads_or(c != 0.0f);
     if (j == 0) {
-        w.kbase[h] = moved ? (const void *)((const char *)w.Kc + (size_t)h * head_bytes)
-                           : (const void *)((const char *)K + (size_t)h * head_bytes);
-        w.cand[h] = moved;
-        w.scale[h] = sc.s[blockIdx.x];
+        w.kbase[h] = moved ? (const void *)Kch : (const void *)Kh;
+        w.scale[h] = sc.s[blockIdx.y];
         if (h == 0) w.flag[0] = 0;
     }
-}
-
-template <class TR, int D>
-__global__ void __launch_bounds__(256)
-density_prep(const typename TR::Elem *__restrict__ K, PrepWs w, int L, int Lpad)
-{
-    typedef typename TR::Elem Elem;
-    constexpr bool kBf16 = sizeof(Elem) == 2;
-    __shared__ double part[256];
-    const int h = blockIdx.y;
-    const int j = blockIdx.x * 256 + threadIdx.x;
-    const float *cv = w.cvec + (size_t)h * D;
-    const bool moved = kBf16 && w.kbase[h] != (const void *)(K + (size_t)h * L * D);
     uint4 rec;
     double n = 0.0;
     if (j < L) {
         // whole row through 16-byte loads (a thread owns a row: 8 or more loads hit the same lines)
-        const uint4 *row = reinterpret_cast<const uint4 *>(K + ((size_t)h * L + j) * D);
-        uint4 *crow = reinterpret_cast<uint4 *>(reinterpret_cast<Elem *>(w.Kc) + ((size_t)h * L + j) * D);
+        const uint4 *row = reinterpret_cast<const uint4 *>(Kh + (size_t)j * D);
+        uint4 *crow = reinterpret_cast<uint4 *>(Kch + (size_t)j * D);
         constexpr int PER = 16 / sizeof(Elem);
         constexpr int NPC = D / PER;             // 16-byte pieces per row
         constexpr int GRP = NPC < 8 ? NPC : 8;   // pieces in flight at a time (all loads of a group before any store)
@@ -266,7 +243,7 @@ density_prep(const typename TR::Elem *__restrict__ K, PrepWs w, int L, int Lpad)
                         xb[i] = __float_as_uint(xf) >> 16;
                         n += (double)xf * (double)xf;
                     } else {
-                        const double x = TR::widen(e[i]);
+                        const double x = (double)e[i];
                         n += x * x;
                     }
                 }
@@ -278,32 +255,23 @@ density_prep(const typename TR::Elem *__restrict__ K, PrepWs w, int L, int Lpad)
             }
         }
         double x = -0.5 * n;
-        if constexpr (kBf16) {
-            uint32_t p[4];
+        uint32_t p[4];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                p[q] = bf16_rne((float)x);
-                x -= (double)__uint_as_float(p[q] << 16);
-            }
-            rec = make_uint4(p[0] | (p[1] << 16), p[2] | (p[3] << 16), 0x3F803F80u, 0x3F803F80u);
-        } else {
-            const float hi = (float)x;
-            const float lo = (float)(x - (double)hi);
-            rec = make_uint4(__float_as_uint(hi), __float_as_uint(lo), 0u, 0u);
+        for (int q = 0; q < 4; ++q) {
+            p[q] = bf16_rne((float)x);
+            x -= (double)__uint_as_float(p[q] << 16);
         }
+        rec = make_uint4(p[0] | (p[1] << 16), p[2] | (p[3] << 16), 0x3F803F80u, 0x3F803F80u);
     } else {
         // padded slot: -1e30 makes exp2() of the pair exactly 0
-        if constexpr (kBf16)
-            rec = make_uint4(bf16_rne(-1e30f), 0u, 0x3F803F80u, 0x3F803F80u);
-        else
-            rec = make_uint4(__float_as_uint(-1e30f), 0u, 0u, 0u);
+        rec = make_uint4(bf16_rne(-1e30f), 0u, 0x3F803F80u, 0x3F803F80u);
     }
     if (j < Lpad) {
         w.ext[(size_t)h * Lpad + j] = rec;
-        // the symmetric sweep's cell of a key starts at its self term, exactly 1 (in 32.32 fixed point): kept out of
+        // the cell of a key starts at its self term, exactly 1 (in 32.32 fixed point): kept out of
         // the fp32 row accumulators, where a 1 would swallow the many kernel values below its half ulp that make
         // up the rest of an isolated key's sum
-        if (w.acc) w.acc[(size_t)h * Lpad + j] = (j < L) ? (1ull << 32) : 0ull;
+        w.acc[(size_t)h * Lpad + j] = (j < L) ? (1ull << 32) : 0ull;
     }
     // sum of the block's squared norms, in a fixed order
     part[threadIdx.x] = n;
@@ -314,126 +282,6 @@ density_prep(const typename TR::Elem *__restrict__ K, PrepWs w, int L, int Lpad)
     }
     if (threadIdx.x == 0) w.nsum[(size_t)h * (Lpad / 256) + blockIdx.x] = part[0];
 }
-
-__global__ void __launch_bounds__(256)
-density_estimate(PrepWs w, int H, int L, int Lpad)
-{
-    const int h = blockIdx.x * 256 + threadIdx.x;
-    if (h >= H) return;
-    double t = 0.0;
-    for (int b = 0; b < Lpad / 256; ++b) t += w.nsum[(size_t)h * (Lpad / 256) + b];
-    // scale = log2(e) / sigma^2
-    const float est = (float)(1.1920928955078125e-7 * (t / (double)L) * ((double)w.scale[h] / 1.4426950408889634));
-    w.est[h] = est;
-    if (!(est <= kErrBound)) atomicExch(w.flag, 1);
-}
-
-// ------------------------------------------------------------------------------------------
-// Main sweep.
-// ------------------------------------------------------------------------------------------
-template <class TR, int D, int RT>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
-density_sweep(const void *const *__restrict__ kbase, const uint4 *__restrict__ ext,
-              const float *__restrict__ scale, float *__restrict__ rho, int L, int Lpad, int nRB, int total)
-{
-    typedef typename TR::Frag Frag;
-    typedef typename TR::Elem Elem;
-    constexpr int NK = D / TR::KSTEP;
-    constexpr int NS = NK + TR::NEXT;
-    constexpr int BM = RT * 32;
-    __shared__ float red[4][BM];
-
-    const int logical = xcd_contiguous(blockIdx.x, total);
-    const int h = logical / nRB;
-    const int rb = logical - h * nRB;
-    const Elem *Kh = reinterpret_cast<const Elem *>(kbase[h]);     // the caller's rows or their translated copy
-    const uint4 *exth = ext + (size_t)h * Lpad;
-    const float s = scale[h];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int n = lane & 31, hb = lane >> 5;
-
-    // A fragments: RT tiles of 32 rows, resident for the whole sweep
-    Frag a[RT][NS];
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-        const int row = rb * BM + rt * 32 + n;          // < Lpad
-        const Elem *rp = Kh + (size_t)min(row, L - 1) * D;
-#pragma unroll
-        for (int kk = 0; kk < NK; ++kk) a[rt][kk] = TR::load(rp, kk, hb);
-        const uint4 rec = exth[row];
-#pragma unroll
-        for (int e = 0; e < TR::NEXT; ++e) a[rt][NK + e] = TR::ext_a(rec, hb, e);
-    }
-
-    float racc[RT][16];
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) racc[rt][r] = 0.0f;
-
-    const int nCT = Lpad / 32;
-    Frag bcur[NS], bnxt[NS];
-    auto load_b = [&](Frag *b, int ct) {
-        const int col = ct * 32 + n;
-        const Elem *cp = Kh + (size_t)min(col, L - 1) * D;
-#pragma unroll
-        for (int kk = 0; kk < NK; ++kk) b[kk] = TR::load(cp, kk, hb);
-        const uint4 rec = exth[col];
-#pragma unroll
-        for (int e = 0; e < TR::NEXT; ++e) b[NK + e] = TR::ext_b(rec, hb, e);
-    };
-
-    int ct = wave;
-    if (ct < nCT) load_b(bcur, ct);
-    for (; ct < nCT; ct += 4) {
-        const bool more = ct + 4 < nCT;     // wave-uniform
-        if (more) load_b(bnxt, ct + 4);
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) {
-            f32x16_t acc;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
-#pragma unroll
-            for (int kk = 0; kk < NS; ++kk) acc = TR::mfma(a[rt][kk], bcur[kk], acc);
-            if (ct == rb * RT + rt) {
-                // diagonal tile: a key's distance to itself is exactly 0, whatever the rounding of
-                // the contraction says (the self term dominates rho for isolated keys)
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    if (8 * (r >> 2) + 4 * hb + (r & 3) == n) acc[r] = 0.0f;
-            }
-#pragma unroll
-            for (int r = 0; r < 16; ++r) racc[rt][r] += __builtin_amdgcn_exp2f(acc[r] * s);
-        }
-        if (more) {
-#pragma unroll
-            for (int kk = 0; kk < NS; ++kk) bcur[kk] = bnxt[kk];
-        }
-    }
-
-    // Row sums: lanes of one half-wave hold the 32 columns of the same rows.
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            float v = racc[rt][r];
-            v += __shfl_xor(v, 1);
-            v += __shfl_xor(v, 2);
-            v += __shfl_xor(v, 4);
-            v += __shfl_xor(v, 8);
-            v += __shfl_xor(v, 16);
-            if (n == 0) red[wave][rt * 32 + 8 * (r >> 2) + 4 * hb + (r & 3)] = v;
-        }
-    __syncthreads();
-    if (threadIdx.x < BM) {
-        const int row = rb * BM + threadIdx.x;
-        if (row < L) {
-            const float t = ((red[0][threadIdx.x] + red[1][threadIdx.x]) + red[2][threadIdx.x]) + red[3][threadIdx.x];
-            rho[(size_t)h * L + row] = t / (float)L;
-        }
-    }
-}
-
 
 // LDS-only barrier: waits for this wave's LDS traffic, not for its global loads
 __device__ __forceinline__ void lds_only_barrier()
@@ -478,6 +326,13 @@ __device__ __forceinline__ void wait_vmcnt()
 // MFMA operand layout (16-byte pieces, XOR-swizzled by row so the 8 lanes served per LDS cycle hit
 // 8 different bank groups; the swizzle is applied on the global side of the copy).  One LDS-only
 // barrier per stage publishes the stage and retires the buffer two stages back.
+//
+// The contraction runs one tile ahead of the vector work through the whole sweep, across tiles, stages and blocks: at two
+// (d = 128) or three (d = 64) waves per SIMD a contraction that stands alone at the head of a column tile is not hidden by
+// the other waves.  Against the form that started each column tile with its first contraction exposed: 20.5 -> 18.4 ms for
+// 8 heads of 131072 keys at d = 128 (matrix cores busy 46 -> 56 % of the cycles), 38.4 -> 37.8 ms for 384 heads of 32768
+// keys at d = 64.  One body serves the diagonal and the one-sided blocks too (they form column sums that are not used):
+// three copies of it do not fit the registers.
 // ------------------------------------------------------------------------------------------
 // The kernel sums of a key come from many workgroups (its own row block, and every block that visits it as
 // a column block).  They are accumulated in 32.32 fixed point with integer atomics: integer addition is
@@ -491,60 +346,58 @@ __device__ __forceinline__ void fixed_add(unsigned long long *cell, float v)
     __hip_atomic_fetch_add(cell, q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-template <int D, int RTW, bool BOTH, bool DIAG>
-__device__ __forceinline__ void sym_tile(const bf16x8_t (&a)[RTW][D / 16 + 1], const bf16x8_t (&b)[D / 16 + 1],
-                                         float (&racc)[RTW][16], float &csum, float s, int n, int hb,
-                                         int diag_rt /* row tile that meets this column tile, or -1 */)
+constexpr int kSymRtw = 2;                        // row tiles per wave of density_sym
+constexpr int kSymBm = 128 * kSymRtw;             // keys per block of density_sym ...
+constexpr int kSmallBm = 128, kSmallSc = 32;      // ... and of density_sym_small, and keys per stage there
+
+// Piece kk of this lane's row of a column tile: the row's pieces sit XOR-swizzled by the row's low three bits, so with the
+// byte of piece 0 in hand the others are an XOR (and an offset) away: one address register for all of them.
+__device__ __forceinline__ uint4 operand_piece(const uint4 *lds, unsigned at, int kk)
 {
-    constexpr int NS = D / 16 + 1;
-    // The contraction of row tile rt+1 is issued before the exponentials of row tile rt, one MFMA per
-    // slice of the vector work, so the matrix core runs under the vector pipe inside one wave.
-    f32x16_t acc[2];
+    return *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(lds) + (at ^ (unsigned)((kk & 3) * 32)) + (kk >> 2) * 128);
+}
+
+// One step of the pipelined sweep: the contraction of the next tile (row operand an, column operand b) into nxt, one
+// MFMA per slice of the vector work of the tile in cur.  diag: cur is a diagonal tile.  RELOAD: this is the last use of
+// the column operand; behind each MFMA its piece is fetched anew for the next column tile (piece 0 at byte `next` of lds,
+// record at ne), a whole step ahead of use and without a second set of registers.  The last three of the 16 values are
+// left behind the last MFMA, whose result the next step begins with.
+template <int NS, bool RELOAD>
+__device__ __forceinline__ void sym_step(const bf16x8_t (&an)[NS], bf16x8_t (&b)[NS], f32x16_t &nxt, f32x16_t &cur,
+                                         float (&racc)[16], float &csum, float s, int n, int hb, bool diag,
+                                         const uint4 *lds, unsigned next, const uint4 *ne)
+{
+    if (diag) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[0][r] = 0.0f;
+        for (int r = 0; r < 16; ++r)
+            if (8 * (r >> 2) + 4 * hb + (r & 3) == n) cur[r] = -1e30f;   // the self term is in the cell already
+    }
 #pragma unroll
-    for (int kk = 0; kk < NS; ++kk) acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0][kk], b[kk], acc[0], 0, 0, 0);
+    for (int r = 0; r < 16; ++r) nxt[r] = 0.0f;
 #pragma unroll
-    for (int rt = 0; rt < RTW; ++rt) {
-        f32x16_t &cur = acc[rt & 1], &nxt = acc[(rt + 1) & 1];
-        if (DIAG && rt == diag_rt) {
+    for (int kk = 0; kk < NS; ++kk) {
+        nxt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(an[kk], b[kk], nxt, 0, 0, 0);
+        if (RELOAD) b[kk] = __builtin_bit_cast(bf16x8_t, kk < NS - 1 ? operand_piece(lds, next, kk) : ne[0]);
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-                if (8 * (r >> 2) + 4 * hb + (r & 3) == n) cur[r] = -1e30f;   // the self term is in the cell already
+        for (int r = kk * 13 / NS; r < (kk < NS - 1 ? (kk + 1) * 13 / NS : 16); ++r) {
+            const float w = __builtin_amdgcn_exp2f(cur[r] * s);
+            racc[r] += w;
+            csum += w;
+            asm volatile("" : "+v"(racc[r]), "+v"(csum));      // or the adds gather behind the step, where no MFMA runs
         }
-        if (rt + 1 < RTW) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) nxt[r] = 0.0f;
-#pragma unroll
-            for (int kk = 0; kk < NS; ++kk) {
-                nxt = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[rt + 1][kk], b[kk], nxt, 0, 0, 0);
-#pragma unroll
-                for (int r = (kk * 16 + NS - 1) / NS; r < ((kk + 1) * 16 + NS - 1) / NS; ++r) {
-                    const float w = __builtin_amdgcn_exp2f(cur[r] * s);
-                    racc[rt][r] += w;
-                    if (BOTH) csum += w;
-                }
-                // keeps each MFMA between its shares of the vector work
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        } else {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float w = __builtin_amdgcn_exp2f(cur[r] * s);
-                racc[rt][r] += w;
-                if (BOTH) csum += w;
-            }
-        }
+        // keeps each MFMA between its shares of the vector work
+        __builtin_amdgcn_sched_barrier(0);
     }
 }
 
-template <int D, int RTW>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((D == 64 && RTW <= 2) ? 3 : 2, (D == 64 && RTW <= 2) ? 3 : 2)))
+template <int D>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(D == 64 ? 3 : 2, D == 64 ? 3 : 2)))
 density_sym(const void *const *__restrict__ kbase, const uint4 *__restrict__ ext, const float *__restrict__ scale,
-            unsigned long long *__restrict__ acc, int L, int Lpad, int nB, int nBoth, int head0, int total)
+            unsigned long long *__restrict__ acc, int L, int Lpad, int nB, int nBoth, int nblk, int parts, int head0, int total)
 {
     constexpr int NK = D / 16, NS = NK + 1;
-    constexpr int BM = 4 * RTW * 32;       // rows (and columns) per block
+    constexpr int RTW = kSymRtw;           // row tiles per wave
+    constexpr int BM = kSymBm;             // rows (and columns) per block
     constexpr int CH = D / 8;              // 16-byte pieces per key row
     constexpr int SC = 64;                 // key rows per LDS stage
     constexpr int SPB = BM / SC;           // stages per block
@@ -552,11 +405,14 @@ density_sym(const void *const *__restrict__ kbase, const uint4 *__restrict__ ext
     constexpr int NBUF = 3, PF = NBUF - 1;  // LDS buffers in rotation; stages the copies run ahead
     __shared__ uint4 sB[NBUF][SC * CH];
     __shared__ uint4 sE[NBUF][SC];
-    __shared__ float cs[4][2][BM];          // column sums of a block: per wave and half-wave
+    __shared__ float cs[2][4][2][BM];       // column sums of a visited block: per wave and half-wave
 
     const int logical = xcd_contiguous(blockIdx.x, total);
-    const int hl = logical / nB, I = logical - hl * nB;
+    // row block I of head h against the visited blocks j0 ... j1-1 of its nblk (see split_parts)
+    const int hI = logical / parts, part = logical - hI * parts;
+    const int hl = hI / nB, I = hI - hl * nB;
     const int h = head0 + hl;
+    const int j0 = (int)((long long)nblk * part / parts), j1 = (int)((long long)nblk * (part + 1) / parts);
     const uint16_t *Kh = reinterpret_cast<const uint16_t *>(kbase[h]);     // the caller's rows or their translated copy
     const uint4 *exth = ext + (size_t)h * Lpad;
     const float s = scale[h];
@@ -569,7 +425,7 @@ density_sym(const void *const *__restrict__ kbase, const uint4 *__restrict__ ext
         const int row = I * BM + (wave * RTW + rt) * 32 + n;      // < Lpad
         const uint16_t *rp = Kh + (size_t)min(row, L - 1) * D;
 #pragma unroll
-        for (int kk = 0; kk < NK; ++kk) a[rt][kk] = Bf16Tr::load(rp, kk, hb);
+        for (int kk = 0; kk < NK; ++kk) a[rt][kk] = load_frag(rp, kk, hb);
         // the record is {m1..m4, 1,1,1,1} with m1+..+m4 = -n/2: the column side uses it as it is, the row side
         // swaps its halves, so the extra k-step adds -n_i/2 - n_j/2.  Only the first 8 k-slots are used: the row
         // side holds zeros in the others, so what the column side holds there does not matter.
@@ -582,8 +438,7 @@ density_sym(const void *const *__restrict__ kbase, const uint4 *__restrict__ ext
 #pragma unroll
         for (int r = 0; r < 16; ++r) racc[rt][r] = 0.0f;
 
-    const int nblk = 1 + nBoth + ((nB > 1 && (nB & 1) == 0) ? 1 : 0);
-    const int nst = nblk * SPB;
+    const int nst = (j1 - j0) * SPB;
 
     // Key rows reach the LDS by asynchronous copies issued two stages ahead, already in the swizzled order the
     // MFMA operand reads expect (slot c of row r holds piece c ^ (r & 7)); three buffers rotate.
@@ -593,7 +448,7 @@ density_sym(const void *const *__restrict__ kbase, const uint4 *__restrict__ ext
     const int crow = tid / CH;
     const unsigned cpiece = (unsigned)(((tid % CH) ^ (crow & 7)) * 16);
     auto issue = [&](int sidx) {
-        const int J = (I + sidx / SPB) % nB;
+        const int J = (I + j0 + sidx / SPB) % nB;
         const int col0 = J * BM + (sidx % SPB) * SC;
         const int bi = sidx % NBUF;
 #pragma unroll
@@ -603,13 +458,6 @@ density_sym(const void *const *__restrict__ kbase, const uint4 *__restrict__ ext
         if (wave == 0) dma16(exth, (unsigned)(col0 + lane) * 16u, &sE[bi][0]);
     };
 
-    // LDS read positions of this lane: row n of a tile, the swizzled pieces of the NK k-steps
-    const int boff0 = n * CH;
-    int bpiece[NK];
-#pragma unroll
-    for (int kk = 0; kk < NK; ++kk) bpiece[kk] = (2 * kk + hb) ^ (n & 7);
-    float *csw = &cs[wave][hb][n];
-
     // The row operands must be in their registers before the first asynchronous copy is issued: the compiler
     // would otherwise wait for them at their first use inside the loop, with a count that also covers the copies.
     wait_vmcnt<0>();
@@ -617,49 +465,62 @@ density_sym(const void *const *__restrict__ kbase, const uint4 *__restrict__ ext
 #pragma unroll
     for (int p = 0; p < PF; ++p)
         if (p < nst) issue(p);
-    for (int sidx = 0; sidx < nst; ++sidx) {
-        const int buf = sidx % NBUF;
-        // this wave's copies of the stage have landed (those of the next stage may still be in flight) ...
+    // the column sums of a visited block go to its keys' cells (cs rotates by block: the next block's sums are written
+    // without another barrier)
+    auto flush = [&](int j) {
+        lds_only_barrier();
+        unsigned long long *dst = acc + (size_t)h * Lpad + (size_t)((I + j) % nB) * BM;
+        const float (*c2)[2][BM] = cs[j & 1];
+        for (int c = tid; c < BM; c += 256)
+            fixed_add(dst + c, ((c2[0][0][c] + c2[0][1][c]) + (c2[1][0][c] + c2[1][1][c])) +
+                                   ((c2[2][0][c] + c2[2][1][c]) + (c2[3][0][c] + c2[3][1][c])));
+    };
+    // this wave's copies of stage sidx have landed (those of the next stage may still be in flight), and so have
+    // everybody's; all waves are through with the stage before
+    auto arrive = [&](int sidx) {
         if (sidx + 1 < nst) {
             if (wave == 0) wait_vmcnt<NLD + 1>();
             else wait_vmcnt<NLD>();
         } else {
             wait_vmcnt<0>();
         }
-        // ... and so have everybody's; all waves are through with the stage before
         lds_only_barrier();
         if (sidx + PF < nst) issue(sidx + PF);
-        const int j = sidx / SPB, sin = sidx - j * SPB;
-        const bool both = j >= 1 && j <= nBoth;
-        const uint4 *sBb = sB[buf] + boff0;          // this lane's row n of the stage, tile 0
-        const uint4 *sEb = sE[buf] + n;
-#pragma unroll 1
-        for (int tt = 0; tt < SC / 32; ++tt) {
-            bf16x8_t b[NS];
+    };
+    const unsigned at0 = (unsigned)(n * CH + (hb ^ (n & 7))) * 16u;     // this lane's piece 0 in tile 0 of buffer 0
+    bf16x8_t b[NS];
+    f32x16_t c0, c1;
+    arrive(0);
 #pragma unroll
-            for (int kk = 0; kk < NK; ++kk) b[kk] = __builtin_bit_cast(bf16x8_t, sBb[tt * 32 * CH + bpiece[kk]]);
-            b[NK] = __builtin_bit_cast(bf16x8_t, sEb[tt * 32]);
-            float csum = 0.0f;
-            if (j == 0) {
-                // column tile index inside the block vs this wave's row tiles
-                const int ctile = sin * (SC / 32) + tt;
-                sym_tile<D, RTW, false, true>(a, b, racc, csum, s, n, hb, ctile - wave * RTW);
-            } else if (both) {
-                sym_tile<D, RTW, true, false>(a, b, racc, csum, s, n, hb, -1);
-                // each half-wave keeps its own partial sum (no cross-lane step, no branch)
-                csw[sin * SC + tt * 32] = csum;
-            } else {
-                sym_tile<D, RTW, false, false>(a, b, racc, csum, s, n, hb, -1);
-            }
-        }
-        if (both && sin == SPB - 1) {
-            __syncthreads();
-            const int J = (I + j) % nB;
-            unsigned long long *dst = acc + (size_t)h * Lpad + (size_t)J * BM;
-            for (int c = tid; c < BM; c += 256)
-                fixed_add(dst + c, ((cs[0][0][c] + cs[0][1][c]) + (cs[1][0][c] + cs[1][1][c])) +
-                                       ((cs[2][0][c] + cs[2][1][c]) + (cs[3][0][c] + cs[3][1][c])));
-        }
+    for (int kk = 0; kk < NK; ++kk) b[kk] = __builtin_bit_cast(bf16x8_t, operand_piece(&sB[0][0], at0, kk));
+    b[NK] = __builtin_bit_cast(bf16x8_t, sE[0][n]);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) c0[r] = 0.0f;
+#pragma unroll
+    for (int kk = 0; kk < NS; ++kk) c0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0][kk], b[kk], c0, 0, 0, 0);
+    for (int sidx = 0; sidx < nst; ++sidx) {
+        const int buf = sidx % NBUF;
+        const int j = j0 + sidx / SPB, sin = sidx % SPB;
+        const bool both = j >= 1 && j <= nBoth;
+        const bool diag = j == 0 && sin == wave;   // (RTW == SC / 32: the row tiles of a wave meet one stage)
+        unsigned next = at0 + (unsigned)(buf * SC + 32) * (CH * 16);
+        asm("" : "+v"(next));       // or every piece keeps an address register of its own from stage to stage
+        const uint4 *ne = sE[buf] + n + 32;
+        float csum = 0.0f;
+        sym_step<NS, true>(a[1], b, c1, c0, racc[0], csum, s, n, hb, diag, &sB[0][0], next, ne);
+        sym_step<NS, false>(a[0], b, c0, c1, racc[1], csum, s, n, hb, false, &sB[0][0], next, ne);
+        if (both) cs[j & 1][wave][hb][n + sin * SC] = csum;
+        csum = 0.0f;
+        // (behind the last stage the first tile of that stage is contracted once more, and not used)
+        if (sidx + 1 < nst) arrive(sidx + 1);
+        const int nbuf = sidx + 1 < nst ? (sidx + 1) % NBUF : buf;
+        next = at0 + (unsigned)(nbuf * SC) * (CH * 16);
+        asm("" : "+v"(next));
+        ne = sE[nbuf] + n;
+        sym_step<NS, true>(a[1], b, c1, c0, racc[0], csum, s, n, hb, false, &sB[0][0], next, ne);
+        sym_step<NS, false>(a[0], b, c0, c1, racc[1], csum, s, n, hb, diag, &sB[0][0], next, ne);
+        if (both) cs[j & 1][wave][hb][n + sin * SC + 32] = csum;
+        if (both && sin == SPB - 1) flush(j);
     }
 
     // each wave owns its rows: reduce over the 32 columns held by the lanes of a half-wave
@@ -678,28 +539,225 @@ density_sym(const void *const *__restrict__ kbase, const uint4 *__restrict__ ext
         }
 }
 
-// rho = accumulated kernel sum / L
+// ------------------------------------------------------------------------------------------
+// The same sweep for fp32 keys and for short heads: blocks of 128 keys, one 32-row tile per wave.
+//
+// fp32 keys.  Bound by the matrix cores.  The fp32 MFMA forms run at a sixteenth of the bf16 rate, so a key is split into
+// its three bf16 pieces (exactly: 24 bits) while a stage is brought to the LDS, and a product of two keys is the six
+// piece products above 2^-26 of it, the small ones summed first: 6 x d/16 + 1 MFMAs of 32 cycles per 32 x 32 tile (800
+// cycles at d = 64) against d/2 + 2 of 64 cycles (2176), and half the tiles.  The split costs 50 vector instructions per
+// wave and stage, which run beside the matrix work.
+//
+// A stage is 32 keys; its rows are loaded one stage ahead into registers and written to the other of two LDS buffers after
+// the stage's work, so there is one barrier per stage.  One fp32 head of 512 keys: the sweep 33 -> 8 us against one over all
+// ordered pairs with fp32 MFMAs.  Error against 64 bits there: 2.3e-7, with fp32 MFMAs 2.6e-7.
+// ------------------------------------------------------------------------------------------
+constexpr unsigned long long kNanCell = 1ull << 63;     // set in a cell that received a NaN (sums stay below 2^56)
+
+__device__ __forceinline__ void fixed_add_or_nan(unsigned long long *cell, float v)
+{
+    if (v == v) fixed_add(cell, v);
+    else __hip_atomic_fetch_or(cell, kNanCell, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <bool F32, int D>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((F32 && D == 128) ? 2 : 3, (F32 && D == 128) ? 2 : 3)))
+density_sym_small(const void *const *__restrict__ kbase, const uint4 *__restrict__ ext, const float *__restrict__ scale,
+                  unsigned long long *__restrict__ acc, int L, int Lpad, int nB, int nBoth, int nblk, int parts, int head0,
+                  int total)
+{
+    typedef typename std::conditional<F32, float, uint16_t>::type Elem;
+    constexpr int NP = F32 ? 3 : 1;         // bf16 pieces per element
+    constexpr int NK = D / 16;
+    constexpr int BM = kSmallBm, SC = kSmallSc, SPB = BM / SC;
+    constexpr int CR = D / 8;               // groups of eight elements per key row: 16 bytes of each piece
+    constexpr int CH = NP * CR;             // 16-byte pieces per LDS row
+    constexpr int NLD = SC * CR / 256;      // groups each thread brings in per stage
+    __shared__ uint4 sB[2][SC * CH];
+    __shared__ uint4 sE[2][SC];
+    __shared__ float cs[4][2][BM];          // column sums of a block: per wave and half-wave
+
+    const int logical = xcd_contiguous(blockIdx.x, total);
+    const int hI = logical / parts, part = logical - hI * parts;
+    const int hl = hI / nB, I = hI - hl * nB;
+    const int h = head0 + hl;
+    // row block I of head h against the visited stages s0 ... s1-1 of its nblk blocks (see split_parts)
+    const int s0 = (int)((long long)nblk * SPB * part / parts), s1 = (int)((long long)nblk * SPB * (part + 1) / parts);
+    const Elem *Kh = reinterpret_cast<const Elem *>(kbase[h]);
+    const uint4 *exth = ext + (size_t)h * Lpad;
+    const float s = scale[h];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 31, hb = lane >> 5;
+
+    bf16x8_t a[NP][NK], aext;
+    {
+        const int row = I * BM + wave * 32 + n;         // < Lpad
+        const Elem *rp = Kh + (size_t)min(row, L - 1) * D;
+#pragma unroll
+        for (int kk = 0; kk < NK; ++kk) {
+            if constexpr (F32) {
+                bf16x8_t p[3];
+                split3(*reinterpret_cast<const f32x8_16_t *>(rp + kk * 16 + hb * 8), p);
+#pragma unroll
+                for (int i = 0; i < 3; ++i) a[i][kk] = p[i];
+            } else {
+                a[0][kk] = load_frag(rp, kk, hb);
+            }
+        }
+        const uint4 rec = exth[row];
+        aext = __builtin_bit_cast(bf16x8_t, hb ? make_uint4(0, 0, 0, 0) : make_uint4(rec.z, rec.w, rec.x, rec.y));
+    }
+    float racc[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) racc[r] = 0.0f;
+
+    // group c of row r of a stage waits in slot c ^ (r & 7) of the row's pieces (8 lanes served per LDS cycle hit 8
+    // different bank groups)
+    typedef typename std::conditional<F32, f32x8_16_t, bf16x8_t>::type Group;
+    Group g[NLD];
+    uint4 grec;
+    auto fetch = [&](int sidx) {
+        const int col0 = ((I + sidx / SPB) % nB) * BM + (sidx % SPB) * SC;
+#pragma unroll
+        for (int i = 0; i < NLD; ++i) {
+            const int q = tid + 256 * i, r = q / CR, c = q % CR;
+            g[i] = *reinterpret_cast<const Group *>(Kh + (size_t)min(col0 + r, L - 1) * D + c * 8);
+        }
+        if (tid < SC) grec = exth[col0 + tid];
+    };
+    auto publish = [&](int buf) {
+#pragma unroll
+        for (int i = 0; i < NLD; ++i) {
+            const int q = tid + 256 * i, r = q / CR, c = q % CR;
+            uint4 *dst = &sB[buf][r * CH + (c ^ (r & 7))];
+            if constexpr (F32) {
+                bf16x8_t p[3];
+                split3(g[i], p);
+#pragma unroll
+                for (int k = 0; k < 3; ++k) dst[k * CR] = __builtin_bit_cast(uint4, p[k]);
+            } else {
+                dst[0] = __builtin_bit_cast(uint4, g[i]);
+            }
+        }
+        if (tid < SC) sE[buf][tid] = grec;
+    };
+
+    fetch(s0);
+    publish(s0 & 1);
+    for (int sidx = s0; sidx < s1; ++sidx) {
+        const int buf = sidx & 1;
+        __syncthreads();        // the stage is in; everybody is through with the other buffer
+        if (sidx + 1 < s1) fetch(sidx + 1);
+        const int j = sidx / SPB, sin = sidx % SPB;
+        const bool both = j >= 1 && j <= nBoth;
+        const uint4 *row = &sB[buf][n * CH];
+        auto piece = [&](int p, int kk) { return __builtin_bit_cast(bf16x8_t, row[p * CR + ((2 * kk + hb) ^ (n & 7))]); };
+        f32x16_t t;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) t[r] = 0.0f;
+        if constexpr (F32) {
+#pragma unroll
+            for (int kk = 0; kk < NK; ++kk) {
+                const bf16x8_t b0 = piece(0, kk), b1 = piece(1, kk), b2 = piece(2, kk);
+                t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[2][kk], b0, t, 0, 0, 0);
+                t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0][kk], b2, t, 0, 0, 0);
+                t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1][kk], b1, t, 0, 0, 0);
+                t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1][kk], b0, t, 0, 0, 0);
+                t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0][kk], b1, t, 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int kk = 0; kk < NK; ++kk) t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0][kk], piece(0, kk), t, 0, 0, 0);
+        t = __builtin_amdgcn_mfma_f32_32x32x16_bf16(aext, __builtin_bit_cast(bf16x8_t, sE[buf][n]), t, 0, 0, 0);
+        if (j == 0 && sin == wave) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                if (8 * (r >> 2) + 4 * hb + (r & 3) == n) t[r] = t[r] == t[r] ? -1e30f : t[r];   // the self term is in the cell already
+        }
+        float csum = 0.0f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const float w = __builtin_amdgcn_exp2f(t[r] * s);
+            racc[r] += w;
+            csum += w;
+        }
+        if (both) cs[wave][hb][sin * SC + n] = csum;
+        if (sidx + 1 < s1) publish(buf ^ 1);
+        if (both && (sin == SPB - 1 || sidx + 1 == s1)) {
+            __syncthreads();
+            const int first = max(s0 - j * SPB, 0) * SC;        // the part may have begun, or end, inside the block
+            unsigned long long *dst = acc + (size_t)h * Lpad + (size_t)((I + j) % nB) * BM;
+            if (tid >= first && tid < (sin + 1) * SC)
+                fixed_add_or_nan(dst + tid, ((cs[0][0][tid] + cs[0][1][tid]) + (cs[1][0][tid] + cs[1][1][tid])) +
+                                                ((cs[2][0][tid] + cs[2][1][tid]) + (cs[3][0][tid] + cs[3][1][tid])));
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const float v = lane_group_sum<32>(racc[r]);
+        if (n == 0) fixed_add_or_nan(acc + (size_t)h * Lpad + I * BM + wave * 32 + 8 * (r >> 2) + 4 * hb + (r & 3), v);
+    }
+}
+
+// rho = accumulated kernel sum / L; the first workgroup of a head also estimates the head's error
 __global__ void __launch_bounds__(256)
-density_finish(const unsigned long long *__restrict__ acc, float *__restrict__ rho, int L, int Lpad, int head0)
+density_finish(PrepWs w, float *__restrict__ rho, int L, int Lpad, int head0)
 {
     const int h = head0 + blockIdx.y;
     const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= L) return;
-    const double t = (double)acc[(size_t)h * Lpad + i] * (1.0 / 4294967296.0);
-    rho[(size_t)h * L + i] = (float)(t / (double)L);
+    if (i < L) {
+        const unsigned long long cell = w.acc[(size_t)h * Lpad + i];
+        const double t = (double)cell * (1.0 / 4294967296.0);
+        rho[(size_t)h * L + i] = cell & kNanCell ? __builtin_nanf("") : (float)(t / (double)L);
+    }
+    if (blockIdx.x != 0) return;
+    __shared__ double part[256];
+    double t = 0.0;
+    for (int b = threadIdx.x; b < Lpad / 256; b += 256) t += w.nsum[(size_t)h * (Lpad / 256) + b];
+    part[threadIdx.x] = t;
+    __syncthreads();
+    for (int o = 128; o >= 1; o >>= 1) {
+        if ((int)threadIdx.x < o) part[threadIdx.x] += part[threadIdx.x + o];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) {
+        // scale = log2(e) / sigma^2
+        const float est = (float)(1.1920928955078125e-7 * (part[0] / (double)L) * ((double)w.scale[h] / 1.4426950408889634));
+        w.est[h] = est;
+        if (!(est <= kErrBound)) atomicExch(w.flag, 1);
+    }
 }
 
 // A launch of the symmetric sweep takes at most this many heads.
 constexpr int kSymChunkHeads = 16384;
 
-constexpr int kSymRtw64 = 2, kSymRtw128 = 2;   // row tiles per wave
-static inline int sym_bm(int d) { return 128 * (d == 64 ? kSymRtw64 : kSymRtw128); }
-static inline bool use_sym(bool bf16, int L, int d) { return bf16 && (L + sym_bm(d) - 1) / sym_bm(d) >= 4; }
+static inline bool use_large(bool bf16, int L) { return bf16 && (L + kSymBm - 1) / kSymBm >= 4; }
+
+// How many workgroups share a row block's visited blocks.  Few heads of few blocks leave the chip idle with one workgroup
+// per row block (16 heads of 4096 keys, d = 64: 256 workgroups where 768 fit), so the visits (blocks in density_sym, stages
+// in density_sym_small) are cut into `parts` ranges: the count that makes rounds x visits per workgroup smallest, a
+// workgroup's start (row operands, first stage) priced at 0.35 blocks, or at two stages.  Launches of many rounds stay
+// whole: cutting them could only add starts.  The call of the example takes 76 us whole and 54 us in three parts.
+static int split_parts(long long wgs, int visits, long long resident, double start)
+{
+    int best = 1;
+    double cost = 1e300;
+    for (int p = 1; p <= visits && p <= 64; ++p) {
+        const long long rounds = (wgs * p + resident - 1) / resident;
+        const double c = (double)rounds * ((visits + p - 1) / p + start);
+        if (c < cost * 0.999) {
+            cost = c;
+            best = p;
+        }
+        if (wgs >= 16 * resident) break;
+    }
+    return best;
+}
 
 // ------------------------------------------------------------------------------------------
 struct DensityWs {
-    size_t est, scale, kbase, cand, cvec, stat, nsum, ext, kc, acc, total;
-    int Lpad, nB, nBoth;
+    size_t est, scale, kbase, cand, stat, full, nsum, ext, kc, acc, total;
+    int Lpad;
 };
 
 static DensityWs density_layout(int H, int L, int d, bool bf16)
@@ -715,9 +773,9 @@ static DensityWs density_layout(int H, int L, int d, bool bf16)
     o += round_up((size_t)H * sizeof(void *), 256);
     w.cand = o;
     o += round_up((size_t)H * sizeof(int), 256);
-    w.cvec = o;
-    o += round_up((size_t)H * d * sizeof(float), 256);
     w.stat = o;
+    if (bf16) o += round_up((size_t)H * kStatChunks * 3 * d * sizeof(float), 256);
+    w.full = o;
     if (bf16) o += round_up((size_t)H * kStatChunks * 3 * d * sizeof(float), 256);
     w.nsum = o;
     o += round_up((size_t)H * (w.Lpad / 256) * sizeof(double), 256);
@@ -726,12 +784,7 @@ static DensityWs density_layout(int H, int L, int d, bool bf16)
     w.kc = o;
     if (bf16) o += round_up((size_t)H * L * d * 2, 256);
     w.acc = o;
-    w.nB = w.nBoth = 0;
-    if (use_sym(bf16, L, d)) {
-        w.nB = w.Lpad / sym_bm(d);
-        w.nBoth = (w.nB - 1) / 2;
-        o += round_up((size_t)H * w.Lpad * sizeof(unsigned long long), 256);
-    }
+    o += round_up((size_t)H * w.Lpad * sizeof(unsigned long long), 256);
     w.total = o;
     return w;
 }
@@ -747,90 +800,65 @@ static PrepWs prep_pointers(const DensityWs &w, char *base)
     p.scale = reinterpret_cast<float *>(base + w.scale);
     p.kbase = reinterpret_cast<const void **>(base + w.kbase);
     p.cand = reinterpret_cast<int *>(base + w.cand);
-    p.cvec = reinterpret_cast<float *>(base + w.cvec);
     p.stat = reinterpret_cast<float *>(base + w.stat);
+    p.full = reinterpret_cast<float *>(base + w.full);
     p.nsum = reinterpret_cast<double *>(base + w.nsum);
     p.ext = reinterpret_cast<uint4 *>(base + w.ext);
     p.Kc = base + w.kc;
-    p.acc = w.nB ? reinterpret_cast<unsigned long long *>(base + w.acc) : nullptr;
+    p.acc = reinterpret_cast<unsigned long long *>(base + w.acc);
     return p;
 }
 
-template <class TR, int D>
-static void run_prep(const void *K, int H, int L, const float *sigma_host, const DensityWs &w, char *base,
-                     hipStream_t st)
+template <bool kBf16, int D>
+static void run_prep(const void *K, int H, int L, const float *sigma_host, const DensityWs &w, const PrepWs &p, hipStream_t st)
 {
-    typedef typename TR::Elem Elem;
-    constexpr bool kBf16 = sizeof(Elem) == 2;
-    const PrepWs p = prep_pointers(w, base);
-    for (int pass = 0; pass < (kBf16 ? 2 : 1); ++pass) {
-        if constexpr (kBf16) {
+    if constexpr (kBf16) {
+        for (int pass = 0; pass < 2; ++pass)
             for (int h0 = 0; h0 < H; h0 += 32768) {      // grid.y is 16 bits wide
                 const int nh = (H - h0 < 32768) ? H - h0 : 32768;
+                const size_t so = (size_t)h0 * kStatChunks * 3 * D;
                 hipLaunchKernelGGL((density_stats<D>), dim3(kStatChunks, nh), dim3(256), 0, st,
-                                   reinterpret_cast<const uint16_t *>(K) + (size_t)h0 * L * D,
-                                   p.stat + (size_t)h0 * kStatChunks * 3 * D, L, pass, p.cand + h0);
+                                   reinterpret_cast<const uint16_t *>(K) + (size_t)h0 * L * D, p.stat + so, p.full + so, L,
+                                   pass, p.cand + h0);
             }
-        }
-        for (int h0 = 0; h0 < H; h0 += 256) {
-            const int nh = (H - h0 < 256) ? H - h0 : 256;
-            ScaleChunk sc;
-            for (int i = 0; i < 256; ++i) {
-                // exponent scale log2(e)/sigma^2, so the sweep can use the hardware exp2
-                const double sg = (i < nh) ? (double)sigma_host[h0 + i] : 1.0;
-                sc.s[i] = (float)(1.4426950408889634 / (sg * sg));
-            }
-            hipLaunchKernelGGL((density_decide<D>), dim3(nh), dim3(D), 0, st, p, K, (size_t)L * D * sizeof(Elem), sc, h0,
-                               kBf16 ? 1 : 0);
-        }
     }
-    for (int h0 = 0; h0 < H; h0 += 32768) {      // grid.y is 16 bits wide
-        const int nh = (H - h0 < 32768) ? H - h0 : 32768;
-        PrepWs q = p;
-        q.cvec += (size_t)h0 * D;
-        q.kbase += h0;
-        q.nsum += (size_t)h0 * (w.Lpad / 256);
-        q.ext += (size_t)h0 * w.Lpad;
-        q.Kc = reinterpret_cast<char *>(q.Kc) + (size_t)h0 * L * D * sizeof(Elem);
-        if (q.acc) q.acc += (size_t)h0 * w.Lpad;
-        hipLaunchKernelGGL((density_prep<TR, D>), dim3(w.Lpad / 256, nh), dim3(256), 0, st,
-                           reinterpret_cast<const Elem *>(K) + (size_t)h0 * L * D, q, L, w.Lpad);
+    for (int h0 = 0; h0 < H; h0 += 256) {
+        const int nh = (H - h0 < 256) ? H - h0 : 256;
+        ScaleChunk sc;
+        for (int i = 0; i < 256; ++i) {
+            // exponent scale log2(e)/sigma^2, so the sweep can use the hardware exp2
+            const double sg = (i < nh) ? (double)sigma_host[h0 + i] : 1.0;
+            sc.s[i] = (float)(1.4426950408889634 / (sg * sg));
+        }
+        hipLaunchKernelGGL((density_prep<kBf16, D>), dim3(w.Lpad / 256, nh), dim3(256), 0, st, K, p, sc, h0, L, w.Lpad);
     }
-    hipLaunchKernelGGL(density_estimate, dim3((H + 255) / 256), dim3(256), 0, st, p, H, L, w.Lpad);
 }
 
-template <class TR, int D, int RT>
+template <bool kBf16, int D>
 static hipError_t run(const void *K, int H, int L, const float *sigma_host, float *rho, void *ws, hipStream_t st)
 {
-    typedef typename TR::Elem Elem;
-    const DensityWs w = density_layout(H, L, D, sizeof(Elem) == 2);
-    char *base = reinterpret_cast<char *>(ws);
-    run_prep<TR, D>(K, H, L, sigma_host, w, base, st);
-    const int BM = RT * 32;
-    const int nRB = (L + BM - 1) / BM;
-    const long long total = (long long)nRB * H;
-    if (total > 0x7FFFFFFFLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((density_sweep<TR, D, RT>), dim3((unsigned)total), dim3(256), 0, st,
-                       reinterpret_cast<const void *const *>(base + w.kbase), reinterpret_cast<const uint4 *>(base + w.ext),
-                       reinterpret_cast<const float *>(base + w.scale), rho, L, w.Lpad, nRB, (int)total);
-    return hipGetLastError();
-}
-
-template <int D, int RTW>
-static hipError_t run_sym(const void *K, int H, int L, const float *sigma_host, float *rho, void *ws, hipStream_t st)
-{
-    const DensityWs w = density_layout(H, L, D, true);
-    char *base = reinterpret_cast<char *>(ws);
-    run_prep<Bf16Tr, D>(K, H, L, sigma_host, w, base, st);
-    unsigned long long *acc = reinterpret_cast<unsigned long long *>(base + w.acc);
-    const int chunk = kSymChunkHeads;            // heads per launch (keeps the grid within 2^31 workgroups)
-    for (int h0 = 0; h0 < H; h0 += chunk) {
-        const int nh = (H - h0 < chunk) ? H - h0 : chunk;
-        const int total = nh * w.nB;
-        hipLaunchKernelGGL((density_sym<D, RTW>), dim3(total), dim3(256), 0, st,
-                           reinterpret_cast<const void *const *>(base + w.kbase), reinterpret_cast<const uint4 *>(base + w.ext),
-                           reinterpret_cast<const float *>(base + w.scale), acc, L, w.Lpad, w.nB, w.nBoth, h0, total);
-        hipLaunchKernelGGL(density_finish, dim3((L + 255) / 256, nh), dim3(256), 0, st, acc, rho, L, w.Lpad, h0);
+    const DensityWs w = density_layout(H, L, D, kBf16);
+    const PrepWs p = prep_pointers(w, reinterpret_cast<char *>(ws));
+    run_prep<kBf16, D>(K, H, L, sigma_host, w, p, st);
+    const bool large = use_large(kBf16, L);
+    const int bm = large ? kSymBm : kSmallBm;
+    const int nB = large ? w.Lpad / bm : (L + bm - 1) / bm, nBoth = (nB - 1) / 2;
+    const int nblk = 1 + nBoth + ((nB > 1 && (nB & 1) == 0) ? 1 : 0);
+    const int cus = current_chip().cus;
+    for (int h0 = 0; h0 < H; h0 += kSymChunkHeads) {
+        const int nh = (H - h0 < kSymChunkHeads) ? H - h0 : kSymChunkHeads;
+        const long long wgs = (long long)nh * nB;
+        if (wgs > 0x7FFFFFFFLL) return hipErrorInvalidValue;
+        const int per_cu = (large ? D == 128 : D == 128 && !kBf16) ? 2 : 3;      // as the kernels' waves_per_eu
+        const int parts = large ? split_parts(wgs, nblk, (long long)cus * per_cu, 0.35)
+                                : split_parts(wgs, nblk * (kSmallBm / kSmallSc), (long long)cus * per_cu, 2.0);
+        const int total = (int)(wgs * parts);
+        auto kern = density_sym_small<!kBf16, D>;
+        if constexpr (kBf16)
+            if (large) kern = density_sym<D>;
+        hipLaunchKernelGGL(kern, dim3(total), dim3(256), 0, st, p.kbase, p.ext, p.scale, p.acc, L, w.Lpad, nB, nBoth, nblk,
+                           parts, h0, total);
+        hipLaunchKernelGGL(density_finish, dim3((L + 255) / 256, nh), dim3(256), 0, st, p, rho, L, w.Lpad, h0);
     }
     return hipGetLastError();
 }
@@ -838,21 +866,12 @@ static hipError_t run_sym(const void *K, int H, int L, const float *sigma_host, 
 hipError_t launch_density(const void *K, bool bf16, int H, int L, int d, const float *sigma_host, float *rho,
                           void *ws, hipStream_t st)
 {
-    if (bf16) {
-        if (use_sym(true, L, d)) {
-            if (d == 64) return run_sym<64, kSymRtw64>(K, H, L, sigma_host, rho, ws, st);
-            if (d == 128) return run_sym<128, kSymRtw128>(K, H, L, sigma_host, rho, ws, st);
-        }
-        if (d == 64) return run<Bf16Tr, 64, 4>(K, H, L, sigma_host, rho, ws, st);
-        if (d == 128) return run<Bf16Tr, 128, 2>(K, H, L, sigma_host, rho, ws, st);
-    } else {
-        if (d == 64) return run<F32Tr, 64, 2>(K, H, L, sigma_host, rho, ws, st);
-        if (d == 128) return run<F32Tr, 128, 1>(K, H, L, sigma_host, rho, ws, st);
-    }
+    if (d == 64) return (bf16 ? run<true, 64> : run<false, 64>)(K, H, L, sigma_host, rho, ws, st);
+    if (d == 128) return (bf16 ? run<true, 128> : run<false, 128>)(K, H, L, sigma_host, rho, ws, st);
     return hipErrorInvalidValue;
 }
 
-// which sweep serves these sizes (for reports): 1 = symmetric, 0 = full
-bool density_uses_symmetric(bool bf16, int L, int d) { return use_sym(bf16, L, d); }
+// which sweep serves these sizes (for reports): 1 = every unordered pair once
+bool density_uses_symmetric(bool, int, int) { return true; }
 
 }  // namespace ws

@@ -1,0 +1,51 @@
+"""The density at the sizes where its two sweeps change hands or run short: edges of the 32-row tiles, of the 128- and
+256-key blocks, odd and even block counts (with an even count the block half way round is visited from both sides), counts
+at which several workgroups share a row block's visits; and a NaN key, which reaches every density of its head."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+# the density tolerances of the parity tests: 2^-23 |k|^2 / sigma^2 per kernel term, about 2e-6 at this bandwidth
+TOL = {"bf16": 5e-5, "f32": 1e-5}
+
+
+@pytest.fixture(scope="module")
+def ws():
+    from paper_2601_01298_amd import binding
+    binding.lib()
+    return binding
+
+
+def cloud(H, L, d, dtype, seed):
+    from paper_2601_01298_amd import synthetic as syn
+    rng = np.random.default_rng(seed)
+    centres = 2.0 * rng.standard_normal((H, 8, d))
+    pick = rng.integers(0, 8, (H, L))
+    K = (np.take_along_axis(centres, pick[:, :, None], axis=1) + 0.5 * rng.standard_normal((H, L, d))).astype(np.float32)
+    return syn.round_to_bf16(K) if dtype == "bf16" else K
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("L", [1, 2, 33, 128, 129, 256, 384, 511, 768, 769, 1024, 1281, 2305])
+def test_density_block_edges(ws, L, d, dtype):
+    import torch
+    from oracle import ws_oracle as oracle
+    H = 2
+    K = cloud(H, L, d, dtype, 1000 * d + L)
+    sigma = [float(np.float32(np.sqrt(max(K[h].var(axis=0).sum(), 1.0) / 16))) for h in range(H)]
+    Kd = torch.from_numpy(K).to(torch.bfloat16 if dtype == "bf16" else torch.float32).cuda()
+    rho = ws.ws_synapse_density(Kd, sigma).cpu().numpy()
+    for h in range(H):
+        ref = oracle.density(K[h], sigma[h])
+        assert np.abs(rho[h] / ref - 1).max() <= TOL[dtype]
+
+
+@pytest.mark.parametrize("L,dtype", [(200, "f32"), (2100, "f32"), (500, "bf16")])
+def test_nan_key_reaches_its_head(ws, L, dtype):
+    import torch
+    K = torch.from_numpy(cloud(2, L, 64, dtype, L)).to(torch.bfloat16 if dtype == "bf16" else torch.float32).cuda()
+    K[1, L // 3, 5] = float("nan")
+    rho = ws.ws_synapse_density(K, [3.0, 3.0])
+    assert torch.isfinite(rho[0]).all() and torch.isnan(rho[1]).all()
