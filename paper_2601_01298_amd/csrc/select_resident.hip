@@ -21,8 +21,8 @@
 // two maxima over all keys of the head, the second depending on the first: D_max, then the best
 // score alpha*D/D_max + (1-alpha)*u.  D_max rarely changes from one step to the next (the far
 // point that sets it stays uncovered for long stretches), so every workgroup scores its keys with
-// the PREVIOUS step's D_max and sends its local D maximum and its candidate in ONE exchange; only
-// when the new D_max differs from the guess are the candidates recomputed and exchanged again
+// the PREVIOUS step's D_max (less the key picked there, if that was the far point) and sends its
+// local D maximum and its candidate in ONE exchange; only when the new D_max differs from the guess are the candidates recomputed and exchanged again
 // (same arithmetic either way, so the picks do not depend on the guess).  An exchange reduces in
 // three levels: lanes of a wave with DPP row operations, the waves of a workgroup through LDS, and
 // the workgroups of the head through two tagged 64-bit slots each in global memory, posted and
@@ -39,8 +39,8 @@ namespace {
 using namespace resident;
 
 struct Shared {
-    unsigned dm[4], hi[4], lo[4];   // one entry per wave of the workgroup
-    unsigned rdm, rhi, rlo;         // result of the exchange
+    unsigned dm[4], dx[4], hi[4], lo[4];   // one entry per wave of the workgroup
+    unsigned rdm, rdx, rhi, rlo;           // result of the exchange
     int abort;
 };
 
@@ -48,6 +48,9 @@ struct Shared {
 //   dm        a 32-bit value (D_max as float bits, or any other unsigned quantity);
 //   (hi, lo)  a candidate compared as one 64-bit number, lo with its low 8 bits clear
 //             (score bits, then the complemented index so that the lowest index wins ties).
+// FAR: dx is dm without the wave's candidate, looked at only where lo carries kSetsMax (the candidate sets dm); dx_out is
+// what dm_out becomes when the winner is taken away (a maximum that falls below a quarter of itself is reported as dm_out):
+// what the next step's D_max is unless the new landmark lowers it.
 // Three levels: lanes of a wave (done by the caller, the inputs are wave-uniform), the 4 waves of a
 // workgroup through LDS, the workgroups of the head through two tagged 64-bit slots each in global
 // memory.  Only wave 0 of a workgroup touches the slots: lanes 0 and 1 post, lane j polls slot A of
@@ -55,14 +58,15 @@ struct Shared {
 // the L2 instead of (4 nwg)^2 * 16.  With `prefetch`, wave 0 touches the key row of this workgroup's
 // candidate after posting, so that it is in this die's L2 when the winner is fetched.
 // Returns false (for every thread of the workgroup) if the bounded wait expired.
-template <bool WIDE>
-__device__ __forceinline__ bool head_max(unsigned dm, unsigned hi, unsigned lo, Shared &sh, unsigned long long *gslots,
-                                         int nwg, int member, unsigned &seq, unsigned &dm_out, unsigned &hi_out,
+template <bool WIDE, bool FAR>
+__device__ __forceinline__ bool head_max(unsigned dm, unsigned dx, unsigned hi, unsigned lo, Shared &sh, unsigned long long *gslots,
+                                         int nwg, int member, unsigned &seq, unsigned &dm_out, unsigned &dx_out, unsigned &hi_out,
                                          unsigned &lo_out, const uint16_t *pf_base, int D, int last_row, bool prefetch)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (lane == 0) {
         sh.dm[wave] = dm;
+        if (FAR && (lo & kSetsMax)) sh.dx[wave] = dx;
         sh.hi[wave] = hi;
         sh.lo[wave] = lo;
     }
@@ -77,6 +81,14 @@ __device__ __forceinline__ bool head_max(unsigned dm, unsigned hi, unsigned lo, 
         unsigned ml = 0u;
 #pragma unroll
         for (int w = 0; w < 4; ++w) ml = max(ml, sh.hi[w] == mh ? sh.lo[w] : 0u);
+        // what the maximum is without the candidate
+        unsigned mx = md;
+        if (FAR && (__builtin_amdgcn_readfirstlane(ml) & kSetsMax)) {
+            mx = 0u;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) mx = max(mx, sh.hi[w] == mh && sh.lo[w] == ml ? sh.dx[w] : sh.dm[w]);
+            if (mx == md) ml &= ~kSetsMax;
+        }
         bool good = true;
         if (nwg > 1) {
             ++seq;
@@ -87,11 +99,11 @@ __device__ __forceinline__ bool head_max(unsigned dm, unsigned hi, unsigned lo, 
             // whole step loop they would be spilled and reloaded on this, the latency-critical path.
             int ln = lane;
             asm volatile("" : "+v"(ln));
-            post_words(slot, MS, member, ln, md, mh, ml, tag);
+            post_words(slot, MS, member, ln, md, mh, ml, tag, FAR ? min(md - mx, 0xFFFFFFu) : 0u);
             unsigned touched = 0u;
             if (prefetch && ln < D / 8) {
-                // candidate index travels in bits 8..31 of lo, complemented
-                const int cand = min((int)(0xFFFFFFu - (ml >> 8)), last_row);
+                // candidate index travels in bits 9..31 of lo, complemented
+                const int cand = min((int)(0x7FFFFFu - (ml >> 9)), last_row);
                 touched = *reinterpret_cast<const volatile unsigned *>(pf_base + (size_t)cand * D + ln * 8);
             }
             const int who = ln & 31, kind = ln >> 5;
@@ -130,10 +142,20 @@ __device__ __forceinline__ bool head_max(unsigned dm, unsigned hi, unsigned lo, 
             if (who >= nwg || !good) g = 0ull;
             const unsigned gh = (unsigned)(g >> 32), gl = (unsigned)g & 0xFFFFFF00u;
             fold_polled(gh, gl, ln, md, mh, ml);
+            // D_max without the winner: its workgroup's word falls by the drop it carries
+            mx = md;
+            if (FAR && (ml & kSetsMax)) {
+                const unsigned long long won = __ballot(kind == 1 && gh == mh && gl == ml);
+                const int wl = won ? (int)__builtin_ctzll(won) & 31 : 0;
+                const unsigned wd = (unsigned)__builtin_amdgcn_readlane((int)gh, wl);
+                const unsigned drop = (unsigned)__builtin_amdgcn_readlane((int)gl, wl) >> 8;
+                if (wd == md && drop != 0xFFFFFFu) mx = wave_umax(ln < 32 ? (ln == wl ? gh - drop : gh) : 0u);
+            }
             if (touched == 0xFFFFFFFFu && seq == 0u) good = false;   // never true: keeps the touch alive
         }
         if (lane == 0) {
             sh.rdm = md;
+            if (FAR) sh.rdx = mx;
             sh.rhi = mh;
             sh.rlo = ml;
             if (!good) sh.abort = 1;
@@ -141,9 +163,143 @@ __device__ __forceinline__ bool head_max(unsigned dm, unsigned hi, unsigned lo, 
     }
     __syncthreads();
     dm_out = sh.rdm;
+    dx_out = FAR ? sh.rdx : dm_out;
     hi_out = sh.rhi;
     lo_out = sh.rlo;
     return sh.abort == 0;
+}
+
+// ---- exact distances for the keys a new landmark may move ------------------------------------------------------
+// As exact_update of the common header, for clouds in which more than a key or two per wave and step move (a twelfth of
+// all keys where isolated keys are picked first): eight lanes share a staged key, so a pass evaluates eight keys; the
+// square root is taken by the keys' owners, one per row slot; and a row slot whose keys no longer fit the strip waits
+// until the keys in it are evaluated.  Only a slot with more than CAP moving keys is evaluated whole, each lane its own
+// key.  Per wave, d = 128, a whole slot costs about 1650 cycles of vector work, a pass of eight keys about 300.
+// landmark: the landmark row in memory; early: this lane's pieces of it, where the registers allow to load them before the
+// screen (no rows in LDS).
+template <int D, int RREG, int RLDS, int CAP>
+__device__ __forceinline__ unsigned exact_groups(const uint32_t (&kr)[RREG > 0 ? RREG : 1][D / 2], const uint4 *lrows,
+                                                 const uint32_t (&lws)[D / 2], float (&Dv)[RREG + RLDS], unsigned needmask,
+                                                 unsigned rowmask, uint32_t *stage, float *sres, int tid, int lane,
+                                                 const uint16_t *landmark, const uint4 (&early)[D / 64], unsigned sh16, unsigned mhi16)
+{
+    constexpr int R = RREG + RLDS;
+    constexpr int DW = D / 2;          // packed bf16 pairs per key row
+    constexpr int NV = D / 8;          // 16-byte pieces per key row
+    constexpr int NP = NV / 8;         // pieces of a staged key per lane
+    static_assert(CAP % 8 == 0, "whole passes");
+    rowmask = __builtin_amdgcn_readfirstlane(rowmask);
+    if (rowmask != 0u) {
+        int ln = lane;                 // lane-derived addresses are rebuilt here: kept across steps they would be spilled
+        asm volatile("" : "+v"(ln));
+        const int sub = ln >> 3, part = ln & 7;
+        uint4 lq[NP];
+#pragma unroll
+        for (int i = 0; i < NP; ++i) lq[i] = RLDS > 0 ? reinterpret_cast<const uint4 *>(landmark)[i * 8 + part] : early[i];
+        int base = 0;                  // staged keys
+        unsigned pm0 = 0u, pm1 = 0u;   // per row slot, 1 + the staging position of this lane's key
+        unsigned stmask = 0u;          // bit r: row slot r has keys in the strip (wave-uniform)
+        auto evaluate = [&]() {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            for (int q0 = 0; q0 < base; q0 += 8) {
+                float acc = 0.0f;
+#pragma unroll
+                for (int i = 0; i < NP; ++i) {
+                    const uint4 k = *reinterpret_cast<const uint4 *>(&stage[(q0 + sub) * DW + (i * 8 + part) * 4]);
+                    const uint32_t kw[4] = {k.x, k.y, k.z, k.w}, lw[4] = {lq[i].x, lq[i].y, lq[i].z, lq[i].w};
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const float d0 = __uint_as_float(kw[j] << 16) - __uint_as_float(lw[j] << 16);
+                        const float d1 = __uint_as_float(kw[j] & 0xFFFF0000u) - __uint_as_float(lw[j] & 0xFFFF0000u);
+                        acc = fmaf(d0, d0, acc);
+                        acc = fmaf(d1, d1, acc);
+                    }
+                }
+                acc = lane_group_sum<8>(acc);
+                if (part == 0) sres[q0 + sub] = acc;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                if (stmask & (1u << r)) {
+                    const unsigned pb = ((r < 4 ? pm0 : pm1) >> (8 * (r & 3))) & 0xFFu;
+                    const float dn = __fsqrt_rn(sres[pb ? pb - 1 : 0]);
+                    if (pb) Dv[r] = fminf(Dv[r], dn);    // chosen keys stay at -1
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        };
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (!(rowmask & (1u << r))) continue;
+            const bool need = (needmask >> r) & 1u;
+            const unsigned long long bal = __ballot(need);
+            const int cnt = __popcll(bal);
+            if (cnt <= CAP) {
+                if (r > 0 && cnt > CAP - base) {
+                    evaluate();
+                    base = 0;
+                    pm0 = pm1 = stmask = 0u;
+                }
+                stmask |= 1u << r;
+                const int pos = base + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(bal >> 32),
+                                                                      __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
+                base += cnt;
+                if (need) {
+#pragma unroll
+                    for (int c = 0; c < NV; ++c) {
+                        uint4 q;
+                        if (r < RREG) {
+                            q = make_uint4(kr[r < RREG ? r : 0][4 * c], kr[r < RREG ? r : 0][4 * c + 1],
+                                           kr[r < RREG ? r : 0][4 * c + 2], kr[r < RREG ? r : 0][4 * c + 3]);
+                        } else {
+                            q = lrows[((r - RREG) * NV + c) * 256 + tid];
+                        }
+                        *reinterpret_cast<uint4 *>(&stage[pos * DW + 4 * c]) = q;
+                        if (r >= RREG) __builtin_amdgcn_sched_barrier(0);
+                    }
+                    if (r < 4) pm0 |= (unsigned)(pos + 1) << (8 * (r & 3));
+                    else pm1 |= (unsigned)(pos + 1) << (8 * (r & 3));
+                }
+            } else {
+                float acc = 0.0f;
+#pragma unroll
+                for (int c = 0; c < NV; ++c) {
+                    uint32_t w4[4];
+                    if (r < RREG) {
+                        w4[0] = kr[r < RREG ? r : 0][4 * c];
+                        w4[1] = kr[r < RREG ? r : 0][4 * c + 1];
+                        w4[2] = kr[r < RREG ? r : 0][4 * c + 2];
+                        w4[3] = kr[r < RREG ? r : 0][4 * c + 3];
+                    } else {
+                        const uint4 q = lrows[((r - RREG) * NV + c) * 256 + tid];
+                        w4[0] = q.x;
+                        w4[1] = q.y;
+                        w4[2] = q.z;
+                        w4[3] = q.w;
+                    }
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const uint32_t wd = lws[4 * c + j];
+                        const float d0 = __uint_as_float(w4[j] << sh16) - __uint_as_float(wd << 16);
+                        acc = fmaf(d0, d0, acc);
+                        const float d1 = __uint_as_float(w4[j] & mhi16) - __uint_as_float(wd & 0xFFFF0000u);
+                        acc = fmaf(d1, d1, acc);
+                    }
+                    if (r >= RREG) __builtin_amdgcn_sched_barrier(0);
+                }
+                Dv[r] = fminf(Dv[r], __fsqrt_rn(acc));    // chosen keys stay at -1
+            }
+        }
+        if (base > 0) evaluate();
+    }
+    float lmax = 0.0f;
+#pragma unroll
+    for (int r = 0; r < R; ++r) lmax = fmaxf(lmax, Dv[r]);
+    return wave_umax(__float_as_uint(lmax));
 }
 
 template <int D, int RREG, int RLDS, bool WIDE>
@@ -155,13 +311,21 @@ select_resident(ResArgs a)
     constexpr int NV = DW / 4;     // 16-byte pieces per key row
     __shared__ uint4 lrows[RLDS > 0 ? RLDS * NV * 256 : 1];
     __shared__ float nrm[R * 256];     // squared norm of every resident key (private to its thread)
-    constexpr int LPK = DW / 2;              // lanes that share one staged key: 2 packed words (4 elements) each
-    constexpr int KPP = 64 / LPK;            // staged keys a wave evaluates per pass (d = 64: four, d = 128: two)
-    constexpr int CAP = (D == 64) ? 12 : 8;  // keys a wave can stage per step
-    static_assert(CAP % KPP == 0, "whole passes");
+    // Clouds with isolated keys pick the far point at most steps and move many keys per step: the instances with more than
+    // one row slot, or rows of 128, carry D_max without the winner through the exchange (a second exchange in 17 % of the
+    // steps of 32 heads of 8192 keys with 1 % outliers, d = 128, against 65 %) and evaluate staged keys in groups
+    // (exact_groups): 924 -> 799 us there, 2409 -> 2102 us for 32 heavy-tailed heads of 16384 keys, within 1 % on clustered
+    // clouds.  With one slot of 64 elements the step is so short that what this adds to it shows: a clustered cloud of 16
+    // heads of 4096 keys 209 -> 223 us (a heavy-tailed one 290 -> 244); that instance does without.  So do the wide ones: four
+    // polled words a lane leave no room for it (4 clustered heads of 65536 keys, d = 128, 1430 -> 1455 ... 1621 us).
+    constexpr bool FAR = !WIDE && (R > 1 || D == 128);
+    // keys a wave can stage at a time (where rows sit in LDS too, there is room for 8)
+    constexpr int CAP = !FAR ? (D == 64 ? 12 : 8) : RLDS > 0 ? 8 : 32;
     __shared__ __align__(16) uint32_t stage_all[4][CAP * DW];   // per wave: the packed rows of the staged keys
     __shared__ float sres_all[4][CAP];                          // per wave: the staged keys' exact distances
     __shared__ Shared sh;
+    // two workgroups share a compute unit: the launch shapes count on it
+    static_assert(sizeof(lrows) + sizeof(nrm) + sizeof(stage_all) + sizeof(sres_all) + sizeof(sh) <= 80 * 1024, "half of the LDS");
 
     // Workgroup ids are dealt to the 8 dies round-robin.  With a multiple of 8 heads in flight every head sits on one
     // die; with 1, 2 or 4 a head takes 8, 4 or 2 whole dies (a 32 MiB head needs the registers and LDS of two).
@@ -259,9 +423,9 @@ select_resident(ResArgs a)
             if (row < a.L) rmin = fminf(rmin, rh[r]);
         }
         {
-            unsigned mdm, mhi, mlo;
+            unsigned mdm, mdx, mhi, mlo;
             const unsigned mine = wave_umax(0xFFFFFFFFu - __float_as_uint(rmin));
-            if (!head_max<WIDE>(mine, 0u, 0u, sh, gslots, a.wgpg, member, seq, mdm, mhi, mlo, Kh, D, a.L - 1, false)) goto bail;
+            if (!head_max<WIDE, FAR>(mine, mine, 0u, 0u, sh, gslots, a.wgpg, member, seq, mdm, mdx, mhi, mlo, Kh, D, a.L - 1, false)) goto bail;
             rmin = __uint_as_float(0xFFFFFFFFu - mdm);
         }
 #pragma unroll
@@ -284,8 +448,12 @@ select_resident(ResArgs a)
                     typedef const uint32_t __attribute__((address_space(4))) *cptr_t;
                     const cptr_t lp = (cptr_t)(uintptr_t)(Kh + (size_t)prev * D);
                     // its squared norm: one packed pair per lane, summed over the wave
-                    // (lane l also keeps pair l mod D/2 of the landmark for the staged evaluation below)
                     const uint32_t lmw = reinterpret_cast<const uint32_t *>(Kh + (size_t)prev * D)[lane % DW];
+                    uint4 early[D / 64];     // and 16-byte pieces of it for the exact evaluation, if there is room for them
+#pragma unroll
+                    for (int i = 0; i < D / 64; ++i)
+                        early[i] = RLDS > 0 || !FAR ? make_uint4(0, 0, 0, 0)
+                                            : reinterpret_cast<const uint4 *>(Kh + (size_t)prev * D)[i * 8 + (lane & 7)];
                     const int wvl = tid >> 6;
                     // Exact evaluation widens the packed bf16 pairs on the fly.  Shift count and mask go
                     // through an empty asm so the compiler cannot treat the widened values as loop-invariant
@@ -320,7 +488,7 @@ select_resident(ResArgs a)
                     unsigned needmask = 0u;          // bit r: this lane's key of row slot r may move
                     unsigned rowmask = 0u;           // bit r: some key of row slot r may move (wave-uniform)
                     float ns = 0.0f;                 // squared norm of the landmark (set once its pair has arrived)
-                    uint32_t lmo = 0u;
+                    uint32_t lmo = 0u;               // for exact_update: the other packed word of the landmark
                     constexpr bool MIX = RLDS > 0;   // groups of 3 + 1
                     constexpr int NG = MIX ? RLDS : (R + 3) / 4;
                     static_assert(!MIX || (RREG == 3 * RLDS), "a group is three register rows and one LDS row");
@@ -382,7 +550,7 @@ select_resident(ResArgs a)
                                 nsp = __builtin_amdgcn_fdot2_f32_bf16(lw, lw, 0.0f, false);
                             }
                             ns = wave_fsum(nsp);
-                            lmo = (uint32_t)__shfl_xor((int)lmw, LPK);   // for the staged evaluation: the other packed word
+                            if (!FAR) lmo = (uint32_t)__shfl_xor((int)lmw, DW / 2);
                         }
 #pragma unroll
                         for (int rr = 0; rr < 4; ++rr) {
@@ -397,8 +565,12 @@ select_resident(ResArgs a)
                             }
                         }
                     }
-                    lbits = exact_update<D, RREG, RLDS, CAP>(kr, lrows, lws, Dv, needmask, rowmask, stage_all[wvl], sres_all[wvl], tid,
-                                                            lane, lmw, lmo, sh16, mhi16);
+                    if constexpr (FAR)
+                        lbits = exact_groups<D, RREG, RLDS, CAP>(kr, lrows, lws, Dv, needmask, rowmask, stage_all[wvl],
+                                                                 sres_all[wvl], tid, lane, Kh + (size_t)prev * D, early, sh16, mhi16);
+                    else
+                        lbits = exact_update<D, RREG, RLDS, CAP>(kr, lrows, lws, Dv, needmask, rowmask, stage_all[wvl],
+                                                                 sres_all[wvl], tid, lane, lmw, lmo, sh16, mhi16);
                 }
 
                 int s;
@@ -408,13 +580,13 @@ select_resident(ResArgs a)
                     sc = alpha;
                 } else {
                     // ---- score = alpha * D/D_max + (1-alpha) * u ; keys in ascending order per lane.
-                    // First with the D_max of the previous step (step 0: coverage term 1 for every key),
-                    // sent together with this step's local D maximum; again only if D_max moved.
-                    unsigned mdm = 0u, mhi = 0u, mlo = 0u;
+                    // First with the D_max the previous step leaves behind its pick (step 0: coverage term 1 for
+                    // every key), sent together with this step's local D maximum; again only if D_max is another.
+                    unsigned mdm = 0u, mdx = 0u, mhi = 0u, mlo = 0u;
                     for (int pass = 0; pass < 2; ++pass) {
                         const float dmax = __uint_as_float(dprev);
                         const float ainv = (t == 0) ? alpha : (dmax > 0.0f ? alpha / dmax : 0.0f);
-                        float best = -1.0f;
+                        float best = -1.0f, bd = 0.0f;
                         int bi = 0;
 #pragma unroll
                         for (int r = 0; r < R; ++r) {
@@ -423,18 +595,32 @@ select_resident(ResArgs a)
                             if (v > best) {
                                 best = v;
                                 bi = rowbase + rstride * r;
+                                bd = Dv[r];
                             }
                         }
                         const unsigned chi = best >= 0.0f ? __float_as_uint(best) : 0u;
-                        const unsigned clo = best >= 0.0f ? (0xFFFFFFu - (unsigned)bi) << 8 : 0u;
+                        const unsigned clo = best >= 0.0f ? (0x7FFFFFu - (unsigned)bi) << 9 : 0u;
                         const unsigned whi = wave_umax(chi);
                         const unsigned wlo = wave_pick_lo(chi == whi, clo);
-                        if (!head_max<WIDE>(lbits, whi, wlo, sh, gslots, a.wgpg, member, seq, mdm, mhi, mlo, Kh, D, a.L - 1, true))
+                        // The wave's D maximum without its candidate: of use only where the candidate sets what is
+                        // taken for the head's D_max.
+                        unsigned xbits = lbits, flag = 0u;
+                        const bool top = chi == whi && clo == wlo;
+                        if (FAR && lbits == dprev && __any(top && __float_as_uint(bd) == lbits)) {
+                            flag = kSetsMax;
+                            float m = 0.0f;
+#pragma unroll
+                            for (int r = 0; r < R; ++r) m = fmaxf(m, top && rowbase + rstride * r == bi ? 0.0f : Dv[r]);
+                            xbits = wave_umax(__float_as_uint(m));
+                        }
+                        if (!head_max<WIDE, FAR>(lbits, xbits, whi, wlo | flag, sh, gslots, a.wgpg, member, seq, mdm, mdx, mhi, mlo, Kh, D,
+                                            a.L - 1, true))
                             goto bail;
                         if (t == 0 || mdm == dprev) break;     // the guess was the true D_max
                         dprev = mdm;
                     }
-                    s = min((int)(0xFFFFFFu - (mlo >> 8)), a.L - 1);   // in range whatever the inputs held
+                    if (FAR && t > 0) dprev = __builtin_amdgcn_readfirstlane(mdx);
+                    s = min((int)(0x7FFFFFu - (mlo >> 9)), a.L - 1);   // in range whatever the inputs held
                     sc = __uint_as_float(mhi);
                 }
                 s = __builtin_amdgcn_readfirstlane(s);

@@ -82,17 +82,21 @@ __device__ __forceinline__ unsigned wave_pick_lo(bool match, unsigned lo)
 
 // ---- the exchange between the workgroups of a head ---------------------------------------------------------
 // Every workgroup owns two tagged 64-bit slots per phase, [kind][member]: kind 0 carries its D maximum
-// (value << 32 | tag), kind 1 its candidate (score bits << 32 | complemented index << 8 | tag).  One wave per
+// (value << 32 | drop << 8 | tag; drop, used by select_resident.hip: by how many units in the last place the maximum
+// falls when the workgroup's candidate is taken, 0xFFFFFF = that many or more), kind 1 its candidate (score bits << 32 | complemented index << 8 | tag; in
+// select_resident.hip complemented index << 9 | kSetsMax where the candidate sets the workgroup's D maximum | tag).  One wave per
 // workgroup posts and polls; `ln` is that wave's lane id (rebuilt by the caller behind an empty statement, so the
 // addresses derived from it do not stay in registers across the step loop).
 
+constexpr unsigned kSetsMax = 0x100u;
+
 // lanes 0 and 1 of the posting wave write the workgroup's two words
 __device__ __forceinline__ void post_words(unsigned long long *slot, int slots_per_kind, int member, int ln, unsigned md,
-                                           unsigned mh, unsigned ml, unsigned tag)
+                                           unsigned mh, unsigned ml, unsigned tag, unsigned drop = 0u)
 {
     if (ln < 2) {
         const unsigned long long word =
-            ln == 0 ? (((unsigned long long)md << 32) | tag) : (((unsigned long long)mh << 32) | ml | tag);
+            ln == 0 ? (((unsigned long long)md << 32) | (drop << 8) | tag) : (((unsigned long long)mh << 32) | ml | tag);
         __hip_atomic_store(slot + ln * slots_per_kind + member, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
