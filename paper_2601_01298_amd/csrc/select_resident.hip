@@ -317,7 +317,7 @@ select_resident(ResArgs a)
     // (exact_groups): 924 -> 799 us there, 2409 -> 2102 us for 32 heavy-tailed heads of 16384 keys, within 1 % on clustered
     // clouds.  With one slot of 64 elements the step is so short that what this adds to it shows: a clustered cloud of 16
     // heads of 4096 keys 209 -> 223 us (a heavy-tailed one 290 -> 244); that instance does without.  So do the wide ones: four
-    // polled words a lane leave no room for it (4 clustered heads of 65536 keys, d = 128, 1430 -> 1455 ... 1621 us).
+    // polled words a lane leave no room for it (4 clustered heads of 65536 keys, d = 128, 1430 -> 1455 us).
     constexpr bool FAR = !WIDE && (R > 1 || D == 128);
     // keys a wave can stage at a time (where rows sit in LDS too, there is room for 8)
     constexpr int CAP = !FAR ? (D == 64 ? 12 : 8) : RLDS > 0 ? 8 : 32;
