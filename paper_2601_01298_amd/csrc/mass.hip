@@ -5,9 +5,9 @@
 // the O(L^2 d) of the kernel density it can stand in for.  Two kernels:
 //   mass_logits   one workgroup per (1024-token tile, KV head): the logits of all query heads that share the KV head
 //                 from one read of the key rows; writes them (log2 units; staged in LDS, one coalesced pass per tile) and
-//                 a (max, sum of exp2) pair per (query head, tile).  bf16 keys: the dot products are MFMA tiles of 16 keys
-//                 by up to 16 query heads, whose operand is fetched from memory as it is, 64 bytes of a row by four lanes;
-//                 fp32 keys: a lane group per row;
+//                 a (max, sum of exp2) pair per (query head, tile).  the dot products are MFMA tiles of 16 keys by up to
+//                 16 query heads, whose operand is fetched from memory as it is, 64 bytes of a row by four lanes
+//                 (mass_logits_rows, for fp32 keys and one or two query heads: 2048 tokens, a lane group per row);
 //   mass_combine  folds the pairs of a layer's heads into (max, 1/sum) per head, then per token adds
 //                 the normalised exponentials over the heads and writes the result to every KV head
 //                 of the layer (as A, or as 1/A when it is to serve as the density).
@@ -19,12 +19,40 @@ namespace {
 
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
-constexpr int kMassTile = 1024;    // tokens per workgroup of mass_logits
+constexpr int kMassTile = 1024;    // tokens per workgroup of mass_logits ...
+constexpr int kRowTile = 2048;     // ... and of mass_logits_rows
 constexpr int kMassMaxHq = 128;    // query heads per layer
 constexpr float kLog2e = 1.4426950408889634f;
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+
+template <bool BF16>
+struct Piece;   // 16 bytes of a row, widened to floats
+template <>
+struct Piece<true> {
+    static constexpr int PER = 8;
+    static __device__ __forceinline__ void widen(const uint4 &q, float (&f)[8])
+    {
+        const uint32_t w[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            f[2 * j] = __uint_as_float(w[j] << 16);
+            f[2 * j + 1] = __uint_as_float(w[j] & 0xFFFF0000u);
+        }
+    }
+};
+template <>
+struct Piece<false> {
+    static constexpr int PER = 4;
+    static __device__ __forceinline__ void widen(const uint4 &q, float (&f)[4])
+    {
+        f[0] = __uint_as_float(q.x);
+        f[1] = __uint_as_float(q.y);
+        f[2] = __uint_as_float(q.z);
+        f[3] = __uint_as_float(q.w);
+    }
+};
 
 // (max, sum of exp2(z - max)) pairs merge associatively; an empty pair is (-inf, 0)
 __device__ __forceinline__ void merge(float &m, float &s, float m2, float s2)
@@ -36,11 +64,117 @@ __device__ __forceinline__ void merge(float &m, float &s, float m2, float s2)
     s = a + b;
 }
 
+// The form for fp32 keys and for one or two query heads per KV head: a lane group per row reads it whole, and the
+// arithmetic is little enough (24 x 16 heads of 32768 keys, d = 64, one query head each: 0.30 ms, 0.36 through the MFMA form).
+template <bool BF16, int D, int MAXG>
+__global__ void __launch_bounds__(256)
+mass_logits_rows(const void *__restrict__ Kv, const void *__restrict__ Qv, float *__restrict__ z,
+            float2 *__restrict__ part, int L, int g, float scale2 /* scale * log2(e) */, int nblk)
+{
+    typedef Piece<BF16> P;
+    constexpr int PER = P::PER;
+    constexpr int ES = BF16 ? 2 : 4;
+    constexpr int LPR = D / PER;          // lanes per key row
+    constexpr int RP = 256 / LPR;         // rows per pass of the workgroup
+    constexpr int UN = 4;                 // rows in flight per lane group
+    __shared__ float wm[4][MAXG], wsum[4][MAXG];
+    // The logits of the tile wait in LDS and leave in one coalesced pass at the end: a 4-byte store per row group
+    // inside the streaming loop costs a memory transaction per 32 bytes.  (Eight query heads per KV head would need
+    // 64 KB: those keep the direct stores.)
+    constexpr bool STAGE = MAXG <= 4;
+    __shared__ float zt[STAGE ? MAXG : 1][STAGE ? kRowTile : 1];
+
+    const int kvh = blockIdx.y, blk = blockIdx.x;
+    const int tid = threadIdx.x, sub = tid % LPR, rsub = tid / LPR;
+    const char *Kh = reinterpret_cast<const char *>(Kv) + (size_t)kvh * L * D * ES;
+
+    float qf[MAXG][PER];
+#pragma unroll
+    for (int j = 0; j < MAXG; ++j) {
+        const int qh = kvh * g + (j < g ? j : 0);
+        const uint4 qq = *reinterpret_cast<const uint4 *>(reinterpret_cast<const char *>(Qv) + ((size_t)qh * D + sub * PER) * ES);
+        P::widen(qq, qf[j]);
+    }
+    float m[MAXG], s[MAXG];
+#pragma unroll
+    for (int j = 0; j < MAXG; ++j) {
+        m[j] = -__builtin_inff();
+        s[j] = 0.0f;
+    }
+
+    const int lo = blk * kRowTile, hi = min(L, lo + kRowTile);
+    for (int r0 = lo; r0 < hi; r0 += UN * RP) {
+        uint4 q[UN];
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const int i = min(r0 + u * RP + rsub, hi - 1);
+            // the keys stream through once: loads marked non-temporal keep them from displacing anything cached
+            const u32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(Kh + ((size_t)i * D + sub * PER) * ES));
+            q[u] = make_uint4(v.x, v.y, v.z, v.w);
+        }
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const int i = r0 + u * RP + rsub;
+            float f[PER];
+            P::widen(q[u], f);
+#pragma unroll
+            for (int j = 0; j < MAXG; ++j) {
+                if (j < g) {
+                    float acc = 0.0f;
+#pragma unroll
+                    for (int e = 0; e < PER; ++e) acc = fmaf(f[e], qf[j][e], acc);
+                    acc = lane_group_sum<LPR>(acc);
+                    const float zz = acc * scale2;
+                    if (i < hi) {
+                        if (sub == 0) {
+                            if constexpr (STAGE) zt[j][i - lo] = zz;
+                            else z[(size_t)(kvh * g + j) * L + i] = zz;
+                        }
+                        const float mn = fmaxf(m[j], zz);
+                        s[j] = s[j] * __builtin_amdgcn_exp2f(m[j] - mn) + __builtin_amdgcn_exp2f(zz - mn);
+                        m[j] = mn;
+                    }
+                }
+            }
+        }
+    }
+    // one lane per row group speaks for its rows; fold the lanes of a wave, then the 4 waves
+    const int lane = tid & 63, wave = tid >> 6;
+#pragma unroll
+    for (int j = 0; j < MAXG; ++j) {
+        if (j < g) {
+            float mm = (sub == 0) ? m[j] : -__builtin_inff();
+            float ss = (sub == 0) ? s[j] : 0.0f;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const float m2 = __shfl_xor(mm, o), s2 = __shfl_xor(ss, o);
+                merge(mm, ss, m2, s2);
+            }
+            if (lane == 0) {
+                wm[wave][j] = mm;
+                wsum[wave][j] = ss;
+            }
+        }
+    }
+    __syncthreads();
+    if constexpr (STAGE) {
+#pragma unroll
+        for (int j = 0; j < MAXG; ++j)
+            if (j < g)
+                for (int i = lo + tid; i < hi; i += 256) z[(size_t)(kvh * g + j) * L + i] = zt[j][i - lo];
+    }
+    if (tid < g) {
+        float mm = wm[0][tid], ss = wsum[0][tid];
+        for (int w = 1; w < 4; ++w) merge(mm, ss, wm[w][tid], wsum[w][tid]);
+        part[(size_t)(kvh * g + tid) * nblk + blk] = make_float2(mm, ss);
+    }
+}
+
 // What bounds it: the read of the keys (nothing is left of the arithmetic on the vector pipe but the exponentials of the
 // staged logits, one per logit).  With a lane group per row, its dot products, the sums over its lanes and a running
 // softmax in every lane of it, the vector pipe took half of the time: 8 heads of 131072 keys, d = 128, four query heads
 // each, 94 us for the call; 64 now.
-template <bool BF16, int D, int MAXG>
+template <int D, int MAXG>
 __global__ void __launch_bounds__(256)
 mass_logits(const void *__restrict__ Kv, const void *__restrict__ Qv, float *__restrict__ z,
             float2 *__restrict__ part, int L, int g, float scale2 /* scale * log2(e) */, int nblk)
@@ -53,7 +187,7 @@ mass_logits(const void *__restrict__ Kv, const void *__restrict__ Qv, float *__r
     const int kvh = blockIdx.y, blk = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int lo = blk * kMassTile, hi = min(L, lo + kMassTile);
-    if constexpr (BF16) {
+    {
         // lane l: key l % 16 of a tile (and query head l % 16), elements kk*32 + (l / 16)*8 ... +7 of it
         constexpr int NK = D / 32, UN = 4;     // k-steps; 16-key tiles in flight per wave
         const int n = lane & 15, kg = lane >> 4;
@@ -83,34 +217,6 @@ mass_logits(const void *__restrict__ Kv, const void *__restrict__ Qv, float *__r
                 if constexpr (NK == 4) acc += p[2] + p[3];
                 // this lane holds query head n against keys kg*4 ... +3 (keys past the end are staged, not used)
                 if (n < g) *reinterpret_cast<f32x4_t *>(&zt[n][r0 - lo + u * 16 + kg * 4]) = acc * scale2;
-            }
-        }
-    } else {
-        constexpr int PER = 4, LPR = D / PER, RP = 256 / LPR, UN = 4;    // lanes per row, rows per pass, passes in flight
-        const int sub = tid % LPR, rsub = tid / LPR;
-        const float *Kh = reinterpret_cast<const float *>(Kv) + (size_t)kvh * L * D;
-        f32x4_t qf[MAXG];
-#pragma unroll
-        for (int j = 0; j < MAXG; ++j)
-            qf[j] = *reinterpret_cast<const f32x4_t *>(reinterpret_cast<const float *>(Qv) + (size_t)(kvh * g + (j < g ? j : 0)) * D + sub * PER);
-        for (int r0 = lo; r0 < hi; r0 += UN * RP) {
-            f32x4_t q[UN];
-#pragma unroll
-            for (int u = 0; u < UN; ++u)
-                q[u] = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t *>(Kh + (size_t)min(r0 + u * RP + rsub, hi - 1) * D + sub * PER));
-#pragma unroll
-            for (int u = 0; u < UN; ++u) {
-                const int i = r0 + u * RP + rsub;
-#pragma unroll
-                for (int j = 0; j < MAXG; ++j) {
-                    if (j < g) {
-                        float acc = 0.0f;
-#pragma unroll
-                        for (int e = 0; e < PER; ++e) acc = fmaf(q[u][e], qf[j][e], acc);
-                        acc = lane_group_sum<LPR>(acc);
-                        if (sub == 0 && i < hi) zt[j][i - lo] = acc * scale2;
-                    }
-                }
             }
         }
     }
@@ -198,18 +304,18 @@ MassWs mass_layout(int G, int Hq, int L)
 }
 
 template <bool BF16, int D>
-void run_logits(const void *K, const void *Q, float *z, float2 *part, int GHkv, int L, int g, float scale2, int nblk,
-                hipStream_t st)
+int run_logits(const void *K, const void *Q, float *z, float2 *part, int GHkv, int L, int g, float scale2, hipStream_t st)
 {
+    const bool rows = !BF16 || g <= 2;
+    const int tile = rows ? kRowTile : kMassTile, nblk = (L + tile - 1) / tile;
     const dim3 grid(nblk, GHkv), block(256);
-    if (g == 1)
-        hipLaunchKernelGGL((mass_logits<BF16, D, 1>), grid, block, 0, st, K, Q, z, part, L, g, scale2, nblk);
-    else if (g == 2)
-        hipLaunchKernelGGL((mass_logits<BF16, D, 2>), grid, block, 0, st, K, Q, z, part, L, g, scale2, nblk);
-    else if (g <= 4)
-        hipLaunchKernelGGL((mass_logits<BF16, D, 4>), grid, block, 0, st, K, Q, z, part, L, g, scale2, nblk);
-    else
-        hipLaunchKernelGGL((mass_logits<BF16, D, 8>), grid, block, 0, st, K, Q, z, part, L, g, scale2, nblk);
+    auto kern = mass_logits_rows<BF16, D, 8>;
+    if (g == 1) kern = mass_logits_rows<BF16, D, 1>;
+    else if (g == 2) kern = mass_logits_rows<BF16, D, 2>;
+    else if (rows && g <= 4) kern = mass_logits_rows<BF16, D, 4>;
+    else if (!rows) kern = g <= 4 ? mass_logits<D, 4> : mass_logits<D, 8>;
+    hipLaunchKernelGGL(kern, grid, block, 0, st, K, Q, z, part, L, g, scale2, nblk);
+    return nblk;
 }
 
 }  // namespace
@@ -227,16 +333,14 @@ hipError_t launch_attention_mass(const void *K, const void *Q, bool bf16, int G,
     float2 *part = reinterpret_cast<float2 *>(base + w.part);
     const int g = Hq / Hkv;
     const float scale2 = scale * kLog2e;
-    if (bf16) {
-        if (d == 64) run_logits<true, 64>(K, Q, z, part, G * Hkv, L, g, scale2, w.nblk, st);
-        else run_logits<true, 128>(K, Q, z, part, G * Hkv, L, g, scale2, w.nblk, st);
-    } else {
-        if (d == 64) run_logits<false, 64>(K, Q, z, part, G * Hkv, L, g, scale2, w.nblk, st);
-        else run_logits<false, 128>(K, Q, z, part, G * Hkv, L, g, scale2, w.nblk, st);
-    }
+    const int GHkv = G * Hkv;
+    const int nblk = bf16 ? (d == 64 ? run_logits<true, 64>(K, Q, z, part, GHkv, L, g, scale2, st)
+                                     : run_logits<true, 128>(K, Q, z, part, GHkv, L, g, scale2, st))
+                          : (d == 64 ? run_logits<false, 64>(K, Q, z, part, GHkv, L, g, scale2, st)
+                                     : run_logits<false, 128>(K, Q, z, part, GHkv, L, g, scale2, st));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(mass_combine, dim3((L + 255) / 256, G), dim3(256), 0, st, z, part, out, L, Hkv, Hq, w.nblk,
+    hipLaunchKernelGGL(mass_combine, dim3((L + 255) / 256, G), dim3(256), 0, st, z, part, out, L, Hkv, Hq, nblk,
                        as_density);
     return hipGetLastError();
 }
