@@ -337,13 +337,48 @@ __device__ __forceinline__ void wait_vmcnt()
 // The kernel sums of a key come from many workgroups (its own row block, and every block that visits it as
 // a column block).  They are accumulated in 32.32 fixed point with integer atomics: integer addition is
 // associative, so the result does not depend on the order in which the workgroups arrive (a floating-point
-// atomic would), and one 8-byte cell per key replaces a slot per visiting workgroup.  A contribution is a sum
-// of at most a few hundred kernel values (<= 1 each), the total at most L < 2^24: no overflow, and the 2^-32
-// resolution is far below fp32 rounding of sums that are >= 1 (the self term).
+// atomic would), and one 8-byte cell per key replaces a slot per visiting workgroup.  The 2^-32 resolution is far
+// below fp32 rounding of sums that are >= 1 (the self term).
+//
+// A kernel value is <= 1 in exact arithmetic, but the exponent is rounded, and at norms far above the bandwidth rounding
+// can leave it positive: a value of any size up to infinity.  So a contribution enters as a number only up to 32 times
+// the pairs it sums (a cell's pairs number less than 2^24 + 2^10, so its sum stays below 2^62); what is larger marks the
+// cell as infinite, a NaN marks it as NaN, and the marks outlast whatever is added.
+constexpr unsigned long long kNanCell = 1ull << 63, kInfCell = 1ull << 62;
+
+__device__ __forceinline__ bool fits_cell(float v, int pairs) { return v <= 32.0f * (float)pairs; }
+
 __device__ __forceinline__ void fixed_add(unsigned long long *cell, float v)
 {
-    const unsigned long long q = (unsigned long long)__float2ll_rn(v * 4294967296.0f);
-    __hip_atomic_fetch_add(cell, q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_fetch_add(cell, (unsigned long long)__float2ll_rn(v * 4294967296.0f), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ void fixed_add_or_mark(unsigned long long *cell, float v, int pairs)
+{
+    if (fits_cell(v, pairs)) fixed_add(cell, v);
+    else __hip_atomic_fetch_or(cell, v == v ? kInfCell : kNanCell, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The row sums of a 32-row tile: summed over the 32 columns held by the lanes of a half-wave, then added to the rows'
+// cells by the half-waves' first lanes (n == 0; acc: the cell of this half-wave's first row).  One test for all of them:
+// with a branch around every add 16 heads of 4096 keys, d = 64, took 55.2 us against 54.3 without the marks; this way 50.6
+// (the sums by DPP steps instead of shuffles are part of that).
+__device__ __forceinline__ void add_row_sums(unsigned long long *acc, float (&v)[16], int pairs, int n)
+{
+    bool fits = true;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        v[r] = lane_group_sum<32>(v[r]);
+        fits = fits && fits_cell(v[r], pairs);
+    }
+    if (__all(fits)) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            if (n == 0) fixed_add(acc + 8 * (r >> 2) + (r & 3), v[r]);
+    } else {
+        for (int r = 0; r < 16; ++r)
+            if (n == 0) fixed_add_or_mark(acc + 8 * (r >> 2) + (r & 3), v[r], pairs);
+    }
 }
 
 constexpr int kSymRtw = 2;                        // row tiles per wave of density_sym
@@ -472,8 +507,8 @@ density_sym(const void *const *__restrict__ kbase, const uint4 *__restrict__ ext
         unsigned long long *dst = acc + (size_t)h * Lpad + (size_t)((I + j) % nB) * BM;
         const float (*c2)[2][BM] = cs[j & 1];
         for (int c = tid; c < BM; c += 256)
-            fixed_add(dst + c, ((c2[0][0][c] + c2[0][1][c]) + (c2[1][0][c] + c2[1][1][c])) +
-                                   ((c2[2][0][c] + c2[2][1][c]) + (c2[3][0][c] + c2[3][1][c])));
+            fixed_add_or_mark(dst + c, ((c2[0][0][c] + c2[0][1][c]) + (c2[1][0][c] + c2[1][1][c])) +
+                                   ((c2[2][0][c] + c2[2][1][c]) + (c2[3][0][c] + c2[3][1][c])), BM);
     };
     // this wave's copies of stage sidx have landed (those of the next stage may still be in flight), and so have
     // everybody's; all waves are through with the stage before
@@ -523,20 +558,10 @@ density_sym(const void *const *__restrict__ kbase, const uint4 *__restrict__ ext
         if (both && sin == SPB - 1) flush(j);
     }
 
-    // each wave owns its rows: reduce over the 32 columns held by the lanes of a half-wave
+    // each wave owns its rows
 #pragma unroll
     for (int rt = 0; rt < RTW; ++rt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            float v = racc[rt][r];
-            v += __shfl_xor(v, 1);
-            v += __shfl_xor(v, 2);
-            v += __shfl_xor(v, 4);
-            v += __shfl_xor(v, 8);
-            v += __shfl_xor(v, 16);
-            if (n == 0)
-                fixed_add(acc + (size_t)h * Lpad + I * BM + (wave * RTW + rt) * 32 + 8 * (r >> 2) + 4 * hb + (r & 3), v);
-        }
+        add_row_sums(acc + (size_t)h * Lpad + I * BM + (wave * RTW + rt) * 32 + 4 * hb, racc[rt], nst * SC, n);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -552,14 +577,6 @@ density_sym(const void *const *__restrict__ kbase, const uint4 *__restrict__ ext
 // the stage's work, so there is one barrier per stage.  One fp32 head of 512 keys: the sweep 33 -> 8 us against one over all
 // ordered pairs with fp32 MFMAs.  Error against 64 bits there: 2.3e-7, with fp32 MFMAs 2.6e-7.
 // ------------------------------------------------------------------------------------------
-constexpr unsigned long long kNanCell = 1ull << 63;     // set in a cell that received a NaN (sums stay below 2^56)
-
-__device__ __forceinline__ void fixed_add_or_nan(unsigned long long *cell, float v)
-{
-    if (v == v) fixed_add(cell, v);
-    else __hip_atomic_fetch_or(cell, kNanCell, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 template <bool F32, int D>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((F32 && D == 128) ? 2 : 3, (F32 && D == 128) ? 2 : 3)))
 density_sym_small(const void *const *__restrict__ kbase, const uint4 *__restrict__ ext, const float *__restrict__ scale,
@@ -688,15 +705,11 @@ density_sym_small(const void *const *__restrict__ kbase, const uint4 *__restrict
             const int first = max(s0 - j * SPB, 0) * SC;        // the part may have begun, or end, inside the block
             unsigned long long *dst = acc + (size_t)h * Lpad + (size_t)((I + j) % nB) * BM;
             if (tid >= first && tid < (sin + 1) * SC)
-                fixed_add_or_nan(dst + tid, ((cs[0][0][tid] + cs[0][1][tid]) + (cs[1][0][tid] + cs[1][1][tid])) +
-                                                ((cs[2][0][tid] + cs[2][1][tid]) + (cs[3][0][tid] + cs[3][1][tid])));
+                fixed_add_or_mark(dst + tid, ((cs[0][0][tid] + cs[0][1][tid]) + (cs[1][0][tid] + cs[1][1][tid])) +
+                                         ((cs[2][0][tid] + cs[2][1][tid]) + (cs[3][0][tid] + cs[3][1][tid])), BM);
         }
     }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const float v = lane_group_sum<32>(racc[r]);
-        if (n == 0) fixed_add_or_nan(acc + (size_t)h * Lpad + I * BM + wave * 32 + 8 * (r >> 2) + 4 * hb + (r & 3), v);
-    }
+    add_row_sums(acc + (size_t)h * Lpad + I * BM + wave * 32 + 4 * hb, racc, (s1 - s0) * SC, n);
 }
 
 // rho = accumulated kernel sum / L; the first workgroup of a head also estimates the head's error
@@ -708,7 +721,9 @@ density_finish(PrepWs w, float *__restrict__ rho, int L, int Lpad, int head0)
     if (i < L) {
         const unsigned long long cell = w.acc[(size_t)h * Lpad + i];
         const double t = (double)cell * (1.0 / 4294967296.0);
-        rho[(size_t)h * L + i] = cell & kNanCell ? __builtin_nanf("") : (float)(t / (double)L);
+        rho[(size_t)h * L + i] = cell & kNanCell   ? __builtin_nanf("")
+                                 : cell & kInfCell ? __builtin_inff()
+                                                   : (float)(t / (double)L);
     }
     if (blockIdx.x != 0) return;
     __shared__ double part[256];

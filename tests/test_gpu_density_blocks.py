@@ -1,6 +1,7 @@
 """The density at the sizes where its two sweeps change hands or run short: edges of the 32-row tiles, of the 128- and
 256-key blocks, odd and even block counts (with an even count the block half way round is visited from both sides), counts
-at which several workgroups share a row block's visits; and a NaN key, which reaches every density of its head."""
+at which several workgroups share a row block's visits; a NaN key, which reaches every density of its head; and kernel sums
+that rounding has driven to infinity, which have to come out as that."""
 import numpy as np
 import pytest
 
@@ -42,10 +43,34 @@ def test_density_block_edges(ws, L, d, dtype):
         assert np.abs(rho[h] / ref - 1).max() <= TOL[dtype]
 
 
-@pytest.mark.parametrize("L,dtype", [(200, "f32"), (2100, "f32"), (500, "bf16")])
+@pytest.mark.parametrize("L,dtype", [(200, "f32"), (2100, "f32"), (500, "bf16"), (769, "bf16"), (2100, "bf16")])
 def test_nan_key_reaches_its_head(ws, L, dtype):
     import torch
     K = torch.from_numpy(cloud(2, L, 64, dtype, L)).to(torch.bfloat16 if dtype == "bf16" else torch.float32).cuda()
     K[1, L // 3, 5] = float("nan")
     rho = ws.ws_synapse_density(K, [3.0, 3.0])
     assert torch.isfinite(rho[0]).all() and torch.isnan(rho[1]).all()
+
+
+@pytest.mark.parametrize("L,dtype", [(300, "f32"), (2100, "f32"), (300, "bf16"), (768, "bf16"), (769, "bf16"), (2100, "bf16")])
+def test_overflowing_sums_are_infinite_and_flagged(ws, L, dtype):
+    """Norms of 6e9 around a common point, differences of order 1: the exponents are rounding errors of up to several times the
+    fp32 spacing there (512), of either sign, which the bandwidth of 0.01 turns into 0 or infinity.  A density is then infinite
+    or a plain sum of values (never below its self term, never a number out of range, never NaN); the head beside it is not
+    touched."""
+    import torch
+    K = cloud(2, L, 64, dtype, L)
+    rng = np.random.default_rng(L)
+    K[1] = 1e4 * rng.standard_normal(64) + rng.standard_normal((L, 64))
+    K[1, 0] = 0.01                      # (a key near zero: the head cannot be moved to the origin exactly)
+    Kd = torch.from_numpy(K).to(torch.bfloat16 if dtype == "bf16" else torch.float32).cuda()
+    space = torch.empty(ws.ws_synapse_workspace_bytes(ws.WS_OP_DENSITY, ws.WS_BF16 if dtype == "bf16" else ws.WS_F32, 2, L, 64),
+                        dtype=torch.uint8, device="cuda")
+    rho = ws.ws_synapse_density(Kd, [3.0, 0.01], workspace=space)
+    flagged, est = ws.ws_synapse_density_check(space, 2)
+    assert flagged and est[1] > 2e-5 >= est[0]
+    rho = rho.cpu().numpy()
+    assert np.isinf(rho[1]).sum() > L // 3
+    rest = rho[1, ~np.isinf(rho[1])]
+    assert (rest >= 0.999 / L).all() and (rest <= 32).all()
+    assert (rho[0] > 0).all() and (rho[0] <= 1).all()
