@@ -83,8 +83,8 @@ typedef void *ws_stream; /* hipStream_t */
  * bandwidth shrinks below the spread and for offsets that cannot be removed exactly; every call writes it
  * per head to the workspace and raises a flag when it exceeds 2e-5 (ws_synapse_density_check).  An isolated
  * key's self term is exact whatever the estimate.  fp32 keys are swept in place (no translation).  Where norms are so far
- * above the bandwidth that rounding leaves exponents positive and a kernel sum out of range (such heads are flagged), rho
- * is +infinity; a NaN coordinate makes every rho of its head NaN.
+ * above the bandwidth that rounding leaves exponents positive and a kernel sum out of range, rho is +infinity; a NaN
+ * coordinate makes every rho of its head NaN.
  */
 ws_status ws_synapse_density(const void *K, ws_dtype dt, int H, int L, int d,
                              const float *sigma_host, float *rho,

@@ -86,18 +86,18 @@ struct PrepWs {
     float *scale;           // [H] log2(e) / sigma^2
     const void **kbase;     // [H] the rows the sweep reads: the caller's, or the translated copy
     int *cand;              // [H] some coordinate of the head may be moved, going by the sample (bf16 keys only)
-    float *stat;            // [H][kStatChunks][3][D] min, max, smallest non-zero magnitude of the sample (bf16 keys only)
-    float *full;            // the same of all rows, for the heads with cand set
+    uint16_t *stat;         // [H][kStatChunks][3][D] min, max, smallest non-zero magnitude of the sample (bf16 keys only):
+                            // values of the keys, so their 16 bits hold them
+    uint16_t *full;         // the same of all rows, for the heads with cand set
     double *nsum;           // [H][Lpad/256] sum of squared norms per block of keys
-    uint4 *ext;             // [H][Lpad] side records
+    void *ext;              // [H][Lpad] side records: 16 bytes, or (density_sym_small) the 8 that are not constant
     void *Kc;               // [H][L][D] translated copy (bf16 keys only)
     unsigned long long *acc;   // [H][Lpad] kernel sums in fixed point: started here at the self term
+    int large;              // density_sym reads the records
 };
 
-// Two passes.  Pass 0 looks at the first eighth of every chunk of rows.  More keys only widen a coordinate's range
-// and refine its grid, so a coordinate that fails the exactness test on the sample is taken to fail it on the whole
-// head (a rule on the safe side: it decides only whether a head is moved, never a value): heads without a candidate
-// coordinate are settled by the sample, and pass 1, which reads the rest and merges, skips them.
+constexpr uint32_t kOnes = 0x3F803F80u;     // two bf16 ones
+
 // 2^(floor(log2 v) - 7): the spacing of bf16 numbers around |v| (v finite, normal, non-zero)
 __device__ __forceinline__ float bf16_ulp(float v)
 {
@@ -105,17 +105,20 @@ __device__ __forceinline__ float bf16_ulp(float v)
     return e > 7u ? __uint_as_float((e - 7u) << 23) : 0.0f;
 }
 
+__device__ __forceinline__ float from_bf16(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
+__device__ __forceinline__ uint16_t bits_of_bf16(float v) { return (uint16_t)(__float_as_uint(v) >> 16); }     // v is one
+
 // the reference point of coordinate j, from the statistics of the head's chunks; 0: the coordinate stays
 template <int D>
-__device__ __forceinline__ float reference_point(const float *__restrict__ stat /* the head's */, int j)
+__device__ __forceinline__ float reference_point(const uint16_t *__restrict__ stat /* the head's */, int j)
 {
     float mn = __builtin_inff(), mx = -__builtin_inff(), ma = __builtin_inff();
 #pragma unroll
     for (int ch = 0; ch < kStatChunks; ++ch) {
-        const float *st = stat + (size_t)ch * 3 * D;
-        mn = fminf(mn, st[j]);
-        mx = fmaxf(mx, st[D + j]);
-        ma = fminf(ma, st[2 * D + j]);
+        const uint16_t *st = stat + (size_t)ch * 3 * D;
+        mn = fminf(mn, from_bf16(st[j]));
+        mx = fmaxf(mx, from_bf16(st[D + j]));
+        ma = fminf(ma, from_bf16(st[2 * D + j]));
     }
     float c = 0.0f;
     if (mx >= mn && ma < __builtin_inff()) {          // finite, not all zero
@@ -131,9 +134,13 @@ __device__ __forceinline__ float reference_point(const float *__restrict__ stat 
     return c;
 }
 
+// Two passes.  Pass 0 looks at the first eighth of every chunk of rows.  More keys only widen a coordinate's range
+// and refine its grid, so a coordinate that fails the exactness test on the sample is taken to fail it on the whole
+// head (a rule on the safe side: it decides only whether a head is moved, never a value): heads without a candidate
+// coordinate are settled by the sample, and pass 1, which reads the rest and merges, skips them.
 template <int D>
 __global__ void __launch_bounds__(256)
-density_stats(const uint16_t *__restrict__ K, float *__restrict__ stat, float *__restrict__ full, int L, int pass,
+density_stats(const uint16_t *__restrict__ K, uint16_t *__restrict__ stat, uint16_t *__restrict__ full, int L, int pass,
               int *__restrict__ cand)
 {
     constexpr int CH = D / 8;            // 16-byte pieces per row
@@ -184,8 +191,12 @@ density_stats(const uint16_t *__restrict__ K, float *__restrict__ stat, float *_
         float v = red[which][0][j];
         for (int r = 1; r < RPS; ++r) v = (which == 1) ? fmaxf(v, red[which][r][j]) : fminf(v, red[which][r][j]);
         const size_t at = (((size_t)h * kStatChunks + chunk) * 3 + which) * D + j;
-        if (pass == 1) full[at] = (which == 1) ? fmaxf(v, stat[at]) : fminf(v, stat[at]);
-        else stat[at] = v;
+        if (pass == 1) {
+            const float o = from_bf16(stat[at]);
+            full[at] = bits_of_bf16((which == 1) ? fmaxf(v, o) : fminf(v, o));
+        } else {
+            stat[at] = bits_of_bf16(v);
+        }
     }
 }
 
@@ -214,7 +225,7 @@ density_prep(const void *__restrict__ K, PrepWs w, ScaleChunk sc, int head0, int
         w.scale[h] = sc.s[blockIdx.y];
         if (h == 0) w.flag[0] = 0;
     }
-    uint4 rec;
+    uint2 rec;
     double n = 0.0;
     if (j < L) {
         // whole row through 16-byte loads (a thread owns a row: 8 or more loads hit the same lines)
@@ -261,13 +272,14 @@ density_prep(const void *__restrict__ K, PrepWs w, ScaleChunk sc, int head0, int
             p[q] = bf16_rne((float)x);
             x -= (double)__uint_as_float(p[q] << 16);
         }
-        rec = make_uint4(p[0] | (p[1] << 16), p[2] | (p[3] << 16), 0x3F803F80u, 0x3F803F80u);
+        rec = make_uint2(p[0] | (p[1] << 16), p[2] | (p[3] << 16));
     } else {
         // padded slot: -1e30 makes exp2() of the pair exactly 0
-        rec = make_uint4(bf16_rne(-1e30f), 0u, 0x3F803F80u, 0x3F803F80u);
+        rec = make_uint2(bf16_rne(-1e30f), 0u);
     }
     if (j < Lpad) {
-        w.ext[(size_t)h * Lpad + j] = rec;
+        if (w.large) reinterpret_cast<uint4 *>(w.ext)[(size_t)h * Lpad + j] = make_uint4(rec.x, rec.y, kOnes, kOnes);
+        else reinterpret_cast<uint2 *>(w.ext)[(size_t)h * Lpad + j] = rec;
         // the cell of a key starts at its self term, exactly 1 (in 32.32 fixed point): kept out of
         // the fp32 row accumulators, where a 1 would swallow the many kernel values below its half ulp that make
         // up the rest of an isolated key's sum
@@ -579,7 +591,7 @@ density_sym(const void *const *__restrict__ kbase, const uint4 *__restrict__ ext
 // ------------------------------------------------------------------------------------------
 template <bool F32, int D>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((F32 && D == 128) ? 2 : 3, (F32 && D == 128) ? 2 : 3)))
-density_sym_small(const void *const *__restrict__ kbase, const uint4 *__restrict__ ext, const float *__restrict__ scale,
+density_sym_small(const void *const *__restrict__ kbase, const uint2 *__restrict__ ext, const float *__restrict__ scale,
                   unsigned long long *__restrict__ acc, int L, int Lpad, int nB, int nBoth, int nblk, int parts, int head0,
                   int total)
 {
@@ -601,7 +613,7 @@ density_sym_small(const void *const *__restrict__ kbase, const uint4 *__restrict
     // row block I of head h against the visited stages s0 ... s1-1 of its nblk blocks (see split_parts)
     const int s0 = (int)((long long)nblk * SPB * part / parts), s1 = (int)((long long)nblk * SPB * (part + 1) / parts);
     const Elem *Kh = reinterpret_cast<const Elem *>(kbase[h]);
-    const uint4 *exth = ext + (size_t)h * Lpad;
+    const uint2 *exth = ext + (size_t)h * Lpad;
     const float s = scale[h];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 31, hb = lane >> 5;
@@ -621,8 +633,8 @@ density_sym_small(const void *const *__restrict__ kbase, const uint4 *__restrict
                 a[0][kk] = load_frag(rp, kk, hb);
             }
         }
-        const uint4 rec = exth[row];
-        aext = __builtin_bit_cast(bf16x8_t, hb ? make_uint4(0, 0, 0, 0) : make_uint4(rec.z, rec.w, rec.x, rec.y));
+        const uint2 rec = exth[row];
+        aext = __builtin_bit_cast(bf16x8_t, hb ? make_uint4(0, 0, 0, 0) : make_uint4(kOnes, kOnes, rec.x, rec.y));
     }
     float racc[16];
 #pragma unroll
@@ -632,7 +644,7 @@ density_sym_small(const void *const *__restrict__ kbase, const uint4 *__restrict
     // different bank groups)
     typedef typename std::conditional<F32, f32x8_16_t, bf16x8_t>::type Group;
     Group g[NLD];
-    uint4 grec;
+    uint2 grec;
     auto fetch = [&](int sidx) {
         const int col0 = ((I + sidx / SPB) % nB) * BM + (sidx % SPB) * SC;
 #pragma unroll
@@ -656,7 +668,7 @@ density_sym_small(const void *const *__restrict__ kbase, const uint4 *__restrict
                 dst[0] = __builtin_bit_cast(uint4, g[i]);
             }
         }
-        if (tid < SC) sE[buf][tid] = grec;
+        if (tid < SC) sE[buf][tid] = make_uint4(grec.x, grec.y, kOnes, kOnes);
     };
 
     fetch(s0);
@@ -775,6 +787,8 @@ struct DensityWs {
     int Lpad;
 };
 
+// What callers were told to hold when the statistics were 32-bit, every record 16 bytes and short heads had no cells is
+// enough for this layout at all sizes.
 static DensityWs density_layout(int H, int L, int d, bool bf16)
 {
     DensityWs w;
@@ -788,14 +802,15 @@ static DensityWs density_layout(int H, int L, int d, bool bf16)
     o += round_up((size_t)H * sizeof(void *), 256);
     w.cand = o;
     o += round_up((size_t)H * sizeof(int), 256);
+    const size_t stat_bytes = bf16 ? (size_t)H * kStatChunks * 3 * d * sizeof(uint16_t) : 0;     // a multiple of 256
     w.stat = o;
-    if (bf16) o += round_up((size_t)H * kStatChunks * 3 * d * sizeof(float), 256);
+    o += stat_bytes;
     w.full = o;
-    if (bf16) o += round_up((size_t)H * kStatChunks * 3 * d * sizeof(float), 256);
+    o += stat_bytes;
     w.nsum = o;
     o += round_up((size_t)H * (w.Lpad / 256) * sizeof(double), 256);
     w.ext = o;
-    o += (size_t)H * w.Lpad * sizeof(uint4);
+    o += (size_t)H * w.Lpad * (use_large(bf16, L) ? sizeof(uint4) : sizeof(uint2));
     w.kc = o;
     if (bf16) o += round_up((size_t)H * L * d * 2, 256);
     w.acc = o;
@@ -807,7 +822,7 @@ static DensityWs density_layout(int H, int L, int d, bool bf16)
 size_t density_workspace_bytes(int H, int L, int d, bool bf16) { return density_layout(H, L, d, bf16).total; }
 size_t density_estimate_offset() { return kDensityFlagBytes; }
 
-static PrepWs prep_pointers(const DensityWs &w, char *base)
+static PrepWs prep_pointers(const DensityWs &w, char *base, bool large)
 {
     PrepWs p;
     p.flag = reinterpret_cast<int *>(base);
@@ -815,12 +830,13 @@ static PrepWs prep_pointers(const DensityWs &w, char *base)
     p.scale = reinterpret_cast<float *>(base + w.scale);
     p.kbase = reinterpret_cast<const void **>(base + w.kbase);
     p.cand = reinterpret_cast<int *>(base + w.cand);
-    p.stat = reinterpret_cast<float *>(base + w.stat);
-    p.full = reinterpret_cast<float *>(base + w.full);
+    p.stat = reinterpret_cast<uint16_t *>(base + w.stat);
+    p.full = reinterpret_cast<uint16_t *>(base + w.full);
     p.nsum = reinterpret_cast<double *>(base + w.nsum);
-    p.ext = reinterpret_cast<uint4 *>(base + w.ext);
+    p.ext = base + w.ext;
     p.Kc = base + w.kc;
     p.acc = reinterpret_cast<unsigned long long *>(base + w.acc);
+    p.large = large;
     return p;
 }
 
@@ -853,9 +869,9 @@ template <bool kBf16, int D>
 static hipError_t run(const void *K, int H, int L, const float *sigma_host, float *rho, void *ws, hipStream_t st)
 {
     const DensityWs w = density_layout(H, L, D, kBf16);
-    const PrepWs p = prep_pointers(w, reinterpret_cast<char *>(ws));
-    run_prep<kBf16, D>(K, H, L, sigma_host, w, p, st);
     const bool large = use_large(kBf16, L);
+    const PrepWs p = prep_pointers(w, reinterpret_cast<char *>(ws), large);
+    run_prep<kBf16, D>(K, H, L, sigma_host, w, p, st);
     const int bm = large ? kSymBm : kSmallBm;
     const int nB = large ? w.Lpad / bm : (L + bm - 1) / bm, nBoth = (nB - 1) / 2;
     const int nblk = 1 + nBoth + ((nB > 1 && (nB & 1) == 0) ? 1 : 0);
@@ -868,11 +884,13 @@ static hipError_t run(const void *K, int H, int L, const float *sigma_host, floa
         const int parts = large ? split_parts(wgs, nblk, (long long)cus * per_cu, 0.35)
                                 : split_parts(wgs, nblk * (kSmallBm / kSmallSc), (long long)cus * per_cu, 2.0);
         const int total = (int)(wgs * parts);
-        auto kern = density_sym_small<!kBf16, D>;
-        if constexpr (kBf16)
-            if (large) kern = density_sym<D>;
-        hipLaunchKernelGGL(kern, dim3(total), dim3(256), 0, st, p.kbase, p.ext, p.scale, p.acc, L, w.Lpad, nB, nBoth, nblk,
-                           parts, h0, total);
+        if (!large)
+            hipLaunchKernelGGL((density_sym_small<!kBf16, D>), dim3(total), dim3(256), 0, st, p.kbase,
+                               reinterpret_cast<const uint2 *>(p.ext), p.scale, p.acc, L, w.Lpad, nB, nBoth, nblk, parts, h0,
+                               total);
+        else if constexpr (kBf16)
+            hipLaunchKernelGGL(density_sym<D>, dim3(total), dim3(256), 0, st, p.kbase, reinterpret_cast<const uint4 *>(p.ext),
+                               p.scale, p.acc, L, w.Lpad, nB, nBoth, nblk, parts, h0, total);
         hipLaunchKernelGGL(density_finish, dim3((L + 255) / 256, nh), dim3(256), 0, st, p, rho, L, w.Lpad, h0);
     }
     return hipGetLastError();

@@ -249,6 +249,25 @@ def test_density_workspace_size(lib):
     assert 4 * 1000 * 16 <= f < 4 * 1024 * 16 + (1 << 20)
 
 
+def up(x, m=256):
+    return (x + m - 1) // m * m
+
+
+@pytest.mark.parametrize("H", [1, 3, 16, 384])
+@pytest.mark.parametrize("L", [1, 33, 512, 700, 768, 769, 1025, 4096, 32768])
+def test_density_workspace_fits_what_callers_held_before(lib, H, L):
+    """A caller may have kept the size it was told: 16 bytes a key for the records, 32-bit statistics and a reference point
+    per head, cells for bf16 heads of four blocks of 256 keys up.  What fitted then has to be accepted."""
+    from paper_2601_01298_amd import binding as b
+    Lpad = up(L, 512)
+    for d in (64, 128):
+        for dt in (b.WS_F32, b.WS_BF16):
+            n = 256 + 2 * up(4 * H) + up(8 * H) + up(4 * H) + up(4 * H * d) + up(8 * H * (Lpad // 256)) + 16 * H * Lpad
+            if dt == b.WS_BF16:
+                n += up(H * 16 * 3 * d * 4) + up(H * L * d * 2) + (up(8 * H * Lpad) if (L + 255) // 256 >= 4 else 0)
+            assert b.ws_synapse_workspace_bytes(b.WS_OP_DENSITY, dt, H, L, d) <= n
+
+
 def test_bench_refuses_more_than_one_gpu():
     """One GPU only: asking for more ends with a message and a non-zero status, before anything touches a device."""
     import os
