@@ -249,6 +249,9 @@ ws_status ws_synapse_attend_indexed(const void *Q, const void *K, const void *V,
  *   K   dev [G*Hkv, L, d];  Q dev [G*Hq, d] (one query token per head), both dtype `dt`
  *   out dev [G*Hkv, L] fp32: every KV head of a group receives the group's values
  *   Hq <= 128 per group, Hq/Hkv <= 8;  scale <= 0 means 1/sqrt(d)
+ *   A workspace with room for one (max, sum) pair per query head and 2048 tokens behind the logits, which is what
+ *   ws_synapse_workspace_bytes once reported (now: per 1024 tokens), is accepted; bf16 keys with more than two query heads
+ *   per KV head are slower with it.
  */
 ws_status ws_synapse_attention_mass(const void *K, const void *Q, ws_dtype dt, int G, int Hkv, int Hq,
                                     int L, int d, float scale, int as_density, float *out,

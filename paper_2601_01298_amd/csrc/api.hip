@@ -255,11 +255,11 @@ ws_status ws_synapse_attention_mass(const void *K, const void *Q, ws_dtype dt, i
     if (L >= kMaxL || !ws::mass_supported(Hkv, Hq) || (long long)G * Hkv > 65535 || (long long)G * Hq > (1 << 20))
         return WS_ERR_UNSUPPORTED;
     if (G > 65535) return WS_ERR_UNSUPPORTED;
-    s = check_ws(workspace, workspace_bytes, ws::mass_workspace_bytes(G, Hq, L));
+    s = check_ws(workspace, workspace_bytes, ws::mass_workspace_least(G, Hq, L));
     if (s != WS_OK) return s;
     if (scale <= 0.0f) scale = 1.0f / std::sqrt((float)d);
     const hipError_t e = ws::launch_attention_mass(K, Q, dt == WS_BF16, G, Hkv, Hq, L, d, scale, as_density, out,
-                                                   workspace, (hipStream_t)stream);
+                                                   workspace, workspace_bytes, (hipStream_t)stream);
     return e == hipSuccess ? WS_OK : WS_ERR_HIP;
 }
 

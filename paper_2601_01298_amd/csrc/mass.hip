@@ -5,9 +5,10 @@
 // the O(L^2 d) of the kernel density it can stand in for.  Two kernels:
 //   mass_logits   one workgroup per (1024-token tile, KV head): the logits of all query heads that share the KV head
 //                 from one read of the key rows; writes them (log2 units; staged in LDS, one coalesced pass per tile) and
-//                 a (max, sum of exp2) pair per (query head, tile).  the dot products are MFMA tiles of 16 keys by up to
+//                 a (max, sum of exp2) pair per (query head, tile).  The dot products are MFMA tiles of 16 keys by up to
 //                 16 query heads, whose operand is fetched from memory as it is, 64 bytes of a row by four lanes
-//                 (mass_logits_rows, for fp32 keys and one or two query heads: 2048 tokens, a lane group per row);
+//                 (mass_logits_rows, for fp32 keys, one or two query heads, and workspaces that hold a pair per 2048
+//                 tokens only: 2048 tokens, a lane group per row);
 //   mass_combine  folds the pairs of a layer's heads into (max, 1/sum) per head, then per token adds
 //                 the normalised exponentials over the heads and writes the result to every KV head
 //                 of the layer (as A, or as 1/A when it is to serve as the density).
@@ -66,10 +67,11 @@ __device__ __forceinline__ void merge(float &m, float &s, float m2, float s2)
 
 // The form for fp32 keys and for one or two query heads per KV head: a lane group per row reads it whole, and the
 // arithmetic is little enough (24 x 16 heads of 32768 keys, d = 64, one query head each: 0.30 ms, 0.36 through the MFMA form).
+// It also serves more query heads where the caller's workspace has a pair per 2048 tokens.
 template <bool BF16, int D, int MAXG>
 __global__ void __launch_bounds__(256)
 mass_logits_rows(const void *__restrict__ Kv, const void *__restrict__ Qv, float *__restrict__ z,
-            float2 *__restrict__ part, int L, int g, float scale2 /* scale * log2(e) */, int nblk)
+                 float2 *__restrict__ part, int L, int g, float scale2 /* scale * log2(e) */, int nblk)
 {
     typedef Piece<BF16> P;
     constexpr int PER = P::PER;
@@ -293,10 +295,10 @@ struct MassWs {
     int nblk;
 };
 
-MassWs mass_layout(int G, int Hq, int L)
+MassWs mass_layout(int G, int Hq, int L, int tile)
 {
     MassWs w;
-    w.nblk = (L + kMassTile - 1) / kMassTile;
+    w.nblk = (L + tile - 1) / tile;
     w.z = 0;
     w.part = round_up((size_t)G * Hq * L * sizeof(float), 256);
     w.total = w.part + round_up((size_t)G * Hq * w.nblk * sizeof(float2), 256);
@@ -304,43 +306,40 @@ MassWs mass_layout(int G, int Hq, int L)
 }
 
 template <bool BF16, int D>
-int run_logits(const void *K, const void *Q, float *z, float2 *part, int GHkv, int L, int g, float scale2, hipStream_t st)
+void run_logits(bool rows, const void *K, const void *Q, float *z, float2 *part, int GHkv, int L, int g, float scale2, int nblk,
+                hipStream_t st)
 {
-    const bool rows = !BF16 || g <= 2;
-    const int tile = rows ? kRowTile : kMassTile, nblk = (L + tile - 1) / tile;
-    const dim3 grid(nblk, GHkv), block(256);
     auto kern = mass_logits_rows<BF16, D, 8>;
     if (g == 1) kern = mass_logits_rows<BF16, D, 1>;
     else if (g == 2) kern = mass_logits_rows<BF16, D, 2>;
     else if (rows && g <= 4) kern = mass_logits_rows<BF16, D, 4>;
     else if (!rows) kern = g <= 4 ? mass_logits<D, 4> : mass_logits<D, 8>;
-    hipLaunchKernelGGL(kern, grid, block, 0, st, K, Q, z, part, L, g, scale2, nblk);
-    return nblk;
+    hipLaunchKernelGGL(kern, dim3(nblk, GHkv), dim3(256), 0, st, K, Q, z, part, L, g, scale2, nblk);
 }
 
 }  // namespace
 
 bool mass_supported(int Hkv, int Hq) { return Hq % Hkv == 0 && Hq <= kMassMaxHq && Hq / Hkv <= 8; }
 
-size_t mass_workspace_bytes(int G, int Hq, int L) { return mass_layout(G, Hq, L).total; }
+size_t mass_workspace_bytes(int G, int Hq, int L) { return mass_layout(G, Hq, L, kMassTile).total; }
+size_t mass_workspace_least(int G, int Hq, int L) { return mass_layout(G, Hq, L, kRowTile).total; }
 
 hipError_t launch_attention_mass(const void *K, const void *Q, bool bf16, int G, int Hkv, int Hq, int L, int d,
-                                 float scale, int as_density, float *out, void *ws, hipStream_t st)
+                                 float scale, int as_density, float *out, void *ws, size_t ws_bytes, hipStream_t st)
 {
-    const MassWs w = mass_layout(G, Hq, L);
+    const int g = Hq / Hkv;
+    const bool rows = !bf16 || g <= 2 || ws_bytes < mass_workspace_bytes(G, Hq, L);
+    const MassWs w = mass_layout(G, Hq, L, rows ? kRowTile : kMassTile);
     char *base = reinterpret_cast<char *>(ws);
     float *z = reinterpret_cast<float *>(base + w.z);
     float2 *part = reinterpret_cast<float2 *>(base + w.part);
-    const int g = Hq / Hkv;
     const float scale2 = scale * kLog2e;
-    const int GHkv = G * Hkv;
-    const int nblk = bf16 ? (d == 64 ? run_logits<true, 64>(K, Q, z, part, GHkv, L, g, scale2, st)
-                                     : run_logits<true, 128>(K, Q, z, part, GHkv, L, g, scale2, st))
-                          : (d == 64 ? run_logits<false, 64>(K, Q, z, part, GHkv, L, g, scale2, st)
-                                     : run_logits<false, 128>(K, Q, z, part, GHkv, L, g, scale2, st));
+    auto run = bf16 ? (d == 64 ? run_logits<true, 64> : run_logits<true, 128>)
+                    : (d == 64 ? run_logits<false, 64> : run_logits<false, 128>);
+    run(rows, K, Q, z, part, G * Hkv, L, g, scale2, w.nblk, st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(mass_combine, dim3((L + 255) / 256, G), dim3(256), 0, st, z, part, out, L, Hkv, Hq, nblk,
+    hipLaunchKernelGGL(mass_combine, dim3((L + 255) / 256, G), dim3(256), 0, st, z, part, out, L, Hkv, Hq, w.nblk,
                        as_density);
     return hipGetLastError();
 }

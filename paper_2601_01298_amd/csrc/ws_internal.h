@@ -130,8 +130,9 @@ hipError_t launch_attend_indexed(const void *Q, const void *K, const void *V, co
 // ---- steps next to the hot path -------------------------------------------------------
 bool mass_supported(int Hkv, int Hq);
 size_t mass_workspace_bytes(int G, int Hq, int L);
+size_t mass_workspace_least(int G, int Hq, int L);      // what is still served, by the row form throughout
 hipError_t launch_attention_mass(const void *K, const void *Q, bool bf16, int G, int Hkv, int Hq, int L, int d,
-                                 float scale, int as_density, float *out, void *ws, hipStream_t st);
+                                 float scale, int as_density, float *out, void *ws, size_t ws_bytes, hipStream_t st);
 
 int append_max_rows();
 size_t append_workspace_bytes(int H, int L);

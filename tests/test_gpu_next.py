@@ -66,6 +66,31 @@ def test_attention_mass(ws, oracle, cfg, G, Hkv, g, L):
     assert worst <= MASS_TOL
 
 
+@pytest.mark.parametrize("d,g,L", [(64, 3, 9000), (64, 8, 5000), (128, 4, 4097)])
+def test_attention_mass_in_a_workspace_of_an_earlier_size(ws, oracle, d, g, L):
+    """A caller may have kept the size it was told when a query head had one (max, sum) pair per 2048 tokens: accepted, and
+    nothing beyond it is written; one byte less is refused."""
+    import torch
+    w = variant(5 if d == 128 else 2, H=2, Hq=2 * g, L=L)
+    K = np.stack([syn.cloud(w, h, syn.TENSOR_K) for h in range(2)])
+    Q = syn.main_query(w)
+    up = lambda x: (x + 255) // 256 * 256
+    n = up(4 * w.Hq * L) + up(8 * w.Hq * ((L + 2047) // 2048))
+    space = torch.full((n + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    out = torch.empty((2, L), device="cuda")
+    Kd, Qd = to_device(K, "bf16"), to_device(Q, "bf16")
+    call = lambda size: ws.lib().ws_synapse_attention_mass(Kd.data_ptr(), Qd.data_ptr(), ws.WS_BF16, 1, 2, w.Hq, L, d, 0.0, 0,
+                                                           out.data_ptr(), space.data_ptr(), size, None)
+    assert call(n - 1) == ws.WS_ERR_WORKSPACE
+    torch.cuda.synchronize()
+    assert call(n) == ws.WS_OK
+    torch.cuda.synchronize()
+    assert (space[n:] == 0x5A).all()
+    ref = oracle.attention_mass(K, Q)
+    big = ref > 1e-12 * ref.max()
+    assert np.abs(out.cpu().numpy()[:, big] / ref[big] - 1).max() <= MASS_TOL
+
+
 def test_attention_mass_feeds_the_selection(ws, oracle):
     """The proxy in place of the kernel density: select on 1/A must follow the oracle's greedy rule on the
     oracle's 1/A (near-tie protocol, since A of far-away tokens underflows to equal values)."""
