@@ -261,7 +261,11 @@ __global__ void __launch_bounds__(256)
 mass_combine(const float *__restrict__ z, const float2 *__restrict__ part, float *__restrict__ out, int L, int Hkv,
              int Hq, int nblk, int as_density)
 {
-    __shared__ float mq[kMassMaxHq], rinv[kMassMaxHq];
+    // A = sum over the heads of exp2(z - ref) * rinv, with an integer for ref and 2^(integer part of z - ref) split off: z - max
+    // itself rounds at the size of the difference (2^-24 of 20 to 100 for most tokens), z - rint(z) is exact.  8 heads of
+    // 131072 heavy-tailed keys, d = 128, four query heads each, mean 2-norm error of 1/A against 64 bits over 160 inputs:
+    // 9.0e-7 with z - max, 8.3e-7 this way (with running sums in every lane and z - max: 8.3e-7); d = 64: 8.3e-7, 7.4e-7.
+    __shared__ float ref[kMassMaxHq], rinv[kMassMaxHq];
     const int grp = blockIdx.y, tid = threadIdx.x;
     for (int q0 = 0; q0 < Hq; q0 += 32) {       // eight lanes per head
         const int q = q0 + tid / 8;
@@ -276,8 +280,8 @@ mass_combine(const float *__restrict__ z, const float2 *__restrict__ part, float
             merge(mm, ss, m2, s2);
         }
         if (q < Hq && (tid & 7) == 0) {
-            mq[q] = mm;
-            rinv[q] = 1.0f / ss;
+            ref[q] = rintf(mm);
+            rinv[q] = __builtin_amdgcn_exp2f(ref[q] - mm) / ss;
         }
     }
     __syncthreads();
@@ -285,7 +289,10 @@ mass_combine(const float *__restrict__ z, const float2 *__restrict__ part, float
     if (i >= L) return;
     float A = 0.0f;
 #pragma unroll 8
-    for (int q = 0; q < Hq; ++q) A += __builtin_amdgcn_exp2f(z[(size_t)(grp * Hq + q) * L + i] - mq[q]) * rinv[q];
+    for (int q = 0; q < Hq; ++q) {
+        const float zz = z[(size_t)(grp * Hq + q) * L + i], whole = rintf(zz);
+        A = fmaf(__builtin_amdgcn_ldexpf(__builtin_amdgcn_exp2f(zz - whole), (int)(whole - ref[q])), rinv[q], A);
+    }
     const float v = as_density ? 1.0f / fmaxf(A, 1e-30f) : A;
     for (int hk = 0; hk < Hkv; ++hk) out[(size_t)(grp * Hkv + hk) * L + i] = v;
 }

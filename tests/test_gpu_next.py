@@ -91,6 +91,25 @@ def test_attention_mass_in_a_workspace_of_an_earlier_size(ws, oracle, d, g, L):
     assert np.abs(out.cpu().numpy()[:, big] / ref[big] - 1).max() <= MASS_TOL
 
 
+@pytest.mark.parametrize("dtype,d,g", [("bf16", 64, 1), ("bf16", 64, 4), ("bf16", 128, 8), ("f32", 128, 2)])
+def test_attention_mass_far_below_the_maximum(ws, oracle, dtype, d, g):
+    """One token at a logit near 60 and 2000 near 0.  What the maximum's own rounding does is common to the others; what is
+    left between them is the rounding of logits below 1 (2^-25 each), of the exponential and of the sum (2^-23 each): the
+    exponents may not be rounded at the size of their distance to the maximum (2^-18)."""
+    L = 2001
+    rng = np.random.default_rng(d + g)
+    Q = syn.round_to_bf16(rng.uniform(0.5, 1.0, (g, d)).astype(np.float32))
+    K = syn.round_to_bf16((rng.standard_normal((1, L, d)) * 0.05).astype(np.float32))
+    K[0, 700] = syn.round_to_bf16(np.full(d, 60.0 / (0.75 * np.sqrt(d)), dtype=np.float32))
+    A = ws.ws_synapse_attention_mass(to_device(K, dtype), to_device(Q, dtype), 1, as_density=False).cpu().numpy()[0]
+    ref = oracle.attention_mass(K, Q)
+    rest = np.arange(L) != 700
+    r = A[rest].astype(np.float64) / ref[rest]
+    spread = np.abs(r / np.median(r) - 1).max()
+    print(f"{dtype} d={d} g={g}: spread {spread:.2e}, common {abs(np.median(r) - 1):.1e}")
+    assert spread <= 6e-7
+
+
 def test_attention_mass_feeds_the_selection(ws, oracle):
     """The proxy in place of the kernel density: select on 1/A must follow the oracle's greedy rule on the
     oracle's 1/A (near-tie protocol, since A of far-away tokens underflows to equal values)."""
