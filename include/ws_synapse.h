@@ -114,13 +114,17 @@ int ws_synapse_density_is_symmetric(ws_dtype dt, int L, int d);
  *   idx       dev [H,k] int32, written in pick order
  *   score_out dev [H,k] fp32 winning score per step, or NULL
  *
- * Two kernels implement this call: one keeps a head's keys resident in registers and LDS for all
- * k steps (bf16 keys, heads that fit on chip), one streams them from memory every step (any size).
- * ws_synapse_select lets the library pick; ws_synapse_select_with names one.
+ * Three kernels implement this call: one keeps a head's keys resident in registers and LDS for all
+ * k steps, spread over the workgroups that share the head (bf16 keys, heads that fit on chip), one
+ * streams them from memory every step (any size), and one holds a short head in the registers of a
+ * single workgroup (L <= 1024 at d = 64, L <= 512 at d = 128; fp32 keys, and bf16 keys of no more heads
+ * than the device has compute units).  ws_synapse_select lets the library pick; ws_synapse_select_with
+ * names one of the first two.  They sum a distance in different orders: picks differ between them only
+ * where scores tie to fp32 rounding.
  *
- * Co-residency contract.  Both kernels are persistent: the workgroups that share a head exchange
- * their partial maxima every step and wait for each other, so the WHOLE grid has to be resident on
- * the device at once.  The launch is sized from the current device (its compute-unit count and the
+ * Co-residency contract.  The resident and the streaming kernel are persistent: the workgroups that
+ * share a head exchange their partial maxima every step and wait for each other, so the WHOLE grid has to be resident on
+ * the device at once (the one-workgroup kernel waits for nobody and cannot give up).  The launch is sized from the current device (its compute-unit count and the
  * number of workgroups of the kernel a compute unit holds, both asked of the runtime at every call),
  * which guarantees this when the selection has the device to itself.  The paper runs the producer
  * beside other streams (Sec. 3.1, Sec. 4); work on other streams that holds compute units while a
@@ -140,7 +144,7 @@ ws_status ws_synapse_select(const void *K, ws_dtype dt, int H, int L, int d,
                             int32_t *idx, float *score_out,
                             void *workspace, size_t workspace_bytes, ws_stream stream);
 
-/* The same step with the kernel named by the caller (tests and profiles; results are identical).
+/* The same step with the kernel named by the caller (tests and profiles; same results up to ties, see above).
  * WS_SELECT_RESIDENT returns WS_ERR_UNSUPPORTED when no resident instance fits the sizes on the
  * current device (fp32 keys, heads too long to sit on chip). */
 typedef enum {
@@ -185,11 +189,11 @@ ws_status ws_synapse_select_failed(const void *workspace, ws_stream stream, int 
  * exceeds compute_units * workgroups per unit.  WS_ERR_UNSUPPORTED: `which` names the resident
  * kernel and no instance fits. */
 typedef struct {
-    int resident;             /* 1 = keys resident on chip, 0 = streaming */
+    int resident;             /* 1 = the resident kernel; 0 = the one-workgroup kernel where rows_in_registers > 0, else streaming */
     int heads_in_flight;
     int workgroups_per_head;
     int threads;              /* per workgroup */
-    int rows_in_registers;    /* resident kernel: key rows per lane held in registers ... */
+    int rows_in_registers;    /* resident kernel: key rows per lane held in registers (one-workgroup kernel: per four lanes) ... */
     int rows_in_lds;          /* ... and in LDS */
     int compute_units;        /* the device shape the plan was made for */
 } ws_select_plan;
@@ -300,8 +304,9 @@ ws_status ws_synapse_inject(void *Kc, void *Vc, ws_dtype dt, int H, int Lcap, in
                             const void *Knew, const void *Vnew, int m, const int32_t *pos, float base,
                             void *workspace, size_t workspace_bytes, ws_stream stream);
 
-/* Which selection kernel ws_synapse_select would run for these sizes on the current device:
- * 1 = keys resident on chip, 0 = streaming.  For reports and profiles. */
+/* Whether ws_synapse_select would keep the keys of bf16 heads of these sizes on chip for all steps on the current
+ * device: 1 = it would (the resident or the one-workgroup kernel), 0 = streaming.  0 for fp32 keys, also where the
+ * one-workgroup kernel takes them (ws_synapse_select_plan says so).  For reports and profiles. */
 int ws_synapse_select_is_resident(ws_dtype dt, int H, int L, int d);
 
 /* Bytes of workspace the given operation needs for these sizes (0 if none).  Arguments an

@@ -143,8 +143,9 @@ ws_status ws_synapse_select_static(const void *K, ws_dtype dt, int H, int L, int
     if (s != WS_OK) return s;
     ws::SelectChoice c;
     if (!ws::choose_select(0, dt == WS_BF16, H, L, d, ws::current_chip(), ws::kStaticSlabBytes, c)) return WS_ERR_TOO_LARGE;
-    const size_t need = c.resident ? ws::resident_select_workspace_bytes(c.res.groups)
-                                   : ws::stream_select_workspace_bytes(c.stream, L);
+    const size_t need = c.small_rows > 0 ? ws::kSelectFlagBytes
+                        : c.resident     ? ws::resident_select_workspace_bytes(c.res.groups)
+                                         : ws::stream_select_workspace_bytes(c.stream, L);
     if (need > ws::kStaticScratchBytes) return WS_ERR_TOO_LARGE;
     void *scratch_ptr = nullptr;
     if (ws::select_static_scratch(&scratch_ptr) != hipSuccess) return WS_ERR_HIP;
@@ -186,7 +187,7 @@ ws_status ws_synapse_select_plan(ws_select_kernel which, ws_dtype dt, int H, int
     plan->heads_in_flight = c.resident ? c.res.groups : c.stream.groups;
     plan->workgroups_per_head = c.resident ? c.res.wgpg : c.stream.members;
     plan->threads = c.resident ? 256 : c.stream.threads;
-    plan->rows_in_registers = c.resident ? c.res.rreg : 0;
+    plan->rows_in_registers = c.resident ? c.res.rreg : c.small_rows;
     plan->rows_in_lds = c.resident ? c.res.rlds : 0;
     plan->compute_units = chip.cus;
     return WS_OK;
@@ -324,7 +325,7 @@ int ws_synapse_select_is_resident(ws_dtype dt, int H, int L, int d)
 {
     ws_select_plan p;
     if (ws_synapse_select_plan(WS_SELECT_AUTO, dt, H, L, d, 0, 0, &p) != WS_OK) return 0;
-    return p.resident;
+    return p.resident || (dt == WS_BF16 && p.rows_in_registers > 0);
 }
 
 const char *ws_status_string(ws_status s)

@@ -410,7 +410,8 @@ size_t select_workspace_bytes(int H, int L, int d, bool bf16)
 
 bool choose_select(int which, bool bf16, int H, int L, int d, const Chip &chip, size_t slab_budget, SelectChoice &c)
 {
-    c.resident = c.small = false;
+    c.resident = false;
+    c.small_rows = 0;
     c.res = ResidentShape{0, 0, 0, 0, 0};
     c.stream = SelectPlan{0, 0, 0};
     const bool can_res = bf16 && which != 1 && resident_select_shape(H, L, d, chip, c.res);
@@ -420,14 +421,11 @@ bool choose_select(int which, bool bf16, int H, int L, int d, const Chip &chip, 
         c.stream = select_plan(H, L, chip, slab_budget);
         if (c.stream.groups < 1) return false;
     }
-    // One workgroup per head where it holds the head and nobody named a kernel (what the fixed scratch refuses stays
-    // refused: the scratch limits are the streaming plan's).
-    if (which == 0 && select_small_fits(bf16, H, L, d, chip)) {
-        c.small = true;
+    // one workgroup per head where it holds the head and nobody named a kernel
+    if (which == 0) c.small_rows = select_small_rows(bf16, H, L, d, chip);
+    if (c.small_rows > 0) {
         c.resident = false;
-        c.stream.groups = slab_budget > 0 && c.stream.groups > 0 ? c.stream.groups : (H < chip.cus ? H : chip.cus);
-        c.stream.members = 1;
-        c.stream.threads = 512;
+        c.stream = SelectPlan{H < chip.cus ? H : chip.cus, 1, 512};
     }
     return true;
 }
@@ -435,7 +433,7 @@ bool choose_select(int which, bool bf16, int H, int L, int d, const Chip &chip, 
 hipError_t launch_select(const SelectChoice &c, const void *K, bool bf16, int H, int L, int d, const float *rho, int k,
                          float alpha, int32_t *idx, float *score_out, void *ws, hipStream_t st)
 {
-    if (c.small)
+    if (c.small_rows > 0)
         return launch_select_small(K, bf16, H, L, d, rho, k, alpha, idx, score_out, reinterpret_cast<int *>(ws), st);
     if (c.resident) return launch_select_resident(K, H, L, d, rho, k, alpha, idx, score_out, ws, c.res, st);
 

@@ -93,15 +93,16 @@ hipError_t launch_select_resident_ahead(const void *K, int H, int L, const float
                                         hipStream_t st);
 hipError_t resident_ahead_occupancy(int *workgroups_per_cu);
 
-// the whole head in the registers of one workgroup: whether it fits (and is the better choice), and the launch
-bool select_small_fits(bool bf16, int H, int L, int d, const Chip &chip);
+// the whole head in the registers of one workgroup: key rows per four lanes (0: does not fit, or another kernel is the
+// better choice), and the launch
+int select_small_rows(bool bf16, int H, int L, int d, const Chip &chip);
 hipError_t launch_select_small(const void *K, bool bf16, int H, int L, int d, const float *rho, int k, float alpha,
                                int32_t *idx, float *score_out, int *fail, hipStream_t st);
 
 // which: 0 = the library chooses, 1 = streaming kernel, 2 = resident kernel
 struct SelectChoice {
     bool resident;
-    bool small;          // one workgroup per head; resident is false and stream says how many heads run at once
+    int small_rows;      // > 0: one workgroup per head; resident is false and stream says how many heads run at once
     SelectPlan stream;
     ResidentShape res;
 };

@@ -39,7 +39,7 @@ int main(void)
     CHECK(ws_synapse_density_check(NULL, H, NULL, &flagged, NULL) == WS_ERR_INVALID_ARG);
     CHECK(ws_synapse_density_check(fake, 0, NULL, &flagged, NULL) == WS_ERR_INVALID_ARG);
     CHECK(ws_synapse_density_check(fake, H, NULL, NULL, NULL) == WS_ERR_INVALID_ARG);
-    CHECK(ws_synapse_density_is_symmetric(WS_BF16, 32768, 64) == 1 && ws_synapse_density_is_symmetric(WS_F32, 32768, 64) == 0);
+    CHECK(ws_synapse_density_is_symmetric(WS_BF16, 32768, 64) == 1 && ws_synapse_density_is_symmetric(WS_F32, 32768, 64) == 1);
     CHECK(ws_synapse_density_is_symmetric(WS_BF16, 32768, 72) == 0);
     const int before = g_launches;
 
@@ -110,7 +110,10 @@ int main(void)
     }
     CHECK(ws_synapse_workspace_bytes(WS_OP_DENSITY, WS_BF16, 0, 1000, 64, 1, 1, 1) == (size_t)-1);
     for (int s = 0; s <= 8; ++s) CHECK(ws_status_string((ws_status)s) != NULL);
-    CHECK(ws_synapse_select_is_resident(WS_BF16, H, 1000, 64) == 1);
+    CHECK(ws_synapse_select_is_resident(WS_BF16, H, 1000, 64) == 1 && ws_synapse_select_is_resident(WS_BF16, H, 5000, 64) == 1);
+    CHECK(ws_synapse_select_is_resident(WS_F32, H, 1000, 64) == 0 && ws_synapse_select_is_resident(WS_F32, H, 5000, 64) == 0);
+    CHECK(ws_synapse_select_plan(WS_SELECT_AUTO, WS_F32, H, 1000, 64, 0, 0, &plan) == WS_OK && plan.rows_in_registers == 8);
+    CHECK(ws_synapse_select_plan(WS_SELECT_STREAMING, WS_F32, H, 1000, 64, 0, 0, &plan) == WS_OK && plan.rows_in_registers == 0);
     CHECK(g_launches - before == 11);
 
     free(sigma);

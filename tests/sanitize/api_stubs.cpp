@@ -9,7 +9,7 @@ namespace ws {
 
 size_t density_workspace_bytes(int H, int L, int, bool) { return (size_t)H * L * 16 + 256; }
 size_t density_estimate_offset() { return kDensityFlagBytes; }
-bool density_uses_symmetric(bool bf16, int L, int) { return bf16 && L >= 1024; }
+bool density_uses_symmetric(bool, int, int) { return true; }
 hipError_t launch_density(const void *, bool, int, int, int, const float *, float *, void *, hipStream_t)
 {
     ++g_launches;
@@ -20,6 +20,11 @@ size_t select_workspace_bytes(int H, int L, int, bool) { return kSelectFlagBytes
 bool choose_select(int which, bool bf16, int, int L, int, const Chip &, size_t, SelectChoice &c)
 {
     c.resident = bf16 && which != 1 && L <= 65536;
+    c.small_rows = 0;
+    if (which == 0 && L <= 1024) {
+        c.resident = false;
+        c.small_rows = 8;
+    }
     if (!c.resident && L > 1000000) return false;      // as if not even one head's slabs fitted a budget
     c.stream = SelectPlan{8, 4, 512};
     c.res = ResidentShape{2, 0, 8, 16, 1};

@@ -198,6 +198,24 @@ def test_selection_kernel_choice_is_host_logic(lib):
                                    for f in os.listdir(os.path.join(ROOT, "paper_2601_01298_amd", "csrc")))
 
 
+def test_short_heads_are_reported_as_held_on_chip(lib):
+    """Heads that the one-workgroup kernel takes: the plan names it by rows in registers without the resident kernel, and
+    ws_synapse_select_is_resident keeps saying that bf16 keys stay on chip (and nothing of the kind for fp32 keys)."""
+    from paper_2601_01298_amd import binding as b
+    for d, most in ((64, 1024), (128, 512)):
+        for L in (1, 128, 256, 257, 512, 513, 1024):
+            for H in (1, 256, 257):
+                for dt in (b.WS_BF16, b.WS_F32):
+                    p = b.ws_synapse_select_plan("auto", dt, H, L, d, 256, 2)
+                    small = L <= most and (dt == b.WS_F32 or H <= 256)
+                    assert (p.rows_in_registers > 0 and not p.resident) == small, (dt, H, L, d)
+                    if small:
+                        assert p.workgroups_per_head == 1 and p.threads == 512 and p.heads_in_flight == min(H, 256)
+                        assert p.rows_in_registers * 128 >= L and p.rows_in_lds == 0
+                        assert b.ws_synapse_select_plan("stream", dt, H, L, d, 256, 2).rows_in_registers == 0
+                    assert b.ws_synapse_select_is_resident(dt, H, L, d) == (dt == b.WS_BF16)
+
+
 @pytest.mark.parametrize("cus", [32, 64, 128, 256, 304])
 @pytest.mark.parametrize("per_cu", [1, 2])
 def test_selection_grid_fits_the_device(lib, cus, per_cu):
