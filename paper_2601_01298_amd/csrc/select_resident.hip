@@ -38,10 +38,11 @@ namespace {
 
 using namespace resident;
 
+constexpr unsigned kExpired = 0xFFFFFFFFu;     // no score: those are the bits of numbers >= 0
+
 struct Shared {
+    uint4 result;                          // of the exchange: dm, hi (kExpired: a wait expired), lo, dx; one read in every thread
     unsigned dm[4], dx[4], hi[4], lo[4];   // one entry per wave of the workgroup
-    unsigned rdm, rdx, rhi, rlo;           // result of the exchange
-    int abort;
 };
 
 // One exchange over every wave of the head, carrying two independent maxima:
@@ -78,16 +79,19 @@ __device__ __forceinline__ bool head_max(unsigned dm, unsigned dx, unsigned hi, 
         // the 4 waves' entries: every lane reads all of them (same address: a broadcast), no cross-lane step
         unsigned md = max(max(sh.dm[0], sh.dm[1]), max(sh.dm[2], sh.dm[3]));
         unsigned mh = max(max(sh.hi[0], sh.hi[1]), max(sh.hi[2], sh.hi[3]));
+        // (asked of all four entries together, beside the chain of maxima and not behind it)
+        const bool flagged = FAR && (__builtin_amdgcn_readfirstlane(sh.lo[0] | sh.lo[1] | sh.lo[2] | sh.lo[3]) & kSetsMax);
         unsigned ml = 0u;
 #pragma unroll
         for (int w = 0; w < 4; ++w) ml = max(ml, sh.hi[w] == mh ? sh.lo[w] : 0u);
         // what the maximum is without the candidate
-        unsigned mx = md;
-        if (FAR && (__builtin_amdgcn_readfirstlane(ml) & kSetsMax)) {
+        unsigned mx = md, drop = 0u;
+        if (flagged && (__builtin_amdgcn_readfirstlane(ml) & kSetsMax)) {
             mx = 0u;
 #pragma unroll
             for (int w = 0; w < 4; ++w) mx = max(mx, sh.hi[w] == mh && sh.lo[w] == ml ? sh.dx[w] : sh.dm[w]);
             if (mx == md) ml &= ~kSetsMax;
+            drop = min(md - mx, 0xFFFFFFu);
         }
         bool good = true;
         if (nwg > 1) {
@@ -99,7 +103,7 @@ __device__ __forceinline__ bool head_max(unsigned dm, unsigned dx, unsigned hi, 
             // whole step loop they would be spilled and reloaded on this, the latency-critical path.
             int ln = lane;
             asm volatile("" : "+v"(ln));
-            post_words(slot, MS, member, ln, md, mh, ml, tag, FAR ? min(md - mx, 0xFFFFFFu) : 0u);
+            post_words(slot, MS, member, ln, md, mh, ml, tag, drop);
             unsigned touched = 0u;
             if (prefetch && ln < D / 8) {
                 // candidate index travels in bits 9..31 of lo, complemented
@@ -148,25 +152,22 @@ __device__ __forceinline__ bool head_max(unsigned dm, unsigned dx, unsigned hi, 
                 const unsigned long long won = __ballot(kind == 1 && gh == mh && gl == ml);
                 const int wl = won ? (int)__builtin_ctzll(won) & 31 : 0;
                 const unsigned wd = (unsigned)__builtin_amdgcn_readlane((int)gh, wl);
-                const unsigned drop = (unsigned)__builtin_amdgcn_readlane((int)gl, wl) >> 8;
-                if (wd == md && drop != 0xFFFFFFu) mx = wave_umax(ln < 32 ? (ln == wl ? gh - drop : gh) : 0u);
+                const unsigned wdrop = (unsigned)__builtin_amdgcn_readlane((int)gl, wl) >> 8;
+                if (wd == md && wdrop != 0xFFFFFFu) mx = wave_umax(ln < 32 ? (ln == wl ? gh - wdrop : gh) : 0u);
             }
             if (touched == 0xFFFFFFFFu && seq == 0u) good = false;   // never true: keeps the touch alive
         }
         if (lane == 0) {
-            sh.rdm = md;
-            if (FAR) sh.rdx = mx;
-            sh.rhi = mh;
-            sh.rlo = ml;
-            if (!good) sh.abort = 1;
+            sh.result = make_uint4(md, good ? mh : kExpired, ml, mx);
         }
     }
     __syncthreads();
-    dm_out = sh.rdm;
-    dx_out = FAR ? sh.rdx : dm_out;
-    hi_out = sh.rhi;
-    lo_out = sh.rlo;
-    return sh.abort == 0;
+    const uint4 r = sh.result;
+    dm_out = r.x;
+    dx_out = r.w;
+    hi_out = r.y;
+    lo_out = r.z;
+    return r.y != kExpired;
 }
 
 // ---- exact distances for the keys a new landmark may move ------------------------------------------------------
@@ -314,13 +315,16 @@ select_resident(ResArgs a)
     // Clouds with isolated keys pick the far point at most steps and move many keys per step: the instances with more than
     // one row slot, or rows of 128, carry D_max without the winner through the exchange (a second exchange in 17 % of the
     // steps of 32 heads of 8192 keys with 1 % outliers, d = 128, against 65 %) and evaluate staged keys in groups
-    // (exact_groups): 924 -> 799 us there, 2409 -> 2102 us for 32 heavy-tailed heads of 16384 keys, within 1 % on clustered
-    // clouds.  With one slot of 64 elements the step is so short that what this adds to it shows: a clustered cloud of 16
-    // heads of 4096 keys 209 -> 223 us (a heavy-tailed one 290 -> 244); that instance does without.  So do the wide ones: four
-    // polled words a lane leave no room for it (4 clustered heads of 65536 keys, d = 128, 1430 -> 1455 us).
+    // (exact_groups).  Against the form without both, 42 selections of 1 to 300 heads of 512 to 16384 keys: heavy-tailed clouds
+    // 0.75 to 1.01 of the time (32 heads of 16384 keys, d = 128, 2538 -> 2214 us), clustered clouds with scaled coordinates 0.97
+    // to 1.04, with a drift 0.93 to 1.03.  The groups alone are worth 0.91 to 1.0 on clustered clouds; what the exchange carries
+    // costs 2 to 3 % where the far point is not picked.  With one slot of 64 elements the step is so short that this shows: a
+    // clustered cloud of 16 heads of 4096 keys 209 -> 223 us (a heavy-tailed one 290 -> 244); that instance does without.  So do
+    // the wide ones: four polled words a lane leave no room for it (4 clustered heads of 65536 keys, d = 128, 1430 -> 1455 us).
     constexpr bool FAR = !WIDE && (R > 1 || D == 128);
-    // keys a wave can stage at a time (where rows sit in LDS too, there is room for 8)
-    constexpr int CAP = !FAR ? (D == 64 ? 12 : 8) : RLDS > 0 ? 8 : 32;
+    // keys a wave can stage at a time (where rows sit in LDS too, there is room for 8; strips of 32 are 1 to 4 % slower: more
+    // of them wait for four passes where the whole slot costs no more)
+    constexpr int CAP = !FAR ? (D == 64 ? 12 : 8) : RLDS > 0 ? 8 : 16;
     __shared__ __align__(16) uint32_t stage_all[4][CAP * DW];   // per wave: the packed rows of the staged keys
     __shared__ float sres_all[4][CAP];                          // per wave: the staged keys' exact distances
     __shared__ Shared sh;
@@ -346,8 +350,6 @@ select_resident(ResArgs a)
     }
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = member * 4 + (tid >> 6);
-    if (tid == 0) sh.abort = 0;
-    __syncthreads();
     // Key blocks of 64 are dealt round-robin to the waves of the head: this lane's r-th key is
     // rowbase + rstride * r.  Neighbouring context positions tend to be neighbours in key space too, so
     // the keys a new landmark moves would otherwise pile up in one workgroup and make the others wait.
@@ -438,6 +440,7 @@ select_resident(ResArgs a)
         {
             int prev = 0;
             unsigned dprev = 0xFFFFFFFFu;    // bits of the D_max the last step ended with (none yet)
+            unsigned left = 0u;              // FAR: what its pick left of it
             for (t = 0; t < a.k; ++t) {
                 unsigned lbits = 0u;
                 if (t > 0) {
@@ -460,6 +463,11 @@ select_resident(ResArgs a)
                     // and keep a second, twice as large copy of the keys.
                     unsigned sh16 = 16u, mhi16 = 0xFFFF0000u;
                     asm volatile("" : "+s"(sh16), "+s"(mhi16));
+                    if (FAR && t > 1) {
+                        // (here, where the landmark is waited for: between the exchange and the fetch it would cost 1 %)
+                        asm volatile("" : "+v"(left));
+                        dprev = __builtin_amdgcn_readfirstlane(left);
+                    }
                     // (a) Screen.  Most keys are far from the new landmark and keep their D.  With
                     // n = |k|^2, |k_i - s|^2 = n_i + n_s - 2 k_i.s, and the dot product runs on packed bf16
                     // pairs (v_dot2c_f32_bf16: two elements per instruction, a sixth of the work of
@@ -617,9 +625,9 @@ select_resident(ResArgs a)
                                             a.L - 1, true))
                             goto bail;
                         if (t == 0 || mdm == dprev) break;     // the guess was the true D_max
-                        dprev = mdm;
+                        dprev = __builtin_amdgcn_readfirstlane(mdm);
                     }
-                    if (FAR && t > 0) dprev = __builtin_amdgcn_readfirstlane(mdx);
+                    left = mdx;
                     s = min((int)(0x7FFFFFu - (mlo >> 9)), a.L - 1);   // in range whatever the inputs held
                     sc = __uint_as_float(mhi);
                 }

@@ -8,7 +8,7 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-def check(K, rho, k, alpha, dtype, kernel="auto"):
+def check(K, rho, k, alpha, dtype, kernel="auto", heads=None):
     import torch
     from oracle import ws_oracle as oracle
     from paper_2601_01298_amd import binding as ws
@@ -16,13 +16,18 @@ def check(K, rho, k, alpha, dtype, kernel="auto"):
     Kd = torch.from_numpy(K).to(torch.bfloat16 if dtype == "bf16" else torch.float32).cuda()
     score = torch.empty((K.shape[0], k), dtype=torch.float32, device="cuda")
     idx = ws.ws_synapse_select(Kd, torch.from_numpy(rho).cuda(), k, alpha, kernel=kernel, score_out=score)[0].cpu().numpy()
-    for h in range(K.shape[0]):
+    score = score.cpu().numpy()
+    for h in range(K.shape[0] if heads is None else heads):
         assert len(set(idx[h])) == k and idx[h].min() >= 0 and idx[h].max() < K.shape[1]
-        ref, _, _ = oracle.select(K[h], rho[h], k, alpha)
+        ref, ref_score, _ = oracle.select(K[h], rho[h], k, alpha)
         if not np.array_equal(idx[h], ref):
             forks, _, deficit = oracle.select_verify(K[h], rho[h], k, alpha, idx[h])
             assert forks >= 0 and deficit.max() <= 1e-5
-    assert np.isfinite(score.cpu().numpy()).all()
+        # the winning scores of one chain are the other's up to the tie rule, whichever of two tied keys was taken
+        same = np.cumprod(idx[h] == ref).astype(bool)
+        assert np.allclose(score[h][same], ref_score[same], rtol=2e-5, atol=0)
+    assert np.isfinite(score).all()
+    return idx, score
 
 
 def data(H, L, d, dtype, seed, far=0.0):
@@ -55,7 +60,19 @@ def test_more_small_heads_than_compute_units():
     check(*data(300, 200, 64, "f32", 9), 4, 0.5, "f32")
 
 
-@pytest.mark.parametrize("d,L", [(64, 1500), (64, 3000), (64, 40000), (128, 1200), (128, 6000), (128, 40000)])
+# heads in the call -> key rows per lane in registers and in LDS (and more than 32 workgroups per head: a wide instance)
+@pytest.mark.parametrize("d,H,L,split", [(64, 2, 1500, (1, 0)), (64, 2, 3000, (1, 0)), (64, 40, 4096, (2, 0)), (64, 96, 4096, (4, 0)),
+                                         (64, 600, 1000, (4, 0)), (64, 2, 40000, (6, 2)), (128, 2, 1200, (1, 0)), (128, 2, 6000, (1, 0)),
+                                         (128, 40, 4096, (2, 0)), (128, 520, 512, (2, 0)), (128, 72, 4096, (3, 1)), (128, 2, 40000, (3, 1))])
 @pytest.mark.parametrize("far", [0.02, 0.3])
-def test_far_points_picked_first(d, L, far):
-    check(*data(2, L, d, "bf16", L, far), 60, 0.5, "bf16", "resident")
+def test_far_points_picked_first(d, H, L, split, far):
+    """Every split of the resident kernel on clouds whose far point is picked at most steps: D_max without the pick carried
+    through the exchange (or, with one workgroup per head, through LDS), and strips that fill up and are refilled.  Heads are
+    copies of two clouds: the two against the oracle, the copies against them."""
+    from paper_2601_01298_amd import binding as ws
+    plan = ws.ws_synapse_select_plan("resident", ws.WS_BF16, H, L, d)
+    assert (plan.rows_in_registers, plan.rows_in_lds) == split, "this head count no longer selects the split"
+    K, rho = data(2, L, d, "bf16", L, far)
+    copies = np.arange(H) % 2
+    idx, score = check(K[copies], rho[copies], 60, 0.5, "bf16", "resident", heads=2)
+    assert np.array_equal(idx, idx[copies]) and np.array_equal(score, score[copies])
