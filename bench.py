@@ -21,7 +21,6 @@ if ROOT not in sys.path:
 
 PEAK_HBM_GBS = 8000.0          # MI355X HBM3E, published
 PEAK_BF16_TFLOPS = 2500.0      # dense bf16 MFMA, published
-PEAK_FP32_MFMA_TFLOPS = 157.3
 
 
 def main() -> int:
@@ -175,7 +174,7 @@ def main() -> int:
     bytes_gather = 2.0 * 2.0 * w.k * w.d * esize * w.H          # K and V rows, read + written
     flops_attend = 4.0 * w.N * w.Hq * w.k * w.d
     bytes_attend = 2.0 * w.k * w.d * esize * w.H + w.N * w.Hq * w.d * (esize + 4)
-    peak_mfma = PEAK_BF16_TFLOPS if bf16 else PEAK_FP32_MFMA_TFLOPS
+    peak_mfma = PEAK_BF16_TFLOPS if bf16 else PEAK_BF16_TFLOPS / 6      # a product of fp32 keys is six products of bf16 pieces
     per_stage = {
         "density": {"bound": "mfma", "achieved": flops_density / (stage_ms["density"] * 1e-3) / 1e12,
                     "peak": peak_mfma, "unit": "TFLOP/s"},
@@ -196,10 +195,10 @@ def main() -> int:
                                       "floor_ms": (tiles / 1024.0 * 828 / 2.4e9 * 1e3) if w.d == 64 else None}
         if w.d == 64:
             per_stage["attend"]["alu"]["frac_back_to_back"] = per_stage["attend"]["alu"]["floor_ms"] / b2b["attend"]
-    sym = ws.ws_synapse_density_is_symmetric(dt, w.L, w.d)      # the library's own choice of sweep
-    if sym:
-        # What the sweep is bound by in practice is the vector pipe, not the matrix core: every unordered pair
-        # costs multiply + v_exp_f32 + two adds = 4 + 8 + 4 + 4 cycles per 64 pairs on one of 1024 SIMDs.
+    large = bf16 and (w.L + 255) // 256 >= 4      # the library's own rule: the sweep in blocks of 256 keys, else of 128
+    if bf16:
+        # What the sweep is bound by in practice is the vector pipe, not the matrix core (fp32 keys: the matrix core): every
+        # unordered pair costs multiply + v_exp_f32 + two adds = 4 + 8 + 4 + 4 cycles per 64 pairs on one of 1024 SIMDs.
         pairs = 0.5 * w.L * w.L * w.H
         floor_ms = pairs / 64.0 * 20.0 / 1024.0 / 2.4e9 * 1e3
         per_stage["density"]["alu"] = {"bound": "alu", "cycles_per_64_pairs": 20, "clock_ghz": 2.4,
@@ -233,7 +232,7 @@ def main() -> int:
         if s in b2b:
             per_stage[s]["ms_back_to_back"] = b2b[s]
             per_stage[s]["frac_back_to_back"] = per_stage[s]["frac"] * stage_ms[s] / b2b[s]
-    if sym:
+    if bf16:
         # `frac` prices the ALGORITHMIC 2 L^2 d flop per head against the matrix-core peak; the symmetric sweep executes
         # about 0.63 of them, and what bounds it is the vector pipe (see "alu"): `frac` is not matrix-core utilisation.
         per_stage["density"]["algorithmic_frac"] = per_stage["density"]["frac"]
@@ -244,8 +243,9 @@ def main() -> int:
             per_stage["density"]["alu"]["frac_at_held_clock"] = fl / stage_ms["density"]
     dominant = max(stages, key=lambda s: stage_ms[s])
     roofline = dict(per_stage[dominant])
-    kernel_of = {"density": "density_sym" if sym else "density_sweep",
-                 "select": "select_resident" if ws.ws_synapse_select_is_resident(dt, w.H, w.L, w.d) else "select_stream",
+    plan = ws.ws_synapse_select_plan("auto", dt, w.H, w.L, w.d)
+    kernel_of = {"density": "density_sym" if large else "density_sym_small",
+                 "select": "select_resident" if plan.resident else "select_small" if plan.rows_in_registers else "select_stream",
                  "gather": "gather_rows", "attend": "attend_bf16" if bf16 else "attend_f32"}
     roofline["kernel"] = kernel_of[dominant]
     for s_ in stages:
@@ -274,7 +274,8 @@ def main() -> int:
         ms = timed(lambda: ws.ws_synapse_attention_mass(K, Qm, G, out=rho_m, workspace=ws_mass))
         nbytes = float(w.H) * w.L * w.d * esize + 4.0 * w.H * w.L
         next_steps["attention_mass"] = {"ms": ms, "bound": "hbm", "achieved": nbytes / (ms * 1e-3) / 1e9,
-                                        "peak": PEAK_HBM_GBS, "unit": "GB/s", "kernel": "mass_logits",
+                                        "peak": PEAK_HBM_GBS, "unit": "GB/s",
+                                        "kernel": "mass_logits" if bf16 and w.Hq // w.H > 2 else "mass_logits_rows",
                                         "shape": f"G={G} Hkv={w.H // G} Hq={w.Hq // G} L={w.L} d={w.d}"}
         del ws_mass, rho_m
         ws_app = torch.empty(ws.ws_synapse_workspace_bytes(ws.WS_OP_DENSITY_APPEND, dt, w.H, w.L, w.d),
