@@ -85,6 +85,10 @@ typedef void *ws_stream; /* hipStream_t */
  * key's self term is exact whatever the estimate.  fp32 keys are swept in place (no translation).  Where norms are so far
  * above the bandwidth that rounding leaves exponents positive and a kernel sum out of range, rho is +infinity; a NaN
  * coordinate makes every rho of its head NaN.
+ *
+ * Repeatability.  The same call on the same device gives the same bits.  How the sweep of a head is shared out (and with it
+ * the grouping of its fp32 partial sums) follows H, L and the device's compute-unit count, so the last bits of a head's rho
+ * may differ between a call for one layer and a call for all: by rounding, within the accuracy above.
  */
 ws_status ws_synapse_density(const void *K, ws_dtype dt, int H, int L, int d,
                              const float *sigma_host, float *rho,

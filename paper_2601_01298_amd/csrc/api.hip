@@ -317,8 +317,7 @@ ws_status ws_synapse_inject(void *Kc, void *Vc, ws_dtype dt, int H, int Lcap, in
 
 int ws_synapse_density_is_symmetric(ws_dtype dt, int L, int d)
 {
-    if (check_common(dt, d) != WS_OK || L < 1) return 0;
-    return ws::density_uses_symmetric(dt == WS_BF16, L, d) ? 1 : 0;
+    return check_common(dt, d) == WS_OK && L >= 1;      // both sweeps are
 }
 
 int ws_synapse_select_is_resident(ws_dtype dt, int H, int L, int d)

@@ -772,7 +772,12 @@ static inline bool use_large(bool bf16, int L) { return bf16 && (L + kSymBm - 1)
 // per row block (16 heads of 4096 keys, d = 64: 256 workgroups where 768 fit), so the visits (blocks in density_sym, stages
 // in density_sym_small) are cut into `parts` ranges: the count that makes rounds x visits per workgroup smallest, a
 // workgroup's start (row operands, first stage) priced at 0.35 blocks, or at two stages.  Launches of many rounds stay
-// whole: cutting them could only add starts.  The call of the example takes 76 us whole and 54 us in three parts.
+// whole: cutting them could only add starts.  The call of the example takes 64 us whole and 51 us in three parts; one fp32
+// head of 512 keys 25 us whole and 17 in twelve.  The prices are set by what they choose: over ten launches of 1 to 384 heads
+// of 512 to 16384 keys the choice was within 2 % of the best of 1 to 12 parts in nine, and 7 % from it for 40 fp32 heads of
+// 2048 (88 us whole, 83 in two parts).
+// The row sums of a head are grouped as its visits are shared out, so its last bits follow the launch (the header says so;
+// sums at fixed visit boundaries instead would add a reduction per boundary to launches that are not cut).
 static int split_parts(long long wgs, int visits, long long resident, double start)
 {
     int best = 1;
@@ -911,8 +916,5 @@ hipError_t launch_density(const void *K, bool bf16, int H, int L, int d, const f
     if (d == 128) return (bf16 ? run<true, 128> : run<false, 128>)(K, H, L, sigma_host, rho, ws, st);
     return hipErrorInvalidValue;
 }
-
-// which sweep serves these sizes (for reports): 1 = every unordered pair once
-bool density_uses_symmetric(bool, int, int) { return true; }
 
 }  // namespace ws

@@ -178,6 +178,8 @@ __device__ __forceinline__ bool head_max(unsigned dm, unsigned dx, unsigned hi, 
 // key.  Per wave, d = 128, a whole slot costs about 1650 cycles of vector work, a pass of eight keys about 300.
 // landmark: the landmark row in memory; early: this lane's pieces of it, where the registers allow to load them before the
 // screen (no rows in LDS).
+// The copy of a key into the strip and the evaluation of a whole slot are those of exact_update, written out again: as
+// functions of the row slot shared by both they take the instances with rows in LDS from 4 spilled registers to 143.
 template <int D, int RREG, int RLDS, int CAP>
 __device__ __forceinline__ unsigned exact_groups(const uint32_t (&kr)[RREG > 0 ? RREG : 1][D / 2], const uint4 *lrows,
                                                  const uint32_t (&lws)[D / 2], float (&Dv)[RREG + RLDS], unsigned needmask,
@@ -693,7 +695,7 @@ int instance_occupancy(int d, int rreg)
         else if (rreg == 2) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, select_resident<128, 2, 0, false>, 256, 0);
         else e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, select_resident<128, 3, 1, false>, 256, 0);
     }
-    // (the wide instances differ from these only in the exchange's polling loop)
+    // (the wide instances are built for two as well: same rows, their own polling loop, no D_max without the pick)
     if (e != hipSuccess) {
         (void)hipGetLastError();
         return 2;

@@ -9,7 +9,6 @@ namespace ws {
 
 size_t density_workspace_bytes(int H, int L, int, bool) { return (size_t)H * L * 16 + 256; }
 size_t density_estimate_offset() { return kDensityFlagBytes; }
-bool density_uses_symmetric(bool, int, int) { return true; }
 hipError_t launch_density(const void *, bool, int, int, int, const float *, float *, void *, hipStream_t)
 {
     ++g_launches;
