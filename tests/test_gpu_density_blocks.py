@@ -1,6 +1,7 @@
 """The density at the sizes where its two sweeps change hands or run short: edges of the 32-row tiles, of the 128- and
-256-key blocks, odd and even block counts (with an even count the block half way round is visited from both sides), counts
-at which several workgroups share a row block's visits; a NaN key, which reaches every density of its head; and kernel sums
+256-key blocks, odd and even block counts (with an even count the block half way round is visited from both sides; the sweep
+in blocks of 256 pads to an even count, so odd ones are those of the sweep in blocks of 128), counts at which several
+workgroups share a row block's visits; a NaN key, which reaches every density of its head; and kernel sums
 that rounding has driven to infinity, which have to come out as that."""
 import numpy as np
 import pytest

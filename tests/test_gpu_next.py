@@ -66,6 +66,24 @@ def test_attention_mass(ws, oracle, cfg, G, Hkv, g, L):
     assert worst <= MASS_TOL
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("g", [3, 4, 5, 8])
+@pytest.mark.parametrize("L", [1, 15, 17, 64, 1023, 1024, 1025, 2049])
+def test_attention_mass_on_the_matrix_cores(ws, oracle, d, g, L):
+    """bf16 keys with three and more query heads per KV head: both instances of the kernel, group sizes below an instance's,
+    the edges of its 16-key tiles and 1024-key workgroups; two groups of two KV heads."""
+    w = variant(5 if d == 128 else 2, H=4, Hq=4 * g, L=L)
+    K = np.stack([syn.cloud(w, h, syn.TENSOR_K) for h in range(4)])
+    Q = syn.main_query(w)
+    A = ws.ws_synapse_attention_mass(to_device(K, "bf16"), to_device(Q, "bf16"), 2, as_density=False).cpu().numpy()
+    for grp in range(2):
+        ref = oracle.attention_mass(K[2 * grp:2 * grp + 2], Q[2 * grp * g:(2 * grp + 2) * g])
+        big = ref > 1e-12 * ref.max()
+        assert np.abs(A[2 * grp][big] / ref[big] - 1).max() <= MASS_TOL
+        assert np.abs(A[2 * grp][~big]).max(initial=0.0) <= 1e-11 * ref.max()
+        assert np.array_equal(A[2 * grp], A[2 * grp + 1])
+
+
 @pytest.mark.parametrize("d,g,L", [(64, 3, 9000), (64, 8, 5000), (128, 4, 4097)])
 def test_attention_mass_in_a_workspace_of_an_earlier_size(ws, oracle, d, g, L):
     """A caller may have kept the size it was told when a query head had one (max, sum) pair per 2048 tokens: accepted, and

@@ -39,15 +39,16 @@ def variant(cfg, **kw):
 
 @pytest.fixture(params=["auto", "stream"])
 def select_kernel(request):
-    """Run a selection test once per kernel: "auto" takes the on-chip kernel wherever it fits (fp32
-    keys and oversized heads take the streaming kernel either way), "stream" names the streaming one."""
+    """Run a selection test once per kernel: "auto" takes an on-chip kernel wherever one fits (the one-workgroup kernel for
+    short heads, the resident one for longer bf16 heads; other heads take the streaming kernel either way), "stream" names
+    the streaming one."""
     return request.param
 
 
 # ------------------------------------------------------------------------------- density
 @pytest.mark.parametrize("cfg,H,L", [(1, 1, 512), (1, 2, 333), (2, 3, 4096), (2, 2, 1000), (2, 1, 31),
                                      (4, 2, 1500), (3, 2, 2048),
-                                     # the smallest heads the symmetric sweep takes (last row block nearly empty),
+                                     # the smallest heads the sweep in blocks of 256 takes (last row block nearly empty),
                                      # head counts that do not divide over the dies
                                      (2, 5, 769), (4, 3, 1025), (3, 11, 1536)])
 def test_density_matches_oracle(ws, oracle, cfg, H, L):
@@ -89,7 +90,7 @@ def density_with_report(ws, Kd, sigma):
 
 
 @pytest.mark.parametrize("cfg", [2, 4])               # head dimension 64 and 128
-@pytest.mark.parametrize("L", [2048, 600])            # the symmetric sweep and the full sweep
+@pytest.mark.parametrize("L", [2048, 600])            # the sweep in blocks of 256 keys and the one in blocks of 128
 @pytest.mark.parametrize("offset", [20.0, 100.0, -1000.0])
 def test_density_of_a_translated_cloud(ws, oracle, cfg, L, offset):
     """The density does not depend on where the cloud sits (the oracle pins that), and real key caches sit at an
@@ -312,7 +313,7 @@ def test_select_edge_cases(ws, oracle, select_kernel):
 
 
 def test_select_edge_cases_bf16(ws, oracle, select_kernel):
-    """The same degenerate cases on bf16 keys, which the on-chip kernel serves: k = L with duplicates (the
+    """The same degenerate cases on bf16 keys, which an on-chip kernel serves: k = L with duplicates (the
     covering radius ends at zero), exact ties, heads shorter than one block of keys, k = 1."""
     import torch
     rng = np.random.default_rng(10)

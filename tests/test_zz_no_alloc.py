@@ -1,8 +1,8 @@
 """The selection entry point that allocates nothing (ws_synapse_select_static: its scratch is a fixed array in
 the library's device image) against ws_synapse_select on a caller-owned workspace: same landmarks, bit for
 bit, on two calls in a row, the second with a smaller input (the array keeps the first call's contents, so
-whatever must start at zero has to be cleared by the call itself).  Both kernels are covered: bf16 heads that
-stay on chip, and fp32 heads that stream through the array's slabs."""
+whatever must start at zero has to be cleared by the call itself).  All kernels are covered: bf16 heads that
+stay on chip, fp32 heads that stream through the array's slabs, and short heads that need nothing of it but the flag."""
 import numpy as np
 import pytest
 
@@ -42,7 +42,11 @@ def test_select_static_matches_select_on_two_calls_in_a_row():
     first = both_ways(ws, torch, K, rho, w.k, w.alpha)
     K2 = K[:5, :1000].contiguous()
     rho2 = ws.ws_synapse_density(K2, [float(syn.bandwidth(Kh[h, :1000])) for h in range(5)])
-    both_ways(ws, torch, K2, rho2, 20, w.alpha)
+    both_ways(ws, torch, K2, rho2, 20, w.alpha)                # (one workgroup per head: touches the flag only)
+    K2 = K[:5, :1500].contiguous()                             # the resident kernel again, fewer slots than the call before it
+    rho2 = ws.ws_synapse_density(K2, [float(syn.bandwidth(Kh[h, :1500])) for h in range(5)])
+    assert ws.ws_synapse_select_plan("auto", ws.WS_BF16, 5, 1500, w.d).resident
+    both_ways(ws, torch, K2, rho2, 30, w.alpha)
     again = both_ways(ws, torch, K, rho, w.k, w.alpha)         # and back: the first result, from a used array
     assert torch.equal(first, again)
 
@@ -56,6 +60,11 @@ def test_select_static_matches_select_on_two_calls_in_a_row():
     K3 = Kd[:1, :512].contiguous()
     rho3 = ws.ws_synapse_density(K3, [float(syn.bandwidth(Kf[0, :512]))])
     both_ways(ws, torch, K3, rho3, 10, 1.0)
+    K4 = Kd[:2, :1200].contiguous()                            # streaming again, over smaller slabs
+    rho4 = ws.ws_synapse_density(K4, [float(syn.bandwidth(Kf[h, :1200])) for h in range(2)])
+    plan = ws.ws_synapse_select_plan("auto", ws.WS_F32, 2, 1200, w1.d)
+    assert not plan.resident and plan.rows_in_registers == 0
+    both_ways(ws, torch, K4, rho4, 24, 0.5)
 
     # a size beyond the fixed array is refused before anything runs
     big = torch.zeros((1, 600_000, 64), dtype=torch.float32, device="cuda")
