@@ -41,7 +41,8 @@ using namespace resident;
 constexpr unsigned kExpired = 0xFFFFFFFFu;     // no score: those are the bits of numbers >= 0
 
 struct Shared {
-    uint4 result;                          // of the exchange: dm, hi (kExpired: a wait expired), lo, dx; one read in every thread
+    // of the exchange, one read in every thread: dm, hi, lo, dx; kExpired in place of hi (without FAR: of dx) if a wait expired
+    uint4 result;
     unsigned dm[4], dx[4], hi[4], lo[4];   // one entry per wave of the workgroup
 };
 
@@ -158,7 +159,7 @@ __device__ __forceinline__ bool head_max(unsigned dm, unsigned dx, unsigned hi, 
             if (touched == 0xFFFFFFFFu && seq == 0u) good = false;   // never true: keeps the touch alive
         }
         if (lane == 0) {
-            sh.result = make_uint4(md, good ? mh : kExpired, ml, mx);
+            sh.result = FAR ? make_uint4(md, good ? mh : kExpired, ml, mx) : make_uint4(md, mh, ml, good ? 0u : kExpired);
         }
     }
     __syncthreads();
@@ -167,7 +168,7 @@ __device__ __forceinline__ bool head_max(unsigned dm, unsigned dx, unsigned hi, 
     dx_out = r.w;
     hi_out = r.y;
     lo_out = r.z;
-    return r.y != kExpired;
+    return (FAR ? r.y : r.w) != kExpired;
 }
 
 // ---- exact distances for the keys a new landmark may move ------------------------------------------------------
