@@ -341,9 +341,9 @@ __device__ __forceinline__ void wait_vmcnt()
 //
 // The contraction runs one tile ahead of the vector work through the whole sweep, across tiles, stages and blocks: at two
 // (d = 128) or three (d = 64) waves per SIMD a contraction that stands alone at the head of a column tile is not hidden by
-// the other waves.  Against the form that started each column tile with its first contraction exposed: 20.5 -> 18.4 ms for
-// 8 heads of 131072 keys at d = 128 (matrix cores busy 46 -> 56 % of the cycles), 38.4 -> 37.8 ms for 384 heads of 32768
-// keys at d = 64.  One body serves the diagonal and the one-sided blocks too (they form column sums that are not used):
+// the other waves.  Against the form that started each column tile with its first contraction exposed: 20.2 -> 18.7 ms for
+// 8 heads of 131072 keys at d = 128 (now the matrix cores are busy 54 % of the cycles, the vector pipe 73 %), 39.1 -> 38.2 ms
+// for 384 heads of 32768 keys at d = 64 (41 % and 95 %; 39 % and 90 % before).  One body serves the diagonal and the one-sided blocks too (they form column sums that are not used):
 // three copies of it do not fit the registers.
 // ------------------------------------------------------------------------------------------
 // The kernel sums of a key come from many workgroups (its own row block, and every block that visits it as
@@ -587,7 +587,7 @@ density_sym(const void *const *__restrict__ kbase, const uint4 *__restrict__ ext
 // rounds away.  The split costs 50 vector instructions per wave and stage, which run beside the matrix work.
 //
 // A stage is 32 keys; its rows are loaded one stage ahead into registers and written to the other of two LDS buffers after
-// the stage's work, so there is one barrier per stage.  One fp32 head of 512 keys: the sweep 33 -> 8 us against one over all
+// the stage's work, so there is one barrier per stage.  One fp32 head of 512 keys: the sweep 33 -> 7 us against one over all
 // ordered pairs with fp32 MFMAs.  Mean 2-norm error against 64 bits over five kinds of clouds of 200 to 6000 keys (ten kinds of
 // lattices, duplicates and offsets beside them): d = 64 0.8 to 2.2e-7, with fp32 MFMAs 1.1 to 4.3e-7; d = 128 0.7 to 2.4e-7,
 // 1.2 to 6.0e-7; no kind larger than there.

@@ -7,8 +7,8 @@
 // there for everybody.  Distances are direct differences in fp32, the score is the streaming kernel's.  One workgroup per
 // head, no wait on another one, so any number of heads may be launched.
 // Bound by the chain of a step: distances (128 cycles of vector work per row slot and wave, two waves per SIMD), two
-// reductions and three barriers.  One fp32 head of 512 keys, 10 steps: 56 us with the streaming kernel, about
-// 20 here.
+// reductions and three barriers.  One fp32 head of 512 keys, 10 steps: 56 us with the streaming kernel, 16
+// here.
 #include "select_resident_common.h"
 
 namespace ws {
