@@ -245,7 +245,8 @@ def main() -> int:
     roofline = dict(per_stage[dominant])
     plan = ws.ws_synapse_select_plan("auto", dt, w.H, w.L, w.d)
     kernel_of = {"density": "density_sym" if large else "density_sym_small",
-                 "select": "select_resident" if plan.resident else "select_small" if plan.rows_in_registers else "select_stream",
+                 "select": "select_lazy" if ws.ws_synapse_select_is_lazy(dt, w.H, w.L, w.d, w.k) else
+                           "select_resident" if plan.resident else "select_small" if plan.rows_in_registers else "select_stream",
                  "gather": "gather_rows", "attend": "attend_bf16" if bf16 else "attend_f32"}
     roofline["kernel"] = kernel_of[dominant]
     for s_ in stages:

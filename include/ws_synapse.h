@@ -118,17 +118,20 @@ int ws_synapse_density_is_symmetric(ws_dtype dt, int L, int d);
  *   idx       dev [H,k] int32, written in pick order
  *   score_out dev [H,k] fp32 winning score per step, or NULL
  *
- * Three kernels implement this call: one keeps a head's keys resident in registers and LDS for all
+ * Four kernels implement this call.  Where the heads are many and long, one that looks again only at the keys a
+ * step can depend on runs one workgroup per head (ws_synapse_select_is_lazy says where; at most 131072 keys and
+ * 4096 landmarks per head).  Of the others one keeps a head's keys resident in registers and LDS for all
  * k steps, spread over the workgroups that share the head (bf16 keys, heads that fit on chip), one
  * streams them from memory every step (any size), and one holds a short head in the registers of a
  * single workgroup (L <= 1024 at d = 64, L <= 512 at d = 128; fp32 keys, and bf16 keys of no more heads
  * than the device has compute units).  ws_synapse_select lets the library pick; ws_synapse_select_with
- * names one of the first two.  They sum a distance in different orders: picks differ between them only
+ * names the resident or the streaming one.  A workspace of the size reported before the first kernel was there is accepted:
+ * the call is then served by the others.  They sum a distance in different orders: picks differ between them only
  * where scores tie to fp32 rounding.
  *
  * Co-residency contract.  The resident and the streaming kernel are persistent: the workgroups that
  * share a head exchange their partial maxima every step and wait for each other, so the WHOLE grid has to be resident on
- * the device at once (the one-workgroup kernel waits for nobody and cannot give up).  The launch is sized from the current device (its compute-unit count and the
+ * the device at once (the two kernels with one workgroup per head wait for nobody and cannot give up).  The launch is sized from the current device (its compute-unit count and the
  * number of workgroups of the kernel a compute unit holds, both asked of the runtime at every call),
  * which guarantees this when the selection has the device to itself.  The paper runs the producer
  * beside other streams (Sec. 3.1, Sec. 4); work on other streams that holds compute units while a
@@ -162,8 +165,9 @@ ws_status ws_synapse_select_with(ws_select_kernel which, const void *K, ws_dtype
 /*
  * ws_synapse_select for callers that cannot allocate and have no workspace to hand over: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels and
- * same results as ws_synapse_select, but the scratch the kernels need (failure flag, exchange slots, and
- * the streaming kernel's distance / inverse-density slabs) lives in a fixed array inside the library's
+ * same results as ws_synapse_select (up to ties where the scratch is too small for the kernel that call would take),
+ * but the scratch the kernels need (failure flag, exchange slots, and the streaming kernel's distance /
+ * inverse-density slabs) lives in a fixed array inside the library's
  * device image: 256 bytes + 1 MiB + 4 MiB = 5 243 136 bytes per device, held until the process ends.
  * The call allocates nothing (no hipMalloc, no hipFree, no allocating library routine) and clears what it
  * needs with a small kernel on `stream`.
@@ -186,7 +190,9 @@ ws_status ws_synapse_select_static(const void *K, ws_dtype dt, int H, int L, int
  * the host. */
 ws_status ws_synapse_select_failed(const void *workspace, ws_stream stream, int *failed);
 
-/* How a selection of these sizes is launched: which kernel, how many heads are in flight at once,
+/* How a selection of these sizes is launched by the kernels that hold or stream a head's keys (where
+ * ws_synapse_select_is_lazy says 1, ws_synapse_select does without them unless its workspace is of the earlier, smaller size, as the
+ * fixed scratch of ws_synapse_select_static is for such calls): which kernel, how many heads are in flight at once,
  * how many workgroups share a head.  compute_units = 0 and workgroups_per_cu = 0 ask the current
  * device (256 and the kernels' design value where none is visible); other values answer for a
  * device of that shape (capacity planning, tests).  heads_in_flight * workgroups_per_head never
@@ -308,10 +314,14 @@ ws_status ws_synapse_inject(void *Kc, void *Vc, ws_dtype dt, int H, int Lcap, in
                             const void *Knew, const void *Vnew, int m, const int32_t *pos, float base,
                             void *workspace, size_t workspace_bytes, ws_stream stream);
 
-/* Whether ws_synapse_select would keep the keys of bf16 heads of these sizes on chip for all steps on the current
- * device: 1 = it would (the resident or the one-workgroup kernel), 0 = streaming.  0 for fp32 keys, also where the
+/* Whether bf16 heads of these sizes stay on chip for all steps on the current device where ws_synapse_select_is_lazy says 0:
+ * 1 = they do (the resident or the one-workgroup kernel), 0 = streaming.  0 for fp32 keys, also where the
  * one-workgroup kernel takes them (ws_synapse_select_plan says so).  For reports and profiles. */
 int ws_synapse_select_is_resident(ws_dtype dt, int H, int L, int d);
+
+/* Whether ws_synapse_select takes the kernel that evaluates only the keys a step can depend on, for these sizes, on the current
+ * device and with a workspace of the reported size: 1 or 0.  For reports and profiles. */
+int ws_synapse_select_is_lazy(ws_dtype dt, int H, int L, int d, int k);
 
 /* Bytes of workspace the given operation needs for these sizes (0 if none).  Arguments an
  * operation does not use are ignored.  Returns (size_t)-1 for unsupported sizes. */

@@ -80,6 +80,8 @@ def lib() -> ctypes.CDLL:
         L.ws_synapse_inject.restype = ci
         L.ws_synapse_select_is_resident.argtypes = [ci, ci, ci, ci]
         L.ws_synapse_select_is_resident.restype = ci
+        L.ws_synapse_select_is_lazy.argtypes = [ci, ci, ci, ci, ci]
+        L.ws_synapse_select_is_lazy.restype = ci
         L.ws_status_string.argtypes = [ci]
         L.ws_status_string.restype = ctypes.c_char_p
         _lib = L
@@ -157,6 +159,10 @@ def ws_synapse_workspace_bytes(op: int, dt: int, H: int, L: int, d: int, k: int 
 
 def ws_synapse_select_is_resident(dt: int, H: int, L: int, d: int) -> bool:
     return bool(lib().ws_synapse_select_is_resident(dt, H, L, d))
+
+
+def ws_synapse_select_is_lazy(dt: int, H: int, L: int, d: int, k: int) -> bool:
+    return bool(lib().ws_synapse_select_is_lazy(dt, H, L, d, k))
 
 
 def ws_synapse_density(K: torch.Tensor, sigma, rho: torch.Tensor | None = None, workspace=None, stream=None):

@@ -39,7 +39,10 @@ size_t ws_synapse_workspace_bytes(ws_op op, ws_dtype dt, int H, int L, int d, in
         return ws::density_workspace_bytes(H, L, d, dt == WS_BF16);
     case WS_OP_SELECT:
         if (H < 1 || L < 1 || L >= kMaxL) return (size_t)-1;
-        return ws::select_workspace_bytes(H, L, d, dt == WS_BF16);
+    {
+        const size_t least = ws::select_workspace_bytes(H, L, d, dt == WS_BF16), lazy = ws::lazy_select_workspace_bytes(H, L);
+        return least > lazy ? least : lazy;
+    }
     case WS_OP_GATHER:
         return 0;
     case WS_OP_ATTEND:
@@ -123,6 +126,7 @@ ws_status ws_synapse_select_with(ws_select_kernel which, const void *K, ws_dtype
     if (s != WS_OK) return s;
     ws::SelectChoice c;
     if (!ws::choose_select((int)which, dt == WS_BF16, H, L, d, ws::current_chip(), 0, c)) return WS_ERR_UNSUPPORTED;
+    if (which == WS_SELECT_AUTO) c.lazy_scratch = workspace_bytes;
     const hipError_t e = ws::launch_select(c, K, dt == WS_BF16, H, L, d, rho, k, alpha, idx, score_out, workspace,
                                            (hipStream_t)stream);
     return e == hipSuccess ? WS_OK : WS_ERR_HIP;
@@ -147,6 +151,7 @@ ws_status ws_synapse_select_static(const void *K, ws_dtype dt, int H, int L, int
                         : c.resident     ? ws::resident_select_workspace_bytes(c.res.groups)
                                          : ws::stream_select_workspace_bytes(c.stream, L);
     if (need > ws::kStaticScratchBytes) return WS_ERR_TOO_LARGE;
+    c.lazy_scratch = ws::kStaticScratchBytes;
     void *scratch_ptr = nullptr;
     if (ws::select_static_scratch(&scratch_ptr) != hipSuccess) return WS_ERR_HIP;
     const hipError_t e = ws::launch_select(c, K, dt == WS_BF16, H, L, d, rho, k, alpha, idx, score_out, scratch_ptr,

@@ -18,6 +18,7 @@
 // the index entries it still owes and leaves, so the grid always drains.
 #include <atomic>
 
+#include "../../include/ws_synapse.h"
 #include "ws_internal.h"
 
 namespace ws {
@@ -430,11 +431,25 @@ bool choose_select(int which, bool bf16, int H, int L, int d, const Chip &chip, 
     return true;
 }
 
+// The lazy kernel in place of the kernel chosen, if it is the faster one.  The resident kernel takes 3.6 us (4.55 at d = 128) per
+// step and pass over the heads at the least; the streaming one reads the keys at every step, at up to 5.6 TB/s, and takes 6 us for a step at
+// the least.
+static LazyShape lazy_instead(const SelectChoice &c, bool bf16, int H, int L, int d, int k, size_t scratch_bytes)
+{
+    const float swept = (float)H * (float)L * (float)d * (bf16 ? 2.0f : 4.0f) / 5.6e6f;
+    const float step = c.resident ? (d == 64 ? 3.6f : 4.55f) * (float)c.res.rounds : swept > 6.0f ? swept : 6.0f;
+    return select_lazy_shape(bf16, H, L, d, k, step * (float)k, current_chip(), scratch_bytes);
+}
+
 hipError_t launch_select(const SelectChoice &c, const void *K, bool bf16, int H, int L, int d, const float *rho, int k,
                          float alpha, int32_t *idx, float *score_out, void *ws, hipStream_t st)
 {
     if (c.small_rows > 0)
         return launch_select_small(K, bf16, H, L, d, rho, k, alpha, idx, score_out, reinterpret_cast<int *>(ws), st);
+    if (c.lazy_scratch > 0) {
+        const LazyShape s = lazy_instead(c, bf16, H, L, d, k, c.lazy_scratch);
+        if (s.groups > 0) return launch_select_lazy(s, K, bf16, H, L, d, rho, k, alpha, idx, score_out, ws, st);
+    }
     if (c.resident) return launch_select_resident(K, H, L, d, rho, k, alpha, idx, score_out, ws, c.res, st);
 
     const SelectPlan &p = c.stream;
@@ -470,3 +485,13 @@ hipError_t launch_select(const SelectChoice &c, const void *K, bool bf16, int H,
 }
 
 }  // namespace ws
+
+// (beside the launcher, as it answers for the choice made there)
+extern "C" int ws_synapse_select_is_lazy(ws_dtype dt, int H, int L, int d, int k)
+{
+    if ((dt != WS_F32 && dt != WS_BF16) || (d != 64 && d != 128) || H < 1 || L < 1 || L >= 1 << 24 || k < 1 || k > L) return 0;
+    const bool bf16 = dt == WS_BF16;
+    ws::SelectChoice c;
+    if (!ws::choose_select(0, bf16, H, L, d, ws::current_chip(), 0, c) || c.small_rows > 0) return 0;
+    return ws::lazy_instead(c, bf16, H, L, d, k, ws::lazy_select_workspace_bytes(H, L)).groups > 0;
+}

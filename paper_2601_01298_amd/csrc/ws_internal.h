@@ -98,12 +98,35 @@ int select_small_rows(bool bf16, int H, int L, int d, const Chip &chip);
 hipError_t launch_select_small(const void *K, bool bf16, int H, int L, int d, const float *rho, int k, float alpha,
                                int32_t *idx, float *score_out, int *fail, hipStream_t st);
 
+// Only the keys a step can depend on, one workgroup per head (select_lazy.hip).  A head in flight needs 12 bytes per key of
+// scratch; no workgroup waits on another one, so any number of heads may be in flight.
+constexpr int kLazyGroup = 64;              // keys per group
+constexpr int kMaxLazyK = 4096;             // landmarks the kernel lists in LDS
+constexpr int kLazyWaves = 8;               // per workgroup
+constexpr int kMaxLazyL = kLazyGroup * 64 * kLazyWaves * 4;     // four groups per lane
+constexpr int kMaxLazyHeads = 512;          // heads in flight the reported workspace is sized for
+struct LazyShape {
+    int slots;    // groups a lane keeps
+    int per_cu;   // workgroups per compute unit
+    int groups;   // heads in flight; 0 = not this kernel
+};
+static inline size_t lazy_slab_bytes(int L) { return 3 * round_up((size_t)L, kLazyGroup) * sizeof(float); }
+static inline size_t lazy_select_workspace_bytes(int H, int L)
+{
+    return kSelectFlagBytes + (size_t)(H < kMaxLazyHeads ? H : kMaxLazyHeads) * lazy_slab_bytes(L);
+}
+LazyShape select_lazy_shape(bool bf16, int H, int L, int d, int k, float other_us, const Chip &chip, size_t scratch_bytes);
+hipError_t launch_select_lazy(const LazyShape &shape, const void *K, bool bf16, int H, int L, int d, const float *rho, int k,
+                              float alpha, int32_t *idx, float *score_out, void *ws, hipStream_t st);
+
 // which: 0 = the library chooses, 1 = streaming kernel, 2 = resident kernel
 struct SelectChoice {
     bool resident;
     int small_rows;      // > 0: one workgroup per head; resident is false and stream says how many heads run at once
     SelectPlan stream;
     ResidentShape res;
+    // > 0: nobody named a kernel, and the scratch behind `ws` has this many bytes: launch_select may take the lazy kernel
+    size_t lazy_scratch = 0;
 };
 // false when `which` asks for the resident kernel and no instance fits these sizes on this chip
 bool choose_select(int which, bool bf16, int H, int L, int d, const Chip &chip, size_t slab_budget, SelectChoice &c);

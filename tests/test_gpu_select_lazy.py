@@ -1,0 +1,132 @@
+"""The selection that evaluates only the keys a step can depend on (long heads, many of them): at the edges of its groups,
+records and landmark ring, against the oracle and against the streaming kernel.  Keys on a lattice of small integers have distances
+that every kernel forms without rounding, so there the picks and scores of all kernels are the same bits, ties included."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def clouds(L, d, seed, kind):
+    """Two clouds and densities as device tensors, fp32."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    if kind == "lattice":       # coordinates 0 ... 3 in eight dimensions, the rest equal: ties and duplicates everywhere
+        K = torch.full((2, L, d), 2.0, device="cuda")
+        K[:, :, :8] = torch.randint(0, 4, (2, L, 8), generator=gen, device="cuda").float()
+        return K, 2.0 ** -torch.randint(1, 5, (2, L), generator=gen, device="cuda").float()
+    K = 2.0 * torch.randn((2, 16, d), generator=gen, device="cuda")
+    K = torch.gather(K, 1, torch.randint(0, 16, (2, L, 1), generator=gen, device="cuda").expand(-1, -1, d))
+    K += 0.5 * torch.randn((2, L, d), generator=gen, device="cuda")
+    far = torch.rand((2, L), generator=gen, device="cuda") < 0.003
+    K[far] = torch.rand((int(far.sum()), d), generator=gen, device="cuda") * 16.0 - 8.0
+    rho = torch.rand((2, L), generator=gen, device="cuda") * 0.9 + 0.1
+    rho[far] = 0.1
+    return K, rho
+
+
+def heads(K, rho, H, dtype):
+    import torch
+    K = K.to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    copies = torch.arange(H, device="cuda") % 2
+    return K[copies], rho[copies].contiguous(), copies
+
+
+# one, two and four records per lane, the last group whole, ragged and a single key; two heads per compute unit (H = 384)
+SHAPES = [("bf16", 64, 384, 32768, 500), ("bf16", 64, 200, 32767, 900), ("bf16", 64, 200, 32769, 700), ("bf16", 64, 200, 40001, 500),
+          ("bf16", 64, 100, 65537, 1000), ("bf16", 64, 96, 131072, 1300), ("bf16", 128, 200, 16449, 600), ("bf16", 128, 100, 65536, 1000),
+          ("f32", 64, 220, 4095, 90), ("f32", 64, 250, 4160, 90), ("f32", 128, 80, 16384, 500)]
+
+
+@pytest.mark.parametrize("dtype,d,H,L,k", SHAPES)
+@pytest.mark.parametrize("alpha", [0.5, 1.0, 0.0])
+def test_lattice_picks_are_the_streaming_kernels(dtype, d, H, L, k, alpha):
+    import torch
+    from paper_2601_01298_amd import binding as ws
+    assert ws.ws_synapse_select_is_lazy(ws.WS_BF16 if dtype == "bf16" else ws.WS_F32, H, L, d, k)
+    K2, rho2 = clouds(L, d, L + d, "lattice")
+    K, rho, copies = heads(K2, rho2, H, dtype)
+    idx, score = ws.ws_synapse_select(K, rho, k, alpha, want_score=True)
+    ref, ref_score = ws.ws_synapse_select(K[:2].contiguous(), rho[:2].contiguous(), k, alpha, want_score=True, kernel="stream")
+    assert torch.equal(idx, ref[copies]) and torch.equal(score, ref_score[copies])
+
+
+@pytest.mark.parametrize("dtype,d,H,L,k", [("bf16", 64, 384, 32768, 400), ("bf16", 128, 160, 16390, 400), ("f32", 64, 220, 4100, 90)])
+def test_picks_against_the_oracle(dtype, d, H, L, k):
+    """Clusters and far points, picked first: D_max falls at most of the first steps, and more landmarks wait for a group than a
+    visit looks at."""
+    import torch
+    from oracle import ws_oracle as oracle
+    from paper_2601_01298_amd import binding as ws
+    assert ws.ws_synapse_select_is_lazy(ws.WS_BF16 if dtype == "bf16" else ws.WS_F32, H, L, d, k)
+    K2, rho2 = clouds(L, d, 3 * L + d, "clusters")
+    K, rho, copies = heads(K2, rho2, H, dtype)
+    idx, score = ws.ws_synapse_select(K, rho, k, 0.5, want_score=True)
+    assert torch.equal(idx, idx[:2][copies]) and torch.equal(score, score[:2][copies])
+    for h in range(2):
+        Kh, rh, got = K[h].float().cpu().numpy(), rho[h].cpu().numpy(), idx[h].cpu().numpy()
+        ref, ref_score, _ = oracle.select(Kh, rh, k, 0.5)
+        if not np.array_equal(got, ref):
+            forks, _, deficit = oracle.select_verify(Kh, rh, k, 0.5, got)
+            assert forks >= 0 and deficit.max() <= 1e-5         # the near-tie rule of the parity tests
+        same = np.cumprod(got == ref).astype(bool)
+        assert np.allclose(score[h].cpu().numpy()[same], ref_score[same], rtol=2e-5, atol=0)
+
+
+def test_every_key_at_an_offset_and_at_a_tiny_scale():
+    """Offsets far above the spread (the screen can tell nothing apart) and rows whose squares underflow in it: every pair is
+    evaluated, and the picks are still the streaming kernel's."""
+    import torch
+    from paper_2601_01298_amd import binding as ws
+    H, L, d, k = 220, 4096, 64, 90
+    K2, rho2 = clouds(L, d, 11, "lattice")
+    for K0 in (K2 + 512.0, K2 * 2.0 ** -62):
+        K, rho, copies = heads(K0, rho2, H, "f32")
+        idx = ws.ws_synapse_select(K, rho, k, 0.5)
+        ref = ws.ws_synapse_select(K[:2].contiguous(), rho[:2].contiguous(), k, 0.5, kernel="stream")
+        assert torch.equal(idx, ref[copies])
+
+
+def test_the_earlier_workspace_is_still_accepted():
+    """A caller may have kept the size reported before this kernel needed a slab for every head in flight: 32 heads' slabs."""
+    import torch
+    from paper_2601_01298_amd import binding as ws
+    H, L, d, k = 200, 32768, 64, 500
+    K2, rho2 = clouds(L, d, 5, "lattice")
+    K, rho, copies = heads(K2, rho2, H, "bf16")
+    old = 256 + 32 * 2 * 64 * 8 + 2 * 32 * L * 4
+    assert old < ws.ws_synapse_workspace_bytes(ws.WS_OP_SELECT, ws.WS_BF16, H, L, d, k)
+    small = torch.empty(old, dtype=torch.uint8, device="cuda")
+    idx = torch.empty((H, k), dtype=torch.int32, device="cuda")
+    ws._check(ws.lib().ws_synapse_select(K.data_ptr(), ws.WS_BF16, H, L, d, rho.data_ptr(), k, 0.5, idx.data_ptr(), None,
+                                         small.data_ptr(), old, torch.cuda.current_stream().cuda_stream), "select")
+    assert not ws.ws_synapse_select_failed(small)
+    assert torch.equal(idx, ws.ws_synapse_select(K, rho, k, 0.5))
+
+
+def test_under_graph_capture():
+    import torch
+    from paper_2601_01298_amd import binding as ws
+    H, L, d, k = 384, 32768, 64, 400
+    assert ws.ws_synapse_select_is_lazy(ws.WS_BF16, H, L, d, k)
+    K2, rho2 = clouds(L, d, 21, "clusters")
+    K, rho, _ = heads(K2, rho2, H, "bf16")
+    idx = torch.empty((H, k), dtype=torch.int32, device="cuda")
+    space = torch.empty(ws.ws_synapse_workspace_bytes(ws.WS_OP_SELECT, ws.WS_BF16, H, L, d, k), dtype=torch.uint8, device="cuda")
+    run = lambda: ws.ws_synapse_select(K, rho, k, 0.5, idx=idx, workspace=space, check=False)
+    run()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        run()
+    for flip in (False, True, False):
+        if flip:
+            K.copy_(K.flip(1).contiguous())
+            rho.copy_(rho.flip(1).contiguous())
+        run()
+        torch.cuda.synchronize()
+        ref = idx.clone()
+        idx.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(idx, ref) and not ws.ws_synapse_select_failed(space)
