@@ -7,8 +7,8 @@
 //                 from one read of the key rows; writes them (log2 units; staged in LDS, one coalesced pass per tile) and
 //                 a (max, sum of exp2) pair per (query head, tile).  The dot products are MFMA tiles of 16 keys by up to
 //                 16 query heads, whose operand is fetched from memory as it is, 64 bytes of a row by four lanes
-//                 (mass_logits_rows, for fp32 keys, one or two query heads, and workspaces that hold a pair per 2048
-//                 tokens only: 2048 tokens, a lane group per row);
+//                 (mass_logits_rows, for fp32 keys, one or two query heads where the chip is full, and workspaces that hold a
+//                 pair per 2048 tokens only: 2048 tokens, a lane group per row);
 //   mass_combine  folds the pairs of a layer's heads into (max, 1/sum) per head, then per token adds
 //                 the normalised exponentials over the heads and writes the result to every KV head
 //                 of the layer (as A, or as 1/A when it is to serve as the density).
@@ -22,6 +22,7 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kMassTile = 1024;    // tokens per workgroup of mass_logits ...
 constexpr int kRowTile = 2048;     // ... and of mass_logits_rows
+constexpr int kMassFull = 512;     // tiles of mass_logits that fill the chip (a fixed number: the result follows the sizes only)
 constexpr int kMassMaxHq = 128;    // query heads per layer
 constexpr float kLog2e = 1.4426950408889634f;
 
@@ -65,7 +66,7 @@ __device__ __forceinline__ void merge(float &m, float &s, float m2, float s2)
     s = a + b;
 }
 
-// The form for fp32 keys and for one or two query heads per KV head: a lane group per row reads it whole, and the
+// The form for fp32 keys and, where the chip is full, for one or two query heads per KV head: a lane group per row reads it whole, and the
 // arithmetic is little enough (24 x 16 heads of 32768 keys, d = 64, one query head each: 0.30 ms, 0.36 through the MFMA form).
 // It also serves more query heads where the caller's workspace has a pair per 2048 tokens.
 template <bool BF16, int D, int MAXG>
@@ -317,10 +318,10 @@ void run_logits(bool rows, const void *K, const void *Q, float *z, float2 *part,
                 hipStream_t st)
 {
     auto kern = mass_logits_rows<BF16, D, 8>;
-    if (g == 1) kern = mass_logits_rows<BF16, D, 1>;
+    if (!rows) kern = g <= 4 ? mass_logits<D, 4> : mass_logits<D, 8>;
+    else if (g == 1) kern = mass_logits_rows<BF16, D, 1>;
     else if (g == 2) kern = mass_logits_rows<BF16, D, 2>;
-    else if (rows && g <= 4) kern = mass_logits_rows<BF16, D, 4>;
-    else if (!rows) kern = g <= 4 ? mass_logits<D, 4> : mass_logits<D, 8>;
+    else if (g <= 4) kern = mass_logits_rows<BF16, D, 4>;
     hipLaunchKernelGGL(kern, dim3(nblk, GHkv), dim3(256), 0, st, K, Q, z, part, L, g, scale2, nblk);
 }
 
@@ -338,9 +339,12 @@ hipError_t launch_attention_mass(const void *K, const void *Q, bool bf16, int G,
     // Three and more query heads per KV head: 0.16 to 1.0 of the row form's time (2 heads of 32768 keys, d = 128, eight query
     // heads: 124 -> 20 us; 8 heads of 300 keys: equal).  One or two, where the chip is full (64 heads of 32768 keys, 8 of 131072,
     // 128 of 8192, both dimensions): the row form is 0.80 to 1.02 of the matrix cores' time (24 x 16 heads of 32768 keys, d = 64:
-    // 298 us against 360; d = 128, two query heads: 592 against 692).  Where it is not (8 heads of 4096 keys, 2 of 32768) the row
-    // form loses, 26 us against 14 at d = 128; it serves there too, as it always has.
-    const bool rows = !bf16 || g <= 2 || ws_bytes < mass_workspace_bytes(G, Hq, L);
+    // 298 us against 360; d = 128, two query heads: 592 against 692).  Below 512 tiles of 1024 keys the row form, with its larger
+    // tiles and its longer chain per row, takes 1.0 to 2.6 times as long: one query head, d = 64, 480 tiles 25.4 us against 19.6, 8
+    // tiles 17.0 against 15.6; d = 128, 256 tiles 39.4 against 18.7; two, d = 128, 32 tiles 35.6 against 15.7.  Error against 64 bits over 48 of
+    // these sizes: 0.96 of the row form's.
+    const bool idle = (long long)G * Hkv * ((L + kMassTile - 1) / kMassTile) < kMassFull;
+    const bool rows = !bf16 || (g <= 2 && !idle) || ws_bytes < mass_workspace_bytes(G, Hq, L);
     const MassWs w = mass_layout(G, Hq, L, rows ? kRowTile : kMassTile);
     char *base = reinterpret_cast<char *>(ws);
     float *z = reinterpret_cast<float *>(base + w.z);
