@@ -129,21 +129,22 @@ append_sweep(const void *__restrict__ Kv, const float *__restrict__ rho_old, flo
     }
 }
 
-// The form for bf16 keys and three and more new rows, where the direct differences of every pair are what the sweep is bound by
+// The form for bf16 keys and more than a few new rows, where the direct differences of every pair are what the sweep is bound by
 // (two instructions per element and pair against a read of two bytes per element).
 //
 // The dot products of 64 keys with up to 16 (CT = 2: 32) new rows are MFMA tiles, operands fetched as they lie in memory, and
-// |k - s|^2 = (|k|^2 - k.s) + (|s|^2 - k.s), formed for the two halves of the elements.  That is as exact as differences where the two rows are far apart, and loses
-// what |k|^2 + |s|^2 exceeds the distance by where they are near: a pair nearer than kNear of it is evaluated by direct
-// differences, eight lanes (16 at d = 128) to a pair, out of a list of the wave.  A wave that finds a
-// fifth of its pairs near (rows that lie near each other as measured from the origin) evaluates the rest of its tile directly.
+// |k - s|^2 = (|k|^2 - k.s) + (|s|^2 - k.s).  That is as exact as differences where the two rows are far apart, and loses what
+// |k|^2 + |s|^2 exceeds the distance by where they are near: a pair nearer than kNear of it is evaluated by direct differences,
+// eight lanes (16 at d = 128) to a pair, out of a list of the wave.  A wave that finds a fifth of its pairs near (rows that lie
+// near each other as measured from the origin) evaluates the rest of its tile directly: from there the list would cost more.
 // Every lane keeps the column sums of its rows, summed over the lanes at the end.
 //
-// Bound by the read of the keys as one new row is: 384 heads of 32768 keys, d = 64, 8 rows 540 -> 380 us (1 row: 317), 16 rows 1020 ->
-// 380; 8 heads of 131072, d = 128, 8 rows 150 -> 79 us, 32 rows 410 -> 86.  New rows out of the clusters of the old, so that a few
-// per cent of the pairs go through the list: 545 -> 480, 1030 -> 555, 145 -> 109.  All pairs near (keys at an offset of 20 per
-// coordinate): 530 -> 620, 1000 -> 1065, 146 -> 160, as the registers of the other form leave the direct loop half the waves.
-// Fewer rows than the line stay with append_sweep (6 rows, d = 64, near pairs: 425 against 475; 3 rows, d = 128: 92 against 97).
+// Bound by the read of the keys as one new row is: 384 heads of 32768 keys, d = 64, 8 rows 540 -> 380 us (1 row: 317), 16 rows 990 ->
+// 380; 8 heads of 131072, d = 128, 8 rows 148 -> 78 us, 32 rows 410 -> 84.  New rows out of the clusters of the old, so that a few
+// per cent of the pairs go through the list: 547 -> 480, 987 -> 560, 147 -> 107.  All pairs near (keys at an offset of 20 per
+// coordinate), so in the direct loop: 541 -> 443, 943 -> 775, 146 -> 117; with four keys in flight and an exponential in every lane
+// of a group it took 619, 1065 and 160.  Fewer rows than the line stay with append_sweep (6 rows, d = 64, near pairs: 425
+// against 475; 3 rows, d = 128: 92 against 97).
 // Mean error of the new rows' densities over 36 refreshes: 0.73 of append_sweep's with its sums in fp32 to the end.
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
@@ -160,6 +161,29 @@ __device__ __forceinline__ float quad_sum(float v)
     v = __uint_as_float(a.x) + __uint_as_float(a.y);
     const u32x2_t b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     return __uint_as_float(b.x) + __uint_as_float(b.y);
+}
+
+// Eight values of each lane summed over the LPR lanes of its group: the sum of value u ends up in lane u (LPR = 8), in lanes 2 u and
+// 2 u + 1 (LPR = 16).  Half the values change hands at every step, so one lane is left with one exponential to form instead of eight.
+template <int CTRL>
+__device__ __forceinline__ float pass_on(bool upper, float low, float high)
+{
+    const float keep = upper ? high : low, give = upper ? low : high;
+    return keep + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(give), CTRL, 0xF, 0xF, false));
+}
+
+template <int LPR>
+__device__ __forceinline__ float group_scatter(const float (&v)[8], int part)
+{
+    static_assert(LPR == 8 || LPR == 16, "");
+    constexpr int BIT = LPR / 2;        // of the lane: which half of the values it keeps first
+    float f[4], t[2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) f[i] = pass_on<LPR == 16 ? 0x140 : 0x141>((part & BIT) != 0, v[i], v[i + 4]);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) t[i] = pass_on<LPR == 16 ? 0x141 : 0x4E>((part & BIT / 2) != 0, f[i], f[i + 2]);
+    if constexpr (LPR == 8) return pass_on<0xB1>((part & 1) != 0, t[0], t[1]);
+    else return dpp_add_f32<0xB1>(pass_on<0x4E>((part & 2) != 0, t[0], t[1]));
 }
 
 template <int D, int CT>
@@ -246,159 +270,150 @@ append_gram(const uint16_t *__restrict__ K, const float *__restrict__ rho_old, f
     };
 
     const int part = lane % LPR, grp = lane / LPR;
-    bool far = true;                                // the MFMA form goes on
-    for (int b0 = lo + wave * KB; b0 < hi; b0 += 4 * KB) {
+    int b0 = lo + wave * KB;
+    for (; b0 < hi; b0 += 4 * KB) {
         const bool tail = b0 + KB > Lold;           // new rows among the keys: a row's own 1 joins its sum last, in append_finish
-        if (far) {
-            u32x4_t k4[KT][NK];
+        bool far = true;
+        u32x4_t k4[KT][NK];
+#pragma unroll
+        for (int j = 0; j < KT; ++j)
+#pragma unroll
+            for (int kk = 0; kk < NK; ++kk) k4[j][kk] = kn[j][kk];
+        fetch(b0 + 4 * KB);                         // (past the tile: its last row, not used)
+        float nk[KT], add[KT];
+        bool in[KT];
+#pragma unroll
+        for (int j = 0; j < KT; ++j) {
+            const f32x4_t g = products(k4[j], k4[j]);       // |k|^2: its diagonal
+            const float dg = (c & 2) ? ((c & 1) ? g[3] : g[2]) : ((c & 1) ? g[1] : g[0]);
+            nk[j] = quad_sum(q == c >> 2 ? dg : 0.0f);
+            in[j] = b0 + j * 16 + c < hi;
+            add[j] = 0.0f;
+        }
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+            float d2[KT][4];
+            unsigned long long near[KT][4];
+            int cnt = 0;
+#pragma unroll
+            for (int j = 0; j < KT; ++j) {
+                const f32x4_t dot = products(a[ct], k4[j]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    d2[j][e] = (nk[j] - dot[e]) + (ns[ct][e] - dot[e]);
+                    // (a NaN is near)
+                    near[j][e] = __ballot(in[j] && use[ct][e] && !(d2[j][e] >= kNear * (nk[j] + ns[ct][e])));
+                    cnt += (int)__popcll(near[j][e]);
+                }
+            }
+            if (ct == 0 && cnt > kMany * min(m, 16)) {
+                far = false;
+                break;
+            }
+            for (int first = 0; first < cnt; first += kPairs) {     // the list, as often as it takes (once for 16 rows)
+                int at = -first;
+#pragma unroll
+                for (int j = 0; j < KT; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const unsigned long long n = near[j][e];
+                        if (n == 0ull) continue;
+                        const int w = at + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(n >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)n, 0u));
+                        if ((n >> lane & 1) && (CT == 1 || (w >= 0 && w < kPairs)))
+                            list[wave][w] = (unsigned)(j * 16 + c) << 8 | (unsigned)(16 * ct + 4 * q + e);
+                        at += (int)__popcll(n);
+                    }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                const int some = CT == 1 ? cnt : min(cnt - first, kPairs);
+                for (int i = 0; i < some; i += GRP) {
+                    const int w = min(i + grp, some - 1), r = (int)(list[wave][w] & 0xFFu);
+                    float x[8], acc = 0.0f;
+                    widen16<true>(*reinterpret_cast<const uint4 *>(
+                                      Kh + (size_t)min(b0 + (int)(list[wave][w] >> 8), hi - 1) * D + part * 8), x);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const float t = x[e] - nr[r][part * 8 + e];
+                        acc = fmaf(t, t, acc);
+                    }
+                    acc = lane_group_sum<LPR>(acc);
+                    if (part == 0 && i + grp < some) res[wave][w] = acc;
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                at = -first;
+#pragma unroll
+                for (int j = 0; j < KT; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const unsigned long long n = near[j][e];
+                        if (n == 0ull) continue;
+                        const int w = at + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(n >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)n, 0u));
+                        if ((n >> lane & 1) && (CT == 1 || (w >= 0 && w < kPairs))) d2[j][e] = res[wave][w];
+                        at += (int)__popcll(n);
+                    }
+            }
 #pragma unroll
             for (int j = 0; j < KT; ++j)
 #pragma unroll
-                for (int kk = 0; kk < NK; ++kk) k4[j][kk] = kn[j][kk];
-            fetch(b0 + 4 * KB);                     // (past the tile: its last row, not used)
-            float nk[KT], add[KT];
-            bool in[KT];
-#pragma unroll
-            for (int j = 0; j < KT; ++j) {
-                const f32x4_t g = products(k4[j], k4[j]);       // |k|^2: its diagonal
-                const float dg = (c & 2) ? ((c & 1) ? g[3] : g[2]) : ((c & 1) ? g[1] : g[0]);
-                nk[j] = quad_sum(q == c >> 2 ? dg : 0.0f);
-                in[j] = b0 + j * 16 + c < hi;
-                add[j] = 0.0f;
-            }
-#pragma unroll
-            for (int ct = 0; ct < CT; ++ct) {
-                float d2[KT][4];
-                unsigned long long near[KT][4];
-                int cnt = 0;
-#pragma unroll
-                for (int j = 0; j < KT; ++j) {
-                    const f32x4_t dot = products(a[ct], k4[j]);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        d2[j][e] = (nk[j] - dot[e]) + (ns[ct][e] - dot[e]);
-                        // (a NaN is near)
-                        near[j][e] = __ballot(in[j] && use[ct][e] && !(d2[j][e] >= kNear * (nk[j] + ns[ct][e])));
-                        cnt += (int)__popcll(near[j][e]);
-                    }
+                for (int e = 0; e < 4; ++e) {
+                    d2[j][e] = in[j] && use[ct][e] ? __builtin_amdgcn_exp2f(-d2[j][e] * s2) : 0.0f;
+                    add[j] += d2[j][e];
                 }
-                if (ct == 0 && cnt > kMany * min(m, 16)) {
-                    far = false;
-                    break;
-                }
-                for (int first = 0; first < cnt; first += kPairs) {     // the list, as often as it takes (once for 16 rows)
-                    int at = -first;
-#pragma unroll
-                    for (int j = 0; j < KT; ++j)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const unsigned long long n = near[j][e];
-                            if (n == 0ull) continue;
-                            const int w = at + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(n >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)n, 0u));
-                            if ((n >> lane & 1) && (CT == 1 || (w >= 0 && w < kPairs)))
-                                list[wave][w] = (unsigned)(j * 16 + c) << 8 | (unsigned)(16 * ct + 4 * q + e);
-                            at += (int)__popcll(n);
-                        }
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                    const int some = CT == 1 ? cnt : min(cnt - first, kPairs);
-                    for (int i = 0; i < some; i += GRP) {
-                        const int w = min(i + grp, some - 1), r = (int)(list[wave][w] & 0xFFu);
-                        float x[8], acc = 0.0f;
-                        widen16<true>(*reinterpret_cast<const uint4 *>(
-                                          Kh + (size_t)min(b0 + (int)(list[wave][w] >> 8), hi - 1) * D + part * 8), x);
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) {
-                            const float t = x[e] - nr[r][part * 8 + e];
-                            acc = fmaf(t, t, acc);
-                        }
-                        acc = lane_group_sum<LPR>(acc);
-                        if (part == 0 && i + grp < some) res[wave][w] = acc;
-                    }
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                    __builtin_amdgcn_wave_barrier();
-                    at = -first;
-#pragma unroll
-                    for (int j = 0; j < KT; ++j)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const unsigned long long n = near[j][e];
-                            if (n == 0ull) continue;
-                            const int w = at + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(n >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)n, 0u));
-                            if ((n >> lane & 1) && (CT == 1 || (w >= 0 && w < kPairs))) d2[j][e] = res[wave][w];
-                            at += (int)__popcll(n);
-                        }
-                }
+            if (tail) {
 #pragma unroll
                 for (int j = 0; j < KT; ++j)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        d2[j][e] = in[j] && use[ct][e] ? __builtin_amdgcn_exp2f(-d2[j][e] * s2) : 0.0f;
-                        add[j] += d2[j][e];
-                    }
-                if (tail) {
-#pragma unroll
-                    for (int j = 0; j < KT; ++j)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (b0 + j * 16 + c - Lold == 16 * ct + 4 * q + e) d2[j][e] = 0.0f;
-                }
-#pragma unroll
-                for (int j = 0; j < KT; ++j)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) col[ct][e] += d2[j][e];
+                    for (int e = 0; e < 4; ++e)
+                        if (b0 + j * 16 + c - Lold == 16 * ct + 4 * q + e) d2[j][e] = 0.0f;
             }
-            if (far) {
 #pragma unroll
-                for (int j = 0; j < KT; ++j) {
-                    const float t = quad_sum(add[j]);
-                    if (q == 0 && in[j]) added[b0 + j * 16 + c - lo] = t;
-                }
-                continue;
-            }
+            for (int j = 0; j < KT; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) col[ct][e] += d2[j][e];
         }
-        // direct differences, a lane group per key, four keys in flight
-        constexpr int UN = 4;
-        for (int r0 = 0; r0 < KB; r0 += UN * GRP) {
-            float x[UN][8], add[UN];
+        if (!far) break;
+#pragma unroll
+        for (int j = 0; j < KT; ++j) {
+            const float t = quad_sum(add[j]);
+            if (q == 0 && in[j]) added[b0 + j * 16 + c - lo] = t;
+        }
+    }
+    // direct differences, a lane group per key, eight keys in flight (at d = 64 those of two turns)
+    constexpr int UN = 8, TURNS = UN * GRP / KB;
+    for (; b0 < hi; b0 += TURNS * 4 * KB) {
+        const bool tail = b0 + (TURNS - 1) * 4 * KB + KB > Lold;
+        float x[UN][8];
+        auto key = [&](int u) { return b0 + u * GRP / KB * 4 * KB + u * GRP % KB + grp; };
+#pragma unroll
+        for (int u = 0; u < UN; ++u) {
+            const u32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(Kh + (size_t)min(key(u), hi - 1) * D + part * 8));
+            widen16<true>(make_uint4(v.x, v.y, v.z, v.w), x[u]);
+        }
+        const int mine = key(LPR == 8 ? part : part >> 1);
+        float add = 0.0f;
+        for (int r = 0; r < m; ++r) {
+            float y[8], w[UN];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) y[e] = nr[r][part * 8 + e];
 #pragma unroll
             for (int u = 0; u < UN; ++u) {
-                const u32x4_t v = __builtin_nontemporal_load(
-                    reinterpret_cast<const u32x4_t *>(Kh + (size_t)min(b0 + r0 + u * GRP + grp, hi - 1) * D + part * 8));
-                widen16<true>(make_uint4(v.x, v.y, v.z, v.w), x[u]);
-                add[u] = 0.0f;
-            }
-            for (int r = 0; r < m; ++r) {
-                float y[8], w[UN];
+                w[u] = 0.0f;
 #pragma unroll
-                for (int e = 0; e < 8; ++e) y[e] = nr[r][part * 8 + e];
-#pragma unroll
-                for (int u = 0; u < UN; ++u) {
-                    float acc = 0.0f;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const float df = x[u][e] - y[e];
-                        acc = fmaf(df, df, acc);
-                    }
-                    acc = lane_group_sum<LPR>(acc);
-                    w[u] = b0 + r0 + u * GRP + grp < hi ? __builtin_amdgcn_exp2f(-acc * s2) : 0.0f;
-                    add[u] += w[u];
-                }
-                if (tail) {
-#pragma unroll
-                    for (int u = 0; u < UN; ++u)
-                        if (b0 + r0 + u * GRP + grp - Lold == r) w[u] = 0.0f;
-                }
-                if (part == 0) cd[r][wave * GRP + grp] += (w[0] + w[1]) + (w[2] + w[3]);    // slot private to this row group
-            }
-            if (part == 0) {
-#pragma unroll
-                for (int u = 0; u < UN; ++u) {
-                    const int i = b0 + r0 + u * GRP + grp;
-                    if (i < hi) added[i - lo] = add[u];
+                for (int e = 0; e < 8; ++e) {
+                    const float df = x[u][e] - y[e];
+                    w[u] = fmaf(df, df, w[u]);
                 }
             }
+            float one = group_scatter<LPR>(w, part);
+            one = mine < hi ? __builtin_amdgcn_exp2f(-one * s2) : 0.0f;
+            add += one;
+            if (tail && mine - Lold == r) one = 0.0f;
+            if constexpr (LPR == 16) one = part & 1 ? 0.0f : one;
+            one = lane_group_sum<LPR>(one);
+            if (part == 0) cd[r][wave * GRP + grp] += one;      // slot private to this row group
         }
+        if (mine < hi && (LPR == 8 || !(part & 1))) added[mine - lo] = add;
     }
     // column sums: the 16 keys of a tile share a row of lanes
 #pragma unroll
