@@ -22,7 +22,7 @@ typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 constexpr int kAppTile = 2048;
 constexpr int kAppMaxM = 32;
-constexpr int kGramRows64 = 8, kGramRows128 = 5;    // new rows from which bf16 keys go through append_gram
+constexpr int kGramRows64 = 8, kGramRows128 = 4;    // new rows from which bf16 keys go through append_gram
 
 constexpr int kAppChunk = 768;               // heads per launch: their scales travel as a kernel argument (3 KB)
 
@@ -46,6 +46,36 @@ __device__ __forceinline__ void widen16(const uint4 &q, float *f)
     }
 }
 
+// N values of each lane summed over the LPR lanes of its group, the sums dealt out to the lanes: lane i is left with the sum of value
+// i / (LPR / N).  While there is more than one value, half of them change hands at every step, so a lane of the group is left with one
+// exponential to form instead of N.  The partners (mirror 16, mirror 8, xor 2, xor 1) are reached by DPP; a mirror also turns the lower bits
+// of the lane around, which nothing depends on yet when it comes first.
+template <int BIT>
+__device__ __forceinline__ float partner(float v)
+{
+    if constexpr (BIT == 16) return __shfl_xor(v, 16);
+    else return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), BIT == 8 ? 0x140 : BIT == 4 ? 0x141 : BIT == 2 ? 0x4E : 0xB1,
+                                                           0xF, 0xF, false));
+}
+
+template <int LPR, int N>
+__device__ __forceinline__ float group_scatter(const float (&v)[N], int part)
+{
+    constexpr int BIT = LPR / 2;
+    if constexpr (LPR == 1) return v[0];
+    else if constexpr (N == 1) {
+        const float t[1] = {v[0] + partner<BIT>(v[0])};
+        return group_scatter<BIT, 1>(t, part);
+    } else {
+        const bool upper = (part & BIT) != 0;
+        float t[N / 2];
+#pragma unroll
+        for (int i = 0; i < N / 2; ++i)
+            t[i] = (upper ? v[i + N / 2] : v[i]) + partner<BIT>(upper ? v[i] : v[i + N / 2]);
+        return group_scatter<BIT, N / 2>(t, part);
+    }
+}
+
 template <bool BF16, int D>
 __global__ void __launch_bounds__(256)
 append_sweep(const void *__restrict__ Kv, const float *__restrict__ rho_old, float *__restrict__ rho_new,
@@ -56,6 +86,9 @@ append_sweep(const void *__restrict__ Kv, const float *__restrict__ rho_old, flo
     constexpr int LPR = D / PER;
     constexpr int RP = 256 / LPR;
     constexpr int UN = 4;
+    // The sums of a turn's keys are dealt out, one exponential per lane.  With every exponential in all the lanes of a group before: d = 64,
+    // 384 heads of 32768 keys, 6 rows 430 -> 358 us, 4 rows 335 -> 323, fewer the same (bound by the read); fp32, 192 heads, 8 rows
+    // 445 -> 333, 32 rows 1446 -> 1085; fp32, d = 128, 4 heads of 131072, 1 row 98 -> 91, 32 rows 668 -> 594; bf16, d = 128 the same.
     __shared__ float nr[kAppMaxM][D];        // the new rows, widened
     __shared__ float cs[kAppMaxM][RP];       // column sums, one slot per row group
     __shared__ float added[kAppTile];        // what the new rows add to each old key of the tile
@@ -77,7 +110,7 @@ append_sweep(const void *__restrict__ Kv, const float *__restrict__ rho_old, flo
     const int lo = blk * kAppTile, hi = min(L, lo + kAppTile);
     for (int r0 = lo; r0 < hi; r0 += UN * RP) {
         uint4 q[UN];
-        float x[UN][PER], add[UN];
+        float x[UN][PER], add = 0.0f;
 #pragma unroll
         for (int u = 0; u < UN; ++u) {
             const int i = min(r0 + u * RP + rsub, hi - 1);
@@ -86,37 +119,28 @@ append_sweep(const void *__restrict__ Kv, const float *__restrict__ rho_old, flo
             q[u] = make_uint4(v.x, v.y, v.z, v.w);
         }
 #pragma unroll
-        for (int u = 0; u < UN; ++u) {
-            widen16<BF16>(q[u], x[u]);
-            add[u] = 0.0f;
-        }
+        for (int u = 0; u < UN; ++u) widen16<BF16>(q[u], x[u]);
+        const int mine = r0 + sub / (LPR / UN) * RP + rsub;     // the key whose sums this lane is left with
         for (int r = 0; r < m; ++r) {
-            float y[PER];
+            float y[PER], acc[UN];
 #pragma unroll
             for (int e = 0; e < PER; ++e) y[e] = nr[r][sub * PER + e];
-            float col = 0.0f;
 #pragma unroll
             for (int u = 0; u < UN; ++u) {
-                float acc = 0.0f;
+                acc[u] = 0.0f;
 #pragma unroll
                 for (int e = 0; e < PER; ++e) {
                     const float t = x[u][e] - y[e];
-                    acc = fmaf(t, t, acc);
+                    acc[u] = fmaf(t, t, acc[u]);
                 }
-                acc = lane_group_sum<LPR>(acc);
-                const float w = (r0 + u * RP + rsub < hi) ? __builtin_amdgcn_exp2f(-acc * s2) : 0.0f;
-                add[u] += w;
-                col += w;
             }
+            const float d2 = group_scatter<LPR, UN>(acc, sub);
+            const float w = mine < hi ? __builtin_amdgcn_exp2f(-d2 * s2) : 0.0f;
+            add += w;
+            const float col = lane_group_sum<LPR>(sub % (LPR / UN) == 0 ? w : 0.0f);
             if (sub == 0) cs[r][rsub] += col;          // slot private to this row group
         }
-        if (sub == 0) {
-#pragma unroll
-            for (int u = 0; u < UN; ++u) {
-                const int i = r0 + u * RP + rsub;
-                if (i < hi) added[i - lo] = add[u];
-            }
-        }
+        if (mine < hi && sub % (LPR / UN) == 0) added[mine - lo] = add;
     }
     __syncthreads();
     // the old keys' refreshed densities, a whole tile at a time: consecutive threads, consecutive keys
@@ -135,7 +159,7 @@ append_sweep(const void *__restrict__ Kv, const float *__restrict__ rho_old, flo
 // The dot products of 64 keys with up to 16 (CT = 2: 32) new rows are MFMA tiles, operands fetched as they lie in memory, and
 // |k - s|^2 = (|k|^2 - k.s) + (|s|^2 - k.s).  That is as exact as differences where the two rows are far apart, and loses what
 // |k|^2 + |s|^2 exceeds the distance by where they are near: a pair nearer than kNear of it is evaluated by direct differences,
-// eight lanes (16 at d = 128) to a pair, out of a list of the wave.  A wave that finds a fifth of its pairs near (rows that lie
+// eight lanes (16 at d = 128) to a pair, out of a list of the wave.  A wave that finds a tenth of its pairs near (rows that lie
 // near each other as measured from the origin) evaluates the rest of its tile directly: from there the list would cost more.
 // Every lane keeps the column sums of its rows, summed over the lanes at the end.
 //
@@ -143,16 +167,17 @@ append_sweep(const void *__restrict__ Kv, const float *__restrict__ rho_old, flo
 // 380; 8 heads of 131072, d = 128, 8 rows 148 -> 78 us, 32 rows 410 -> 84.  New rows out of the clusters of the old, so that a few
 // per cent of the pairs go through the list: 547 -> 480, 987 -> 560, 147 -> 107.  All pairs near (keys at an offset of 20 per
 // coordinate), so in the direct loop: 541 -> 443, 943 -> 775, 146 -> 117; with four keys in flight and an exponential in every lane
-// of a group it took 619, 1065 and 160.  Fewer rows than the line stay with append_sweep (6 rows, d = 64, near pairs: 425
-// against 475; 3 rows, d = 128: 92 against 97).
+// of a group it took 619, 1065 and 160.  Fewer rows than the line stay with append_sweep (far / near /
+// all near; 6 rows, d = 64: 355 / 350 / 340 against 376 / 460 / 380; 3 rows, d = 128: 88 / 88 / 88 against 77 / 90 / 77, 4 rows 99
+// against 78 / 95 / 86, taken).
 // Mean error of the new rows' densities over 36 refreshes: 0.73 of append_sweep's with its sums in fp32 to the end.
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 typedef __attribute__((ext_vector_type(2))) unsigned u32x2_t;
 
 constexpr float kNear = 0.25f;
-constexpr int kPairs = 96;          // pairs in a wave's list: kMany of 16 new rows
-constexpr int kMany = 6;            // near pairs per new row, of 32, from which a wave goes on directly
+constexpr int kPairs = 96;          // pairs in a wave's list
+constexpr int kMany = 3;            // near pairs per new row, of 32, from which a wave goes on directly
 
 // over the four lanes 16 apart, in all of them
 __device__ __forceinline__ float quad_sum(float v)
@@ -161,29 +186,6 @@ __device__ __forceinline__ float quad_sum(float v)
     v = __uint_as_float(a.x) + __uint_as_float(a.y);
     const u32x2_t b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     return __uint_as_float(b.x) + __uint_as_float(b.y);
-}
-
-// Eight values of each lane summed over the LPR lanes of its group: the sum of value u ends up in lane u (LPR = 8), in lanes 2 u and
-// 2 u + 1 (LPR = 16).  Half the values change hands at every step, so one lane is left with one exponential to form instead of eight.
-template <int CTRL>
-__device__ __forceinline__ float pass_on(bool upper, float low, float high)
-{
-    const float keep = upper ? high : low, give = upper ? low : high;
-    return keep + __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(give), CTRL, 0xF, 0xF, false));
-}
-
-template <int LPR>
-__device__ __forceinline__ float group_scatter(const float (&v)[8], int part)
-{
-    static_assert(LPR == 8 || LPR == 16, "");
-    constexpr int BIT = LPR / 2;        // of the lane: which half of the values it keeps first
-    float f[4], t[2];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) f[i] = pass_on<LPR == 16 ? 0x140 : 0x141>((part & BIT) != 0, v[i], v[i + 4]);
-#pragma unroll
-    for (int i = 0; i < 2; ++i) t[i] = pass_on<LPR == 16 ? 0x141 : 0x4E>((part & BIT / 2) != 0, f[i], f[i + 2]);
-    if constexpr (LPR == 8) return pass_on<0xB1>((part & 1) != 0, t[0], t[1]);
-    else return dpp_add_f32<0xB1>(pass_on<0x4E>((part & 2) != 0, t[0], t[1]));
 }
 
 template <int D, int CT>
@@ -310,7 +312,7 @@ append_gram(const uint16_t *__restrict__ K, const float *__restrict__ rho_old, f
                 far = false;
                 break;
             }
-            for (int first = 0; first < cnt; first += kPairs) {     // the list, as often as it takes (once for 16 rows)
+            for (int first = 0; first < cnt; first += kPairs) {     // the list, as often as it takes (once for 16 rows: kMany * 16 pairs)
                 int at = -first;
 #pragma unroll
                 for (int j = 0; j < KT; ++j)
@@ -390,7 +392,7 @@ append_gram(const uint16_t *__restrict__ K, const float *__restrict__ rho_old, f
             const u32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(Kh + (size_t)min(key(u), hi - 1) * D + part * 8));
             widen16<true>(make_uint4(v.x, v.y, v.z, v.w), x[u]);
         }
-        const int mine = key(LPR == 8 ? part : part >> 1);
+        const int mine = key(part / (LPR / UN));
         float add = 0.0f;
         for (int r = 0; r < m; ++r) {
             float y[8], w[UN];
@@ -405,15 +407,15 @@ append_gram(const uint16_t *__restrict__ K, const float *__restrict__ rho_old, f
                     w[u] = fmaf(df, df, w[u]);
                 }
             }
-            float one = group_scatter<LPR>(w, part);
+            float one = group_scatter<LPR, UN>(w, part);
             one = mine < hi ? __builtin_amdgcn_exp2f(-one * s2) : 0.0f;
             add += one;
             if (tail && mine - Lold == r) one = 0.0f;
-            if constexpr (LPR == 16) one = part & 1 ? 0.0f : one;
+            if (part % (LPR / UN) != 0) one = 0.0f;         // each key once
             one = lane_group_sum<LPR>(one);
             if (part == 0) cd[r][wave * GRP + grp] += one;      // slot private to this row group
         }
-        if (mine < hi && (LPR == 8 || !(part & 1))) added[mine - lo] = add;
+        if (mine < hi && part % (LPR / UN) == 0) added[mine - lo] = add;
     }
     // column sums: the 16 keys of a tile share a row of lanes
 #pragma unroll

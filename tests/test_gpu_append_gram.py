@@ -27,7 +27,7 @@ def cloud(kind, H, L, m, d, seed):
     return syn.round_to_bf16(K.astype(np.float32))
 
 
-@pytest.mark.parametrize("d,m", [(64, 7), (64, 8), (64, 15), (64, 16), (64, 17), (64, 32), (128, 4), (128, 5), (128, 16), (128, 31)])
+@pytest.mark.parametrize("d,m", [(64, 7), (64, 8), (64, 15), (64, 16), (64, 17), (64, 32), (128, 3), (128, 4), (128, 5), (128, 16), (128, 31)])
 @pytest.mark.parametrize("kind", ["far", "near", "offset", "copies"])
 @pytest.mark.parametrize("L", [37, 50, 64, 2047, 2049, 2100])
 def test_refresh_with_many_new_rows(d, m, kind, L):
@@ -39,6 +39,20 @@ def test_refresh_with_many_new_rows(d, m, kind, L):
     old = np.stack([oracle.density(K[h, :L - m], sigma[h]) for h in range(H)]).astype(np.float32)
     got = ws.ws_synapse_density_append(to_device(K, "bf16"), m, sigma, to_device(old, "f32")).cpu().numpy()
     for h in range(H):
+        assert np.abs(got[h] / oracle.density(K[h], sigma[h]) - 1).max() <= TOL
+
+
+@pytest.mark.parametrize("d,m", [(64, 1), (64, 3), (64, 32), (128, 1), (128, 7), (128, 32)])
+@pytest.mark.parametrize("L", [37, 63, 64, 2049, 2100])
+def test_refresh_of_fp32_keys(d, m, L):
+    """The sums of a lane group dealt out to its lanes: groups of 16 and 32 lanes, turns and tiles that end anywhere."""
+    from oracle import ws_oracle as oracle
+    from paper_2601_01298_amd import binding as ws
+    K = cloud("near", 2, L, m, d, L + 7 * m + d)
+    sigma = [float(syn.bandwidth(K[h])) for h in range(2)]
+    old = np.stack([oracle.density(K[h, :L - m], sigma[h]) for h in range(2)]).astype(np.float32)
+    got = ws.ws_synapse_density_append(to_device(K, "f32"), m, sigma, to_device(old, "f32")).cpu().numpy()
+    for h in range(2):
         assert np.abs(got[h] / oracle.density(K[h], sigma[h]) - 1).max() <= TOL
 
 
