@@ -276,7 +276,8 @@ def main() -> int:
         nbytes = float(w.H) * w.L * w.d * esize + 4.0 * w.H * w.L
         next_steps["attention_mass"] = {"ms": ms, "bound": "hbm", "achieved": nbytes / (ms * 1e-3) / 1e9,
                                         "peak": PEAK_HBM_GBS, "unit": "GB/s",
-                                        "kernel": "mass_logits" if bf16 and w.Hq // w.H > 2 else "mass_logits_rows",
+                                        "kernel": "mass_logits" if bf16 and (w.Hq // w.H > 2 or w.H * -(-w.L // 1024) < 512)
+                                        else "mass_logits_rows",
                                         "shape": f"G={G} Hkv={w.H // G} Hq={w.Hq // G} L={w.L} d={w.d}"}
         del ws_mass, rho_m
         ws_app = torch.empty(ws.ws_synapse_workspace_bytes(ws.WS_OP_DENSITY_APPEND, dt, w.H, w.L, w.d),

@@ -278,7 +278,8 @@ ws_status ws_synapse_attention_mass(const void *K, const void *Q, ws_dtype dt, i
  * same sigma).  L*rho is a plain sum of kernel values, so
  *     rho_new[j] = ((L-m) * rho_old[j] + sum_{r<m} w(j, L-m+r)) / L            j < L-m
  *     rho_new[L-m+r] = (sum_{j<L} w(j, L-m+r)) / L                             r < m
- * with w(i,j) = exp(-||K_i-K_j||^2 / (2 sigma^2)); distances by direct differences in fp32.
+ * with w(i,j) = exp(-||K_i-K_j||^2 / (2 sigma^2)); distances by direct differences in fp32, or (bf16 keys, many new rows) by dot
+ * products where that is as exact: where the distance is not small against the norms.
  * Cost O(L m d) per head.  Each refresh adds fp32 rounding to the old entries; a full
  * ws_synapse_density at every re-selection sheds it.
  *   K dev [H,L,d];  1 <= m <= 32, m < L;  sigma_host host [H];  rho_old dev [H,L-m];  rho_new dev [H,L]
