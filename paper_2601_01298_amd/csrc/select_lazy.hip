@@ -223,7 +223,7 @@ template <int D, int NW, int SLOTS>
 struct LazyShared {
     int4 meta[NW * 64 * SLOTS];     // per group: D bound, score bound, D_max it was scored with, landmarks it has seen
     uint4 cand[NW][D / 8];          // row of each wave's candidate, as the screen sees it
-    Post post[NW];
+    Post post[2][NW];               // by turns: a round that compares bounds only has no barrier before it posts
     unsigned queue[kQueue];         // groups to visit, and the landmarks they have seen
     int qn[2], qh[2];               // entries, entries taken
     int red[NW], red2[NW];
@@ -612,6 +612,7 @@ select_lazy(LazyArgs a)
         float guess = 0.0f, change = 0.02f, lastS = 0.0f;
         int par = 0, pickd = kGone, picks = kGone;      // par: which of the two queue counters; the rest: of the last pick's group
         int gI = 0, gfix = -1;                          // the pick; its group, until the record has been corrected
+        int side = 0;                                   // which of the two sets of posts this round's go to
 
         for (int t = 1; t < k; ++t) {
             // t landmarks so far
@@ -689,7 +690,8 @@ select_lazy(LazyArgs a)
                     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");    // other waves may visit these groups next
                     lds_barrier();
                 }
-                // ---- tell the other waves
+                // ---- tell the other waves (a wave may still read the last round's posts; it is past those of the round before,
+                // or it had not come to the last round's barrier)
                 int D1, N1;
                 {
                     int d1 = kGone, d2 = kGone, g1 = 0, f1 = 0, n1 = kGone, gn = 0x7fff;
@@ -718,12 +720,13 @@ select_lazy(LazyArgs a)
                     int gl = 0x7fff;
                     if (N1 > kGone) gl = ~wave_imax(n1 == N1 ? ~gn : (int)0x80000000);
                     if (lane == 0) {
-                        sh.post[wave].a = make_int4(D1, D2nd, N1, pk | gl << 16);
-                        sh.post[wave].b = make_int4(cs, ci, cd, cs2);
+                        sh.post[side][wave].a = make_int4(D1, D2nd, N1, pk | gl << 16);
+                        sh.post[side][wave].b = make_int4(cs, ci, cd, cs2);
                     }
                 }
                 lds_barrier();
-                const int4 pa = sh.post[lane % NW].a, pb = sh.post[lane % NW].b;
+                const int4 pa = sh.post[side][lane % NW].a, pb = sh.post[side][lane % NW].b;
+                side ^= 1;
                 const int gD = flat ? __float_as_int(dm) : __builtin_amdgcn_readfirstlane(row_imax(pa.x));
                 const int gF = flat ? gD : __builtin_amdgcn_readfirstlane(row_imax((pa.w & 1) ? pa.x : kGone));
                 const int gN = __builtin_amdgcn_readfirstlane(row_imax(pa.z));

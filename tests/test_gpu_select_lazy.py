@@ -15,6 +15,11 @@ def clouds(L, d, seed, kind):
         K = torch.full((2, L, d), 2.0, device="cuda")
         K[:, :, :8] = torch.randint(0, 4, (2, L, 8), generator=gen, device="cuda").float()
         return K, 2.0 ** -torch.randint(1, 5, (2, L), generator=gen, device="cuda").float()
+    if kind == "tails":         # a few coordinates with heavy tails: the far point is picked, and D_max falls, at nearly every step
+        K = torch.zeros((2, L, d), device="cuda")
+        e = torch.randint(0, 8, (2, L, 8), generator=gen, device="cuda") * torch.randint(0, 2, (2, L, 8), generator=gen, device="cuda")
+        K[:, :, :8] = 2.0 ** e * torch.randint(-1, 2, (2, L, 8), generator=gen, device="cuda")
+        return K, 2.0 ** -torch.randint(1, 5, (2, L), generator=gen, device="cuda").float()
     K = 2.0 * torch.randn((2, 16, d), generator=gen, device="cuda")
     K = torch.gather(K, 1, torch.randint(0, 16, (2, L, 1), generator=gen, device="cuda").expand(-1, -1, d))
     K += 0.5 * torch.randn((2, L, d), generator=gen, device="cuda")
@@ -49,6 +54,23 @@ def test_lattice_picks_are_the_streaming_kernels(dtype, d, H, L, k, alpha):
     idx, score = ws.ws_synapse_select(K, rho, k, alpha, want_score=True)
     ref, ref_score = ws.ws_synapse_select(K[:2].contiguous(), rho[:2].contiguous(), k, alpha, want_score=True, kernel="stream")
     assert torch.equal(idx, ref[copies]) and torch.equal(score, ref_score[copies])
+
+
+@pytest.mark.parametrize("dtype,d,H,L,k", [("bf16", 64, 384, 32768, 500), ("bf16", 64, 100, 65537, 1000), ("bf16", 128, 200, 16449, 600),
+                                           ("f32", 64, 250, 4160, 90)])
+@pytest.mark.parametrize("alpha", [0.75, 1.0])
+def test_d_max_that_falls_at_nearly_every_step(dtype, d, H, L, k, alpha):
+    """Each fall makes a round that compares bounds only, which posts again with no barrier in between: what a slow wave still reads
+    of the round before must not be overwritten.  One and two workgroups per compute unit; every head's copy the same."""
+    import torch
+    from paper_2601_01298_amd import binding as ws
+    assert ws.ws_synapse_select_is_lazy(ws.WS_BF16 if dtype == "bf16" else ws.WS_F32, H, L, d, k)
+    K2, rho2 = clouds(L, d, 7 * L + d, "tails")
+    K, rho, copies = heads(K2, rho2, H, dtype)
+    ref, ref_score = ws.ws_synapse_select(K[:2].contiguous(), rho[:2].contiguous(), k, alpha, want_score=True, kernel="stream")
+    for _ in range(3):
+        idx, score = ws.ws_synapse_select(K, rho, k, alpha, want_score=True)
+        assert torch.equal(idx, ref[copies]) and torch.equal(score, ref_score[copies])
 
 
 @pytest.mark.parametrize("dtype,d,H,L,k", [("bf16", 64, 384, 32768, 400), ("bf16", 128, 160, 16390, 400), ("f32", 64, 220, 4100, 90)])
