@@ -448,7 +448,10 @@ hipError_t launch_select(const SelectChoice &c, const void *K, bool bf16, int H,
         return launch_select_small(K, bf16, H, L, d, rho, k, alpha, idx, score_out, reinterpret_cast<int *>(ws), st);
     if (c.lazy_scratch > 0) {
         const LazyShape s = lazy_instead(c, bf16, H, L, d, k, c.lazy_scratch);
-        if (s.groups > 0) return launch_select_lazy(s, K, bf16, H, L, d, rho, k, alpha, idx, score_out, ws, st);
+        if (s.groups > 0) {
+            hipLaunchKernelGGL(select_clear, dim3(1), dim3(64), 0, st, nullptr, 0, reinterpret_cast<int *>(ws));
+            return launch_select_lazy(s, K, bf16, H, L, d, rho, k, alpha, idx, score_out, ws, st);
+        }
     }
     if (c.resident) return launch_select_resident(K, H, L, d, rho, k, alpha, idx, score_out, ws, c.res, st);
 

@@ -30,6 +30,23 @@ def clouds(L, d, seed, kind):
     return K, rho
 
 
+def late_clouds(L, d, seed, lone, far):
+    """Clusters, `lone` isolated keys of the lowest density, which are picked first, and `far` keys of a tight dense cluster that sets
+    D_max until the others are used up (0: D_max falls when the isolated keys are).  Integers with distances below 2^24, powers of two."""
+    import torch
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    ints = lambda lo, hi, *shape: torch.randint(lo, hi, shape, generator=gen, device="cuda").float()
+    K = torch.gather(ints(-30, 31, 2, 64, d), 1, torch.randint(0, 64, (2, L, 1), generator=gen, device="cuda").expand(-1, -1, d))
+    K += ints(-6, 7, 2, L, d)
+    rho = torch.full((2, L), 2.0 ** -6, device="cuda")
+    order = torch.rand((2, L), generator=gen, device="cuda").argsort(1)
+    for keys, rows, r in ((order[:, :lone], ints(-60, 61, 2, lone, d), 2.0 ** -10),
+                          (order[:, lone:lone + far], 150.0 + ints(-4, 5, 2, far, d), 2.0 ** -3)):
+        K.scatter_(1, keys[:, :, None].expand(-1, -1, d), rows)
+        rho.scatter_(1, keys, r)
+    return K, rho
+
+
 def heads(K, rho, H, dtype):
     import torch
     K = K.to(torch.bfloat16 if dtype == "bf16" else torch.float32)
@@ -93,6 +110,24 @@ def test_picks_against_the_oracle(dtype, d, H, L, k):
             assert forks >= 0 and deficit.max() <= 1e-5         # the near-tie rule of the parity tests
         same = np.cumprod(got == ref).astype(bool)
         assert np.allclose(score[h].cpu().numpy()[same], ref_score[same], rtol=2e-5, atol=0)
+
+
+@pytest.mark.parametrize("dtype,d,H,L,k,lone,far,alpha", [
+    ("bf16", 64, 96, 131072, 2000, 1300, 1310, 0.5), ("bf16", 64, 96, 131072, 2621, 800, 1, 0.25), ("bf16", 64, 96, 131072, 1600, 1300, 0, 1.0),
+    ("bf16", 64, 96, 131072, 4096, 3900, 1310, 0.5), ("bf16", 64, 128, 65536, 3600, 2500, 655, 0.5), ("bf16", 64, 384, 32768, 4000, 2500, 327, 0.25),
+    ("bf16", 128, 96, 131072, 2621, 1300, 1310, 0.5), ("f32", 64, 64, 16384, 1500, 900, 163, 0.5)])
+def test_d_max_that_falls_late(dtype, d, H, L, k, lone, far, alpha):
+    """When the key that sets D_max is picked after hundreds or thousands of others, all groups wait for many visits' worth of
+    landmarks, and most of them have to be looked at in that one step."""
+    import torch
+    from paper_2601_01298_amd import binding as ws
+    assert ws.ws_synapse_select_is_lazy(ws.WS_BF16 if dtype == "bf16" else ws.WS_F32, H, L, d, k)
+    K2, rho2 = late_clouds(L, d, L + k, lone, far)
+    K, rho, copies = heads(K2, rho2, H, dtype)
+    idx, score = ws.ws_synapse_select(K, rho, k, alpha, want_score=True)
+    ref, ref_score = ws.ws_synapse_select(K[:2].contiguous(), rho[:2].contiguous(), k, alpha, want_score=True, kernel="stream")
+    assert torch.equal(idx, ref[copies]) and torch.equal(score, ref_score[copies])
+    assert all(row.unique().numel() == k for row in idx[:2])
 
 
 def test_every_key_at_an_offset_and_at_a_tiny_scale():
