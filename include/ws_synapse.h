@@ -120,7 +120,7 @@ int ws_synapse_density_is_symmetric(ws_dtype dt, int L, int d);
  *
  * Four kernels implement this call.  Where the heads are many and long, one that looks again only at the keys a
  * step can depend on runs one workgroup per head (ws_synapse_select_is_lazy says where; at most 131072 keys and
- * 4096 landmarks per head).  Of the others one keeps a head's keys resident in registers and LDS for all
+ * 4096 landmarks per head; a head with a key whose squared norm is 1e37 or more is left to the streaming kernel, behind it).  Of the others one keeps a head's keys resident in registers and LDS for all
  * k steps, spread over the workgroups that share the head (bf16 keys, heads that fit on chip), one
  * streams them from memory every step (any size), and one holds a short head in the registers of a
  * single workgroup (L <= 1024 at d = 64, L <= 512 at d = 128; fp32 keys, and bf16 keys of no more heads

@@ -39,6 +39,7 @@ struct SelArgs {
     int *fail;                       // set to 1 if a bounded wait expired
     int H, L, k, Lslab;
     int groups, members, slice;      // slice = keys per member (multiple of 64)
+    int left;                        // 1: only the heads whose first index is kSelectLeft
     float alpha;
 };
 
@@ -167,6 +168,8 @@ select_stream(SelArgs a)
     unsigned seq = 0;
 
     for (int h = group; h < a.H; h += a.groups) {
+        // (the mark is overwritten after the first exchange, to which every member comes past this line)
+        if (a.left && a.idx[(size_t)h * a.k] != kSelectLeft) continue;
         const T *Kh = reinterpret_cast<const T *>(a.K) + (size_t)h * a.L * D;
         const float *rhoh = a.rho + (size_t)h * a.L;
         int t = 0;
@@ -272,6 +275,11 @@ select_stream(SelArgs a)
         // a wait expired: mark what this group still owes as invalid and leave
         if (member == 0) {
             for (int hh = h; hh < a.H; hh += a.groups) {
+                if (a.left && hh != h) {
+                    const bool owed = a.idx[(size_t)hh * a.k] == kSelectLeft;
+                    __syncthreads();
+                    if (!owed) continue;
+                }
                 const int t0 = (hh == h) ? t : 0;
                 for (int tt = t0 + (int)threadIdx.x; tt < a.k; tt += TPB) a.idx[(size_t)hh * a.k + tt] = -1;
             }
@@ -284,7 +292,7 @@ __global__ void select_clear(unsigned long long *slots, int n, int *fail)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) slots[i] = 0ull;
-    if (i == 0) *fail = 0;
+    if (i == 0 && fail) *fail = 0;
 }
 
 struct WsLayout {
@@ -446,16 +454,12 @@ hipError_t launch_select(const SelectChoice &c, const void *K, bool bf16, int H,
 {
     if (c.small_rows > 0)
         return launch_select_small(K, bf16, H, L, d, rho, k, alpha, idx, score_out, reinterpret_cast<int *>(ws), st);
-    if (c.lazy_scratch > 0) {
-        const LazyShape s = lazy_instead(c, bf16, H, L, d, k, c.lazy_scratch);
-        if (s.groups > 0) {
-            hipLaunchKernelGGL(select_clear, dim3(1), dim3(64), 0, st, nullptr, 0, reinterpret_cast<int *>(ws));
-            return launch_select_lazy(s, K, bf16, H, L, d, rho, k, alpha, idx, score_out, ws, st);
-        }
-    }
-    if (c.resident) return launch_select_resident(K, H, L, d, rho, k, alpha, idx, score_out, ws, c.res, st);
+    LazyShape lazy{0, 0, 0};
+    if (c.lazy_scratch > 0) lazy = lazy_instead(c, bf16, H, L, d, k, c.lazy_scratch);
+    if (c.resident && lazy.groups == 0) return launch_select_resident(K, H, L, d, rho, k, alpha, idx, score_out, ws, c.res, st);
 
-    const SelectPlan &p = c.stream;
+    // (a workspace that holds the lazy kernel's slabs holds the streaming kernel's: fewer heads, two floats per key instead of three)
+    const SelectPlan p = c.stream.groups > 0 ? c.stream : select_plan(H, L, current_chip(), 0);
     const WsLayout w = layout(p, L);
     char *base = reinterpret_cast<char *>(ws);
     SelArgs a;
@@ -475,8 +479,16 @@ hipError_t launch_select(const SelectChoice &c, const void *K, bool bf16, int H,
     a.members = p.members;
     a.slice = (int)round_up((size_t)(L + p.members - 1) / p.members, 64);
     a.alpha = alpha;
+    a.left = 0;
     const int nslots = p.groups * 2 * kMaxMembers;
-    hipLaunchKernelGGL(select_clear, dim3((nslots + 255) / 256), dim3(256), 0, st, a.slots, nslots, a.fail);
+    hipLaunchKernelGGL(select_clear, dim3(lazy.groups > 0 ? 1 : (nslots + 255) / 256), dim3(256), 0, st, a.slots, lazy.groups > 0 ? 0 : nslots, a.fail);
+    if (lazy.groups > 0) {
+        const hipError_t e = launch_select_lazy(lazy, K, bf16, H, L, d, rho, k, alpha, idx, score_out, ws, st);
+        if (e != hipSuccess) return e;
+        // behind it the heads it has left; its slabs lay on the slots
+        hipLaunchKernelGGL(select_clear, dim3((nslots + 255) / 256), dim3(256), 0, st, a.slots, nslots, nullptr);
+        a.left = 1;
+    }
     if (bf16) {
         if (d == 64) return run_select<uint16_t, 64>(a, p, st);
         if (d == 128) return run_select<uint16_t, 128>(a, p, st);

@@ -12,7 +12,8 @@
 // the records meet in LDS.  A step takes one round where D_max holds, three and more where it falls.
 //
 // A visit: the group's rows come in MFMA operand layout, the landmarks since its last visit are screened against its 64 keys on
-// the matrix cores, 16 at a time (|k|^2 + |s|^2 - 2 k.s with a bound on its error), and per key the nearest of those that may
+// the matrix cores, 16 at a time (|k|^2 + |s|^2 - 2 k.s with a bound on its error; heads whose norms are out of its range are marked
+// and left to the streaming kernel, launched behind this one), and per key the nearest of those that may
 // lower its D is evaluated by direct differences in fp32 (others only where the screen cannot tell them apart).  fp32 keys are
 // rounded to bf16 for the screen (the error bound is wider), never for the evaluation.
 //
@@ -42,6 +43,7 @@ constexpr int kVisit = 16;              // tiles of landmarks a visit looks at a
 // clustered clouds the same within 2 %.
 constexpr int kPatience = 1;
 constexpr float kNever = -3.0e38f;
+constexpr float kHuge = 1.0e37f;        // squared norms the screen can do with: products, sums and distances stay in range
 constexpr float kTiny = 1.0e-30f;       // the screen's products may lose what lies below 1e-38: rows that small are always evaluated
 
 struct LazyArgs {
@@ -332,6 +334,7 @@ select_lazy(LazyArgs a)
 #pragma unroll
         for (int r = 0; r < SLOTS; ++r) mine[r * 64 + lane] = make_int4(kGone, kGone, 0x7f800000, 0x7fffffff);
         int dall = kGone;
+        bool big = false;
         {
             Eight<T> m0[KS];
 #pragma unroll
@@ -357,6 +360,7 @@ select_lazy(LazyArgs a)
                         }
                         dd = quad_sum(dd);
                         nn = quad_sum(nn);
+                        big = big || !(nn < kHuge);
                         Dl = q == j ? dd : Dl;
                         Nl = q == j ? nn * kHalf - kTiny : Nl;
                     }
@@ -379,12 +383,23 @@ select_lazy(LazyArgs a)
         if (tid < 2) sh.qn[tid] = sh.qh[tid] = 0;
         float dm;
         {
-            if (lane == 0) sh.red[wave] = dall;
+            const int any = __ballot(big) != 0ull;
+            if (lane == 0) {
+                sh.red[wave] = dall;
+                sh.red2[wave] = any;
+            }
             __syncthreads();
-            int mm = sh.red[0];
+            int mm = sh.red[0], out = sh.red2[0];
 #pragma unroll
-            for (int w = 1; w < NW; ++w) mm = max(mm, sh.red[w]);
+            for (int w = 1; w < NW; ++w) {
+                mm = max(mm, sh.red[w]);
+                out |= sh.red2[w];
+            }
             dm = __int_as_float(__builtin_amdgcn_readfirstlane(mm));
+            if (__builtin_amdgcn_readfirstlane(out) != 0) {     // (or no number at all): left to the kernel behind this one
+                if (tid == 0) a.idx[(size_t)h * k] = kSelectLeft;
+                continue;
+            }
         }
 
         // the group whose keys this wave holds

@@ -110,6 +110,7 @@ struct LazyShape {
     int per_cu;   // workgroups per compute unit
     int groups;   // heads in flight; 0 = not this kernel
 };
+constexpr int kSelectLeft = -2;             // in place of a head's first pick: its keys are out of range for this kernel
 static inline size_t lazy_slab_bytes(int L) { return 3 * round_up((size_t)L, kLazyGroup) * sizeof(float); }
 static inline size_t lazy_select_workspace_bytes(int H, int L)
 {

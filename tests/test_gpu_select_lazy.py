@@ -144,6 +144,35 @@ def test_every_key_at_an_offset_and_at_a_tiny_scale():
         assert torch.equal(idx, ref[copies])
 
 
+@pytest.mark.parametrize("dtype,d,H,L,k,alpha", [("f32", 64, 220, 4096, 90, 0.5), ("f32", 128, 80, 16384, 500, 1.0),
+                                                 ("bf16", 64, 384, 32768, 400, 0.5), ("bf16", 128, 200, 16449, 600, 0.5)])
+@pytest.mark.parametrize("first", [1.0, 1.5 * 2.0 ** 60])
+def test_norms_beyond_the_range_of_fp32(dtype, d, H, L, k, alpha, first):
+    """The squared norms overflow where the distances do not, in every other head or in all: the screen, which is made of norms, must
+    not be relied on."""
+    import torch
+    from paper_2601_01298_amd import binding as ws
+    assert ws.ws_synapse_select_is_lazy(ws.WS_BF16 if dtype == "bf16" else ws.WS_F32, H, L, d, k)
+    K2, rho2 = clouds(L, d, 13, "lattice")
+    K, rho, copies = heads(K2 * torch.tensor([first, 1.5 * 2.0 ** 60], device="cuda")[:, None, None], rho2, H, dtype)
+    idx, score = ws.ws_synapse_select(K, rho, k, alpha, want_score=True)
+    ref, ref_score = ws.ws_synapse_select(K[:2].contiguous(), rho[:2].contiguous(), k, alpha, want_score=True, kernel="stream")
+    assert torch.equal(idx, ref[copies]) and torch.equal(score, ref_score[copies])
+
+
+@pytest.mark.parametrize("dtype,H,L,k", [("f32", 220, 4096, 90), ("bf16", 384, 32768, 400)])
+def test_distances_beyond_the_range_of_fp32_end(dtype, H, L, k):
+    """Two clouds whose distance overflows: D_max is infinite until both hold a landmark.  Every step ends, with keys that are there
+    and none twice."""
+    import torch
+    from paper_2601_01298_amd import binding as ws
+    K2, rho2 = clouds(L, 64, 17, "lattice")
+    K2[:, ::3] -= 12.0
+    K, rho, _ = heads(K2 * 2.0 ** 62, rho2, H, dtype)
+    idx = ws.ws_synapse_select(K, rho, k, 0.5)
+    assert int(idx.min()) >= 0 and int(idx.max()) < L and all(row.unique().numel() == k for row in idx[:2])
+
+
 def test_the_earlier_workspace_is_still_accepted():
     """A caller may have kept the size reported before this kernel needed a slab for every head in flight: 32 heads' slabs."""
     import torch
