@@ -238,6 +238,11 @@ template <typename T, int D, int NW, int SLOTS, int OCC>
 __global__ void __launch_bounds__(NW * 64, OCC)
 select_lazy(LazyArgs a)
 {
+    // Groups a wave asks for in the first round of a step, the foremost of those that reach what is expected of it: where scores tie or
+    // fall unevenly that may be all of them, and one round tells which matter.  384 heads of 32768 keys, d = 64, with 2, 4, 8, 256:
+    // clustered 16.6, 16.2, 16.1, 16.6 ms, heavy tails 15.5, 15.1, 15.1, 15.1 and at alpha = 0 14.9, 13.2, 19.7, 53.0, 200 points in 164
+    // copies each 80.9, 76.9, 87.7, 152; four records per lane (96 heads of 131072) 40.3, 37.0, 34.8, 33.8.
+    constexpr int kFirst = SLOTS == 1 ? 4 : 8;
     constexpr int PJ = OCC == 4 ? 1 : 2;            // key tiles evaluated side by side, where the registers allow
     constexpr int KS = D / 32;                      // MFMA k-steps, and 16-byte pieces of the screen per lane and key
     constexpr int NP = D / 8;                       // pieces per row
@@ -253,7 +258,7 @@ select_lazy(LazyArgs a)
     const int c = lane & 15, q = lane >> 4;         // key (or landmark) of a tile of 16, and which pieces of its row
     const int L = a.L, k = a.k, nG = (L + kGroup - 1) / kGroup;
     const float alpha = a.alpha, oma = 1.0f - a.alpha;
-    const bool flat = alpha == 0.0f;                // D_max counts for nothing: it stays what it is at first
+    const bool flat = alpha == 0.0f;                // distances count for nothing: D and D_max stay what they are at first
     constexpr float kHalf = 0.5f * (1.0f - Eight<T>::kSlack);
     float *Ds = a.slab + (size_t)blockIdx.x * 3 * a.Lpad, *Ns = Ds + a.Lpad, *Us = Ns + a.Lpad;
 
@@ -644,6 +649,7 @@ select_lazy(LazyArgs a)
                 const float rdm = __builtin_amdgcn_rcpf(dm);
                 if (look) {
                     // ---- what to visit
+                    int room = round == 0 ? kFirst : kQueue;
 #pragma unroll
                     for (int r = 0; r < SLOTS; ++r) {
                         int4 m = mine[r * 64 + lane];
@@ -659,11 +665,13 @@ select_lazy(LazyArgs a)
                                         (wantS && open && (ub > thr || (ub == thr && g < tie)));
                         const unsigned long long bal = __ballot(go);
                         if (bal != 0ull) {
+                            const int rank = (int)__builtin_amdgcn_mbcnt_hi((unsigned)(bal >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
+                            const int cnt = min((int)__popcll(bal), room);
                             int at = 0;
-                            if (lane == 0) at = atomicAdd(&sh.qn[par], (int)__popcll(bal));
-                            at = __builtin_amdgcn_readfirstlane(at) +
-                                 (int)__builtin_amdgcn_mbcnt_hi((unsigned)(bal >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)bal, 0u));
-                            if (go && at < kQueue) sh.queue[at] = (unsigned)g | (unsigned)m.w << 16;
+                            if (lane == 0) at = atomicAdd(&sh.qn[par], cnt);
+                            at = __builtin_amdgcn_readfirstlane(at) + rank;
+                            if (go && rank < room && at < kQueue) sh.queue[at] = (unsigned)g | (unsigned)m.w << 16;
+                            room -= cnt;
                         }
                     }
                     gfix = -1;
@@ -678,8 +686,9 @@ select_lazy(LazyArgs a)
                         int nx = 0;
                         if (lane == 0) nx = atomicAdd(&sh.qh[par], 1);
                         hold(g);
-                        const int t1 = min(t, t0 / kTile * kTile + far);
-                        const bool moved = t0 < t && update(t0, t1, t);
+                        // (alpha = 0: no score depends on D, and D stays as it was at first)
+                        const int t1 = flat ? t : min(t, t0 / kTile * kTile + far);
+                        const bool moved = t0 < t && !flat && update(t0, t1, t);
                         const float D2 = q < 2 ? (q == 0 ? Dt[0] : Dt[1]) : (q == 2 ? Dt[2] : Dt[3]);
                         if (moved) Ds[base + lane] = D2;
                         const float Dl = __fsqrt_rn(D2), cov = dm > 0.0f ? Dl / dm : 0.0f;
