@@ -15,7 +15,7 @@
 // the matrix cores, 16 at a time (|k|^2 + |s|^2 - 2 k.s with a bound on its error; heads whose norms are out of its range are marked
 // and left to the streaming kernel, launched behind this one), and per key the nearest of those that may
 // lower its D is evaluated by direct differences in fp32 (others only where the screen cannot tell them apart).  fp32 keys are
-// rounded to bf16 for the screen (the error bound is wider), never for the evaluation.
+// measured from a mean of theirs and rounded to bf16 for the screen (the error bound is wider), never for the evaluation.
 //
 // What bounds it: the chain of a step (median 9 000 cycles with four groups visited, d = 64; queue, rows, update, score, three
 // barriers), and the first steps and those where D_max falls, in which hundreds of groups contend.  A visit is some 800 vector
@@ -132,6 +132,7 @@ template <> struct Eight<uint16_t> {
     uint4 q;
     __device__ __forceinline__ void load(const uint16_t *p) { q = *reinterpret_cast<const uint4 *>(p); }
     __device__ __forceinline__ uint4 screen() const { return q; }
+    __device__ __forceinline__ void from(const float *, int) {}      // (the screen is as exact as it has to be)
     __device__ __forceinline__ void widen(float (&f)[8]) const
     {
         const uint32_t w[4] = {q.x, q.y, q.z, q.w};
@@ -143,7 +144,8 @@ template <> struct Eight<uint16_t> {
     }
 };
 template <> struct Eight<float> {
-    // both rows rounded to bf16 (2^-8 of an element each): 2 |k||s| (2^-7 + 2^-16) at most, and the sums
+    // both rows, as measured from a point c amid the keys, rounded to bf16 (2^-8 of an element each; a difference to c loses 2^-24 of
+    // itself): 2 |k-c||s-c| (2^-7 + 2^-16) at most, and the sums
     static constexpr float kSlack = 8.0e-3f;
     float4 a, b;
     __device__ __forceinline__ void load(const float *p)
@@ -154,6 +156,15 @@ template <> struct Eight<float> {
     __device__ __forceinline__ uint4 screen() const
     {
         return make_uint4(pack2(a.x, a.y), pack2(a.z, a.w), pack2(b.x, b.y), pack2(b.z, b.w));
+    }
+    __device__ __forceinline__ void from(const float *centre, int at)
+    {
+        // (read where it is used, behind the row: kept or fetched ahead it takes registers there are not)
+        asm volatile("" : "+v"(at), "+v"(b.w));
+        const float *c = centre + at;
+        const float4 u = *reinterpret_cast<const float4 *>(c), v = *reinterpret_cast<const float4 *>(c + 4);
+        a = make_float4(a.x - u.x, a.y - u.y, a.z - u.z, a.w - u.w);
+        b = make_float4(b.x - v.x, b.y - v.y, b.z - v.z, b.w - v.w);
     }
     __device__ __forceinline__ void widen(float (&f)[8]) const
     {
@@ -232,6 +243,8 @@ struct LazyShared {
     unsigned queue[kQueue];         // groups to visit, and the landmarks they have seen
     int qn[2], qh[2];               // entries, entries taken
     int red[NW], red2[NW];
+    float part[NW][64];             // fp32 keys: sums of sampled rows
+    float centre[D];                // and their mean, from which the screen measures
 };
 
 template <typename T, int D, int NW, int SLOTS, int OCC>
@@ -321,10 +334,27 @@ select_lazy(LazyArgs a)
         // ---- landmark 0 into the ring (the rows beside it in its tile take part in the screen, unused), and every key's
         // distance to it
         for (int i = tid; i < a.ring * NP; i += NW * 64) ring[i] = make_uint4(0u, 0u, 0u, 0u);
+        if constexpr (sizeof(T) == 4) {
+            // 64 rows, evenly spaced: a few far ones among them shift the mean by a small part of their distance
+            constexpr int RW = NW * 64 / D;         // rows side by side
+            const int e = tid % D, r0 = tid / D;
+            float sum = 0.0f;
+#pragma unroll
+            for (int r = 0; r < 64; r += RW) sum += (float)Kh[(size_t)((long long)(r + r0) * L >> 6) * D + e];
+            (&sh.part[0][0])[tid] = sum;
+            __syncthreads();
+            if (tid < D) {
+                sum = 0.0f;
+#pragma unroll
+                for (int r = 0; r < RW; ++r) sum += (&sh.part[0][0])[r * D + tid];
+                sh.centre[tid] = sum * (1.0f / 64.0f);
+            }
+        }
         __syncthreads();
         if (wave == 0 && lane < NP) {
             Eight<T> x;
             x.load(Kh + (size_t)pick * D + lane * 8);
+            x.from(sh.centre, lane * 8);
             ring[lane] = x.screen();
             float n = square(x);
             n = lane_group_sum<NP>(n);
@@ -361,6 +391,7 @@ select_lazy(LazyArgs a)
                         for (int s = 0; s < KS; ++s) {
                             if constexpr (sizeof(T) == 2) dd += diff2_held(m0[s].q, x[s]);
                             else dd += diff2(x[s], m0[s]);
+                            x[s].from(sh.centre, (s * 4 + q) * 8);
                             nn += square(x[s]);
                         }
                         dd = quad_sum(dd);
@@ -427,6 +458,7 @@ select_lazy(LazyArgs a)
                 for (int s = 0; s < KS; ++s) {
                     Eight<T> x;
                     x.load(reinterpret_cast<const T *>(reinterpret_cast<const char *>(Kh) + at) + s * 32);
+                    x.from(sh.centre, (s * 4 + q) * 8);
                     kv[j][s] = x.screen();
                 }
                 hk[j] = Ns[base + j * 16 + c];
@@ -446,6 +478,7 @@ select_lazy(LazyArgs a)
                 for (int s = 0; s < KS; ++s) {
                     Eight<T> x;
                     x.load(row + (s * 4 + q) * 8);
+                    x.from(sh.centre, (s * 4 + q) * 8);
                     mv[s] = x.screen();
                 }
             }
@@ -781,7 +814,10 @@ select_lazy(LazyArgs a)
                             ring[row * NP + (lane ^ (row & (NP - 1)))] = w;
                             Eight<T> x;
                             if constexpr (sizeof(T) == 2) x.q = w;
-                            else x.load(Kh + (size_t)gI * D + lane * 8);
+                            else {
+                                x.load(Kh + (size_t)gI * D + lane * 8);
+                                x.from(sh.centre, lane * 8);
+                            }
                             const float n = lane_group_sum<NP>(square(x));
                             if (lane == 0) {
                                 lmC[t] = -n * kHalf;
