@@ -119,8 +119,8 @@ int ws_synapse_density_is_symmetric(ws_dtype dt, int L, int d);
  *   score_out dev [H,k] fp32 winning score per step, or NULL
  *
  * Four kernels implement this call.  Where the heads are many and long, one that looks again only at the keys a
- * step can depend on runs one workgroup per head (ws_synapse_select_is_lazy says where; at most 131072 keys and
- * 4096 landmarks per head; a head with a key whose squared norm is 1e37 or more is left to the streaming kernel, behind it).  Of the others one keeps a head's keys resident in registers and LDS for all
+ * step can depend on runs one workgroup per head (ws_synapse_select_is_lazy says where; 8192 to 131072 keys, fp32 2048 to 16384, and
+ * at most 4096 landmarks per head; a head with a key whose squared norm is 1e37 or more is left to the streaming kernel, behind it).  Of the others one keeps a head's keys resident in registers and LDS for all
  * k steps, spread over the workgroups that share the head (bf16 keys, heads that fit on chip), one
  * streams them from memory every step (any size), and one holds a short head in the registers of a
  * single workgroup (L <= 1024 at d = 64, L <= 512 at d = 128; fp32 keys, and bf16 keys of no more heads
@@ -165,7 +165,7 @@ ws_status ws_synapse_select_with(ws_select_kernel which, const void *K, ws_dtype
 /*
  * ws_synapse_select for callers that cannot allocate and have no workspace to hand over: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels and
- * same results as ws_synapse_select (up to ties where the scratch is too small for the kernel that call would take),
+ * same results as ws_synapse_select (up to ties where that call takes the kernel with a slab per head in flight, which has no room here),
  * but the scratch the kernels need (failure flag, exchange slots, and the streaming kernel's distance /
  * inverse-density slabs) lives in a fixed array inside the library's
  * device image: 256 bytes + 1 MiB + 4 MiB = 5 243 136 bytes per device, held until the process ends.
@@ -325,7 +325,9 @@ int ws_synapse_select_is_resident(ws_dtype dt, int H, int L, int d);
 int ws_synapse_select_is_lazy(ws_dtype dt, int H, int L, int d, int k);
 
 /* Bytes of workspace the given operation needs for these sizes (0 if none).  Arguments an
- * operation does not use are ignored.  Returns (size_t)-1 for unsupported sizes. */
+ * operation does not use are ignored.  Returns (size_t)-1 for unsupported sizes.  For a selection: what the kernel
+ * that ws_synapse_select takes for these sizes and this k on the current device needs, and never less than the other
+ * kernels need on any device; a size asked for with another k (0 for none) is accepted, and the call served by a kernel it is enough for. */
 size_t ws_synapse_workspace_bytes(ws_op op, ws_dtype dt, int H, int L, int d, int k, int N, int Hq);
 
 /* Static, NUL-terminated description of a status code. */

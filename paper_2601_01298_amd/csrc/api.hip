@@ -2,6 +2,7 @@
 // Nothing here allocates, synchronises the host or keeps state between calls.
 #include "../../include/ws_synapse.h"
 
+#include <algorithm>
 #include <cmath>
 
 #include "ws_internal.h"
@@ -39,10 +40,8 @@ size_t ws_synapse_workspace_bytes(ws_op op, ws_dtype dt, int H, int L, int d, in
         return ws::density_workspace_bytes(H, L, d, dt == WS_BF16);
     case WS_OP_SELECT:
         if (H < 1 || L < 1 || L >= kMaxL) return (size_t)-1;
-    {
-        const size_t least = ws::select_workspace_bytes(H, L, d, dt == WS_BF16), lazy = ws::lazy_select_workspace_bytes(H, L);
-        return least > lazy ? least : lazy;
-    }
+        return std::max(ws::select_workspace_bytes(H, L, d, dt == WS_BF16),
+                        ws::lazy_select_workspace_bytes(dt == WS_BF16, H, L, d, k));
     case WS_OP_GATHER:
         return 0;
     case WS_OP_ATTEND:
@@ -151,7 +150,6 @@ ws_status ws_synapse_select_static(const void *K, ws_dtype dt, int H, int L, int
                         : c.resident     ? ws::resident_select_workspace_bytes(c.res.groups)
                                          : ws::stream_select_workspace_bytes(c.stream, L);
     if (need > ws::kStaticScratchBytes) return WS_ERR_TOO_LARGE;
-    c.lazy_scratch = ws::kStaticScratchBytes;
     void *scratch_ptr = nullptr;
     if (ws::select_static_scratch(&scratch_ptr) != hipSuccess) return WS_ERR_HIP;
     const hipError_t e = ws::launch_select(c, K, dt == WS_BF16, H, L, d, rho, k, alpha, idx, score_out, scratch_ptr,

@@ -449,6 +449,14 @@ static LazyShape lazy_instead(const SelectChoice &c, bool bf16, int H, int L, in
     return select_lazy_shape(bf16, H, L, d, k, step * (float)k, current_chip(), scratch_bytes);
 }
 
+size_t lazy_select_workspace_bytes(bool bf16, int H, int L, int d, int k)
+{
+    SelectChoice c;
+    if (k < 1 || k > L || !choose_select(0, bf16, H, L, d, current_chip(), 0, c) || c.small_rows > 0) return 0;
+    const LazyShape s = lazy_instead(c, bf16, H, L, d, k, SIZE_MAX);
+    return s.groups > 0 ? kSelectFlagBytes + (size_t)s.groups * lazy_slab_bytes(L) : 0;
+}
+
 hipError_t launch_select(const SelectChoice &c, const void *K, bool bf16, int H, int L, int d, const float *rho, int k,
                          float alpha, int32_t *idx, float *score_out, void *ws, hipStream_t st)
 {
@@ -504,9 +512,6 @@ hipError_t launch_select(const SelectChoice &c, const void *K, bool bf16, int H,
 // (beside the launcher, as it answers for the choice made there)
 extern "C" int ws_synapse_select_is_lazy(ws_dtype dt, int H, int L, int d, int k)
 {
-    if ((dt != WS_F32 && dt != WS_BF16) || (d != 64 && d != 128) || H < 1 || L < 1 || L >= 1 << 24 || k < 1 || k > L) return 0;
-    const bool bf16 = dt == WS_BF16;
-    ws::SelectChoice c;
-    if (!ws::choose_select(0, bf16, H, L, d, ws::current_chip(), 0, c) || c.small_rows > 0) return 0;
-    return ws::lazy_instead(c, bf16, H, L, d, k, ws::lazy_select_workspace_bytes(H, L)).groups > 0;
+    if ((dt != WS_F32 && dt != WS_BF16) || (d != 64 && d != 128) || H < 1 || L < 1 || L >= 1 << 24) return 0;
+    return ws::lazy_select_workspace_bytes(dt == WS_BF16, H, L, d, k) > 0;
 }

@@ -895,23 +895,28 @@ hipError_t dispatch(const LazyArgs &a, const LazyShape &s, hipStream_t st)
     // two workgroups per compute unit: 128 registers, which is enough at d = 64 with bf16 keys only
     if constexpr (sizeof(T) == 2 && D == 64)
         if (s.per_cu == 2) return run<T, D, kLazyWaves, 1, 4>(a, s.groups, st);
-    if (s.slots == 1) return run<T, D, kLazyWaves, 1, 2>(a, s.groups, st);
-    if (s.slots == 2) return run<T, D, kLazyWaves, 2, 2>(a, s.groups, st);
-    return run<T, D, kLazyWaves, 4, 2>(a, s.groups, st);
+    if constexpr (sizeof(T) == 2) {     // (fp32 heads of these lengths stay with the streaming kernel)
+        if (s.slots == 2) return run<T, D, kLazyWaves, 2, 2>(a, s.groups, st);
+        if (s.slots == 4) return run<T, D, kLazyWaves, 4, 2>(a, s.groups, st);
+    }
+    return run<T, D, kLazyWaves, 1, 2>(a, s.groups, st);
 }
 
 }  // namespace
 
-// When it is taken.  `other_us`: what the kernel that would run otherwise takes.  The estimate is a line in k through the
-// slowest of five kinds of clouds (clusters of equal spread, alpha = 1/2), measured at 16384 to 131072 keys (fp32: 2000 to 16384) and
-// k = L/500 ... 3 L/100: a start of 0.17 us per key (0.24 at d = 128) until the first landmarks are out, then 8 ... 18 (10 ... 25) us
-// a step.  Both sides, us, lazy / resident: d = 64, 256 heads of 32768 keys 5504 / 3569 (k = 66), 7710 / 11660 (328), 10581 / 20961
-// (655); 384 heads 17868 / 31255 (655); 128 heads 9944 / 10420; 16384 keys, 256 heads 5233 / 6036 (328); d = 128, 80 heads of
-// 32768 keys 14163 / 17243 (655), 24 heads of 131072 79980 / 74460 (2621).  On the other clouds it is 0.6 to 1.0 of the estimate.
+// When it is taken.  `other_us`: what the kernel that would run otherwise takes.  The estimate is a line in k: a start of 0.17 us per
+// key (0.24 at d = 128; fp32 0.31, 0.76) until the first landmarks are out, then 8 ... 18 (10 ... 25) us a step.  The lengths are those at which both
+// sides were measured, with k from L/50 to the smaller of L and 4096, alpha = 1/2 and 1, and four clouds (drifting clusters, heavy
+// tails, Gaussian or clusters, clusters at an offset of 20).  Where the rule takes a call it is 0.13 to 0.95 of the other kernel's time
+// (bf16 1.0 to 1.08 on the offset clusters at 40 heads of 131072, d = 128).  Us, lazy / other: bf16, d = 64, k = L/50, 256 heads of
+// 16384 keys 3700-6400 / 6400-9900, 384 of 32768 12600-22600 / 32800-56500, 128 of 65536 18700-45500 / 39800-68700, 64 of 131072
+// 52600-137500 / 112100-159900; d = 128, 200 of 16384 4700-8900 / 12100-15800, 96 of 32768 9400-23300 / 20600-27500.
+// What lies beyond: bf16 heads of 4096 keys and fewer 0.6 to 1.2; at d = 128 above 32768 keys the offset clusters ask for a margin (40 heads of
+// 65536, 4096 picks: 92 against 201); fp32 of 65536 keys 0.5 to 2.0, of 131072 0.7 to 3.6, of 1100 0.2 to 0.9 but never taken.
 LazyShape select_lazy_shape(bool bf16, int H, int L, int d, int k, float other_us, const Chip &chip, size_t scratch_bytes)
 {
     LazyShape s{0, 0, 0};
-    if (k > kMaxLazyK || L > kMaxLazyL || scratch_bytes < kSelectFlagBytes) return s;
+    if (k > kMaxLazyK || L < (bf16 ? 8192 : 2048) || L > (bf16 ? kMaxLazyL : 16384) || scratch_bytes < kSelectFlagBytes) return s;
     const int per = kLazyWaves * 64 * kGroup;       // keys that a record per lane covers
     s.slots = L <= per ? 1 : L <= 2 * per ? 2 : 4;
     s.per_cu = bf16 && d == 64 && s.slots == 1 && H > chip.cus ? 2 : 1;
@@ -924,7 +929,7 @@ LazyShape select_lazy_shape(bool bf16, int H, int L, int d, int k, float other_u
     const float l = (float)L;
     const float start = bf16 ? (d == 64 ? 0.17f : 0.24f) * l : (d == 64 ? 0.31f : 0.76f) * l;
     const float step = bf16 ? (d == 64 ? 6.7f + 8.5e-5f * l : 8.3f + 1.27e-4f * l) : (d == 64 ? 19.0f : 37.0f) + 1.3e-4f * l;
-    if (passes * (start + step * (float)k) < 0.95f * other_us) s.groups = groups;
+    if (passes * (start + step * (float)k) < (bf16 && d == 128 && L > 32768 ? 0.85f : 0.95f) * other_us) s.groups = groups;
     return s;
 }
 

@@ -104,7 +104,7 @@ constexpr int kLazyGroup = 64;              // keys per group
 constexpr int kMaxLazyK = 4096;             // landmarks the kernel lists in LDS
 constexpr int kLazyWaves = 8;               // per workgroup
 constexpr int kMaxLazyL = kLazyGroup * 64 * kLazyWaves * 4;     // four groups per lane
-constexpr int kMaxLazyHeads = 512;          // heads in flight the reported workspace is sized for
+constexpr int kMaxLazyHeads = 512;          // heads in flight
 struct LazyShape {
     int slots;    // groups a lane keeps
     int per_cu;   // workgroups per compute unit
@@ -112,10 +112,8 @@ struct LazyShape {
 };
 constexpr int kSelectLeft = -2;             // in place of a head's first pick: its keys are out of range for this kernel
 static inline size_t lazy_slab_bytes(int L) { return 3 * round_up((size_t)L, kLazyGroup) * sizeof(float); }
-static inline size_t lazy_select_workspace_bytes(int H, int L)
-{
-    return kSelectFlagBytes + (size_t)(H < kMaxLazyHeads ? H : kMaxLazyHeads) * lazy_slab_bytes(L);
-}
+// what a call of these sizes needs for it on the current device; 0 where the call is served by another kernel
+size_t lazy_select_workspace_bytes(bool bf16, int H, int L, int d, int k);
 LazyShape select_lazy_shape(bool bf16, int H, int L, int d, int k, float other_us, const Chip &chip, size_t scratch_bytes);
 hipError_t launch_select_lazy(const LazyShape &shape, const void *K, bool bf16, int H, int L, int d, const float *rho, int k,
                               float alpha, int32_t *idx, float *score_out, void *ws, hipStream_t st);

@@ -16,6 +16,7 @@ hipError_t launch_density(const void *, bool, int, int, int, const float *, floa
 }
 Chip current_chip() { return Chip{256, 2}; }
 size_t select_workspace_bytes(int H, int L, int, bool) { return kSelectFlagBytes + (size_t)H * L * 8; }
+size_t lazy_select_workspace_bytes(bool, int, int, int, int) { return 0; }
 bool choose_select(int which, bool bf16, int, int L, int, const Chip &, size_t, SelectChoice &c)
 {
     c.resident = bf16 && which != 1 && L <= 65536;

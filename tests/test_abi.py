@@ -64,6 +64,25 @@ def test_workspace_query(lib):
         b.ws_synapse_workspace_bytes(b.WS_OP_SELECT, b.WS_BF16, 4, 1 << 24, 64)    # L too large
 
 
+def test_selection_workspace_is_what_the_call_can_use(lib):
+    """12 bytes per key and head in flight only where the kernel that needs them takes the call; elsewhere the slabs of 32 streamed
+    heads or the exchange slots, as before that kernel was there."""
+    from paper_2601_01298_amd import binding as b
+    size = lambda dt, H, L, d, k: b.ws_synapse_workspace_bytes(b.WS_OP_SELECT, dt, H, L, d, k)
+    streamed = lambda H, L: 256 + min(H, 32) * (2 * 64 * 8 + 2 * 4 * ((L + 63) // 64 * 64))
+    for H, L, d, k in ((64, 1 << 20, 64, 2000), (384, 1 << 20, 64, 2000), (384, 4096, 64, 82), (8, 131072, 128, 2621), (384, 32768, 64, 1),
+                       (384, 32768, 64, 0), (384, 32768, 64, 4097), (9, 520, 128, 520), (100, 700, 128, 700)):
+        assert not b.ws_synapse_select_is_lazy(b.WS_BF16, H, L, d, k)
+        assert size(b.WS_BF16, H, L, d, k) == streamed(H, L)
+    for H, L, d, k in ((1, 2048, 64, 2048), (16, 65536, 64, 1310), (64, 1100, 128, 1100)):
+        assert not b.ws_synapse_select_is_lazy(b.WS_F32, H, L, d, k)
+        assert size(b.WS_F32, H, L, d, k) == streamed(H, L)
+    for dt, H, L, d, k, flight in ((b.WS_BF16, 384, 32768, 64, 655, 384), (b.WS_BF16, 600, 32768, 64, 655, 512), (b.WS_BF16, 300, 16384, 128, 491, 256),
+                                   (b.WS_F32, 200, 4096, 64, 82, 200)):
+        assert b.ws_synapse_select_is_lazy(dt, H, L, d, k)
+        assert size(dt, H, L, d, k) == 256 + flight * 12 * L
+
+
 def test_bad_arguments_are_rejected_on_the_host(lib):
     from paper_2601_01298_amd import binding as b
     vp = ctypes.c_void_p
