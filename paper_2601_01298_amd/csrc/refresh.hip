@@ -276,7 +276,7 @@ append_gram(const uint16_t *__restrict__ K, const float *__restrict__ rho_old, f
     int b0 = lo + wave * KB;
     for (; b0 < hi; b0 += 4 * KB) {
         const bool tail = b0 + KB > Lold;           // new rows among the keys: a row's own 1 joins its sum last, in append_finish
-        bool far = true;
+        bool far = true, last = false;
         u32x4_t k4[KT][NK];
 #pragma unroll
         for (int j = 0; j < KT; ++j)
@@ -313,6 +313,8 @@ append_gram(const uint16_t *__restrict__ K, const float *__restrict__ rho_old, f
                 far = false;
                 break;
             }
+            // (the sums already hold the first 16 rows' part of this turn: it is finished, the next ones are not begun)
+            if (ct > 0 && cnt > kMany * min(m - 16, 16)) last = true;
             for (int first = 0; first < cnt; first += kPairs) {     // the list, as often as it takes (once for 16 rows: kMany * 16 pairs)
                 int at = -first;
 #pragma unroll
@@ -380,6 +382,10 @@ append_gram(const uint16_t *__restrict__ K, const float *__restrict__ rho_old, f
         for (int j = 0; j < KT; ++j) {
             const float t = quad_sum(add[j]);
             if (q == 0 && in[j]) added[b0 + j * 16 + c - lo] = t;
+        }
+        if (last) {
+            b0 += 4 * KB;
+            break;
         }
     }
     // direct differences, a lane group per key, eight keys in flight (at d = 64 those of two turns)

@@ -22,6 +22,9 @@ def cloud(kind, H, L, m, d, seed):
         K[:, L - m:] = 2.0 * rng.standard_normal((H, m, d))
     elif kind == "offset":
         K += 30.0
+    elif kind == "split":       # the first 16 new rows far from every key, the rest near to all: each turn fills its list several times
+        K += 30.0
+        K[:, L - m:L - m + 16] -= 60.0
     elif kind == "copies":
         K[:, L - m:] = K[:, :1]
     return syn.round_to_bf16(K.astype(np.float32))
@@ -63,3 +66,35 @@ def test_a_bandwidth_that_underflows_the_scale():
     K = torch.randn((1, 100, 64), device="cuda").to(torch.bfloat16)
     got = ws.ws_synapse_density_append(K, 9, [1.0e19], torch.ones((1, 91), device="cuda"))
     assert torch.equal(got, torch.ones_like(got))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("m", [17, 25, 32])
+@pytest.mark.parametrize("L", [50, 2047, 2100, 6000])
+def test_second_tile_of_new_rows_near(d, m, L):
+    test_refresh_with_many_new_rows(d, m, "split", L)
+
+
+def test_second_tile_of_new_rows_near_is_no_slower_than_direct():
+    """The same at a size that fills the chip, against as many rows all near to every key, which are evaluated directly: 1.2 of its time;
+    2.5 when only the first 16 rows decided whether a wave goes on that way."""
+    import torch
+    from paper_2601_01298_amd import binding as ws
+    H, L, m, d = 96, 32768, 32, 64
+    near = 20.0 + torch.randn((H, L, d), generator=torch.Generator(device="cuda").manual_seed(3), device="cuda")
+    times = []
+    for first in (0.0, 40.0):
+        K = near.clone()
+        K[:, L - m:L - m + 16] -= first
+        K, rho = K.to(torch.bfloat16), torch.full((H, L - m), 0.5, device="cuda")
+        best = float("inf")
+        for _ in range(5):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            ws.ws_synapse_density_append(K, m, [3.0] * H, rho)
+            e1.record()
+            torch.cuda.synchronize()
+            best = min(best, e0.elapsed_time(e1))
+        times.append(best)
+    print(times)
+    assert times[1] < 1.5 * times[0]
