@@ -275,7 +275,8 @@ append_gram(const uint16_t *__restrict__ K, const float *__restrict__ rho_old, f
     const int part = lane % LPR, grp = lane / LPR;
     int b0 = lo + wave * KB;
     for (; b0 < hi; b0 += 4 * KB) {
-        const bool tail = b0 + KB > Lold;           // new rows among the keys: a row's own 1 joins its sum last, in append_finish
+        const bool tail = b0 + KB > Lold;           // new rows among the keys: a row's own 1 joins its sum last, in append_finish (what is
+                                                    // left of it here is 0, or the NaN of a row with an infinity)
         bool far = true, last = false;
         u32x4_t k4[KT][NK];
 #pragma unroll
@@ -370,7 +371,7 @@ append_gram(const uint16_t *__restrict__ K, const float *__restrict__ rho_old, f
                 for (int j = 0; j < KT; ++j)
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        if (b0 + j * 16 + c - Lold == 16 * ct + 4 * q + e) d2[j][e] = 0.0f;
+                        if (in[j] && b0 + j * 16 + c - Lold == 16 * ct + 4 * q + e) d2[j][e] -= 1.0f;
             }
 #pragma unroll
             for (int j = 0; j < KT; ++j)
@@ -417,7 +418,7 @@ append_gram(const uint16_t *__restrict__ K, const float *__restrict__ rho_old, f
             float one = group_scatter<LPR, UN>(w, part);
             one = mine < hi ? __builtin_amdgcn_exp2f(-one * s2) : 0.0f;
             add += one;
-            if (tail && mine - Lold == r) one = 0.0f;
+            if (tail && mine < hi && mine - Lold == r) one -= 1.0f;
             if (part % (LPR / UN) != 0) one = 0.0f;         // each key once
             one = lane_group_sum<LPR>(one);
             if (part == 0) cd[r][wave * GRP + grp] += one;      // slot private to this row group

@@ -98,3 +98,15 @@ def test_second_tile_of_new_rows_near_is_no_slower_than_direct():
         times.append(best)
     print(times)
     assert times[1] < 1.5 * times[0]
+
+
+@pytest.mark.parametrize("m", [2, 8, 20])
+def test_rows_that_are_no_numbers(m):
+    """A new row with an infinity has no density, whichever form the refresh takes (its distance to itself is no number); the keys around
+    it have theirs, as it is infinitely far."""
+    import torch
+    from paper_2601_01298_amd import binding as ws
+    K = cloud("near", 1, 200, m, 64, 5)
+    K[0, 200 - m, 7] = np.inf
+    got = ws.ws_synapse_density_append(to_device(K, "bf16"), m, [3.0], torch.full((1, 200 - m), 0.5, device="cuda")).cpu().numpy()[0]
+    assert np.isnan(got[200 - m]) and np.isfinite(np.delete(got, 200 - m)).all()
