@@ -54,10 +54,12 @@ def heads(K, rho, H, dtype):
     return K[copies], rho[copies].contiguous(), copies
 
 
-# one, two and four records per lane, the last group whole, ragged and a single key; two heads per compute unit (H = 384)
+# one, two and four records per lane, the last group whole, ragged and a single key; two heads per compute unit (H = 384); more heads than
+# are in flight, so that a workgroup takes a second one; every key picked
 SHAPES = [("bf16", 64, 384, 32768, 500), ("bf16", 64, 200, 32767, 900), ("bf16", 64, 200, 32769, 700), ("bf16", 64, 200, 40001, 500),
           ("bf16", 64, 100, 65537, 1000), ("bf16", 64, 96, 131072, 1300), ("bf16", 128, 200, 16449, 600), ("bf16", 128, 100, 65536, 1000),
-          ("f32", 64, 220, 4095, 90), ("f32", 64, 250, 4160, 90), ("f32", 128, 80, 16384, 500)]
+          ("f32", 64, 220, 4095, 90), ("f32", 64, 250, 4160, 90), ("f32", 128, 80, 16384, 500),
+          ("bf16", 128, 300, 16400, 500), ("bf16", 64, 600, 32768, 700), ("f32", 64, 512, 2050, 700), ("bf16", 64, 256, 16384, 4096), ("f32", 64, 256, 2048, 2048)]
 
 
 @pytest.mark.parametrize("dtype,d,H,L,k", SHAPES)
@@ -136,6 +138,7 @@ def test_every_key_at_an_offset_and_at_a_tiny_scale():
     import torch
     from paper_2601_01298_amd import binding as ws
     H, L, d, k = 220, 4096, 64, 90
+    assert ws.ws_synapse_select_is_lazy(ws.WS_F32, H, L, d, k)
     K2, rho2 = clouds(L, d, 11, "lattice")
     for K0 in (K2 + 512.0, K2 * 2.0 ** -62):
         K, rho, copies = heads(K0, rho2, H, "f32")
@@ -166,6 +169,7 @@ def test_distances_beyond_the_range_of_fp32_end(dtype, H, L, k):
     and none twice."""
     import torch
     from paper_2601_01298_amd import binding as ws
+    assert ws.ws_synapse_select_is_lazy(ws.WS_BF16 if dtype == "bf16" else ws.WS_F32, H, L, 64, k)
     K2, rho2 = clouds(L, 64, 17, "lattice")
     K2[:, ::3] -= 12.0
     K, rho, _ = heads(K2 * 2.0 ** 62, rho2, H, dtype)
