@@ -170,7 +170,10 @@ def main() -> int:
 
     # ---- algorithmic work per launch (per-head figures x heads)
     flops_density = 2.0 * w.L * w.L * w.d * w.H                 # 2 L^2 d per head
-    bytes_select = float(w.k) * w.L * w.d * esize * w.H         # streaming model: k sweeps over the head's keys
+    # what a selection cannot do without: keys and density read once, picks written; a sweep over the keys at every step would
+    # read k times that, which neither the kernel that keeps them on chip nor the lazy one does (bound by the chain of k steps)
+    bytes_select = float(w.H) * (w.L * (w.d * esize + 4.0) + 4.0 * w.k)
+    bytes_sweeps = float(w.k) * w.L * w.d * esize * w.H
     bytes_gather = 2.0 * 2.0 * w.k * w.d * esize * w.H          # K and V rows, read + written
     flops_attend = 4.0 * w.N * w.Hq * w.k * w.d
     bytes_attend = 2.0 * w.k * w.d * esize * w.H + w.N * w.Hq * w.d * (esize + 4)
@@ -178,8 +181,9 @@ def main() -> int:
     per_stage = {
         "density": {"bound": "mfma", "achieved": flops_density / (stage_ms["density"] * 1e-3) / 1e12,
                     "peak": peak_mfma, "unit": "TFLOP/s"},
-        "select": {"bound": "hbm", "achieved": bytes_select / (stage_ms["select"] * 1e-3) / 1e9,
-                   "peak": PEAK_HBM_GBS, "unit": "GB/s"},
+        "select": {"bound": "latency", "achieved": bytes_select / (stage_ms["select"] * 1e-3) / 1e9,
+                   "peak": PEAK_HBM_GBS, "unit": "GB/s",
+                   "sweeps_gbs": bytes_sweeps / (stage_ms["select"] * 1e-3) / 1e9},
         "gather": {"bound": "hbm", "achieved": bytes_gather / (stage_ms["gather"] * 1e-3) / 1e9,
                    "peak": PEAK_HBM_GBS, "unit": "GB/s"},
         "attend": {"bound": "hbm", "achieved": bytes_attend / (stage_ms["attend"] * 1e-3) / 1e9,
@@ -219,6 +223,9 @@ def main() -> int:
         c = counters.get(s)
         if isinstance(c, dict):
             per_stage[s]["traffic"] = c.get("hbm_bytes")
+            if s == "select" and c.get("hbm_bytes"):
+                # of the memory's rate, by the bytes counted in the profiled launch
+                per_stage[s]["traffic_frac"] = c["hbm_bytes"] / (stage_ms[s] * 1e-3) / 1e9 / PEAK_HBM_GBS
             for key in ("mfma_busy", "valu_issue", "held_clock_ghz", "waves_waiting"):
                 if key in c:
                     per_stage[s][key] = c[key]
