@@ -131,7 +131,8 @@ int ws_synapse_density_is_symmetric(ws_dtype dt, int L, int d);
  *
  * Co-residency contract.  The resident and the streaming kernel are persistent: the workgroups that
  * share a head exchange their partial maxima every step and wait for each other, so the WHOLE grid has to be resident on
- * the device at once (the two kernels with one workgroup per head wait for nobody and cannot give up).  The launch is sized from the current device (its compute-unit count and the
+ * the device at once (the workgroups of the two kernels with one per head wait for nobody; heads that the first of them leaves to the
+ * streaming kernel are under this contract).  The launch is sized from the current device (its compute-unit count and the
  * number of workgroups of the kernel a compute unit holds, both asked of the runtime at every call),
  * which guarantees this when the selection has the device to itself.  The paper runs the producer
  * beside other streams (Sec. 3.1, Sec. 4); work on other streams that holds compute units while a
@@ -265,7 +266,9 @@ ws_status ws_synapse_attend_indexed(const void *Q, const void *K, const void *V,
  *   Hq <= 128 per group, Hq/Hkv <= 8;  scale <= 0 means 1/sqrt(d)
  *   A workspace with room for one (max, sum) pair per query head and 2048 tokens behind the logits, which is what
  *   ws_synapse_workspace_bytes once reported (now: per 1024 tokens), is accepted; bf16 keys with more than two query heads
- *   per KV head are slower with it.
+ *   per KV head, or of few heads (G * Hkv * L / 1024 below 512), are slower with it.
+ *   The order of the sums follows the sizes of the call and its workspace: with bf16 keys and one or two query heads per KV head the
+ *   same layers may differ in the last bits between one call for all and a call for each.
  */
 ws_status ws_synapse_attention_mass(const void *K, const void *Q, ws_dtype dt, int G, int Hkv, int Hq,
                                     int L, int d, float scale, int as_density, float *out,

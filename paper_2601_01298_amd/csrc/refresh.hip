@@ -156,7 +156,7 @@ append_sweep(const void *__restrict__ Kv, const float *__restrict__ rho_old, flo
 // The form for bf16 keys and more than a few new rows, where the direct differences of every pair are what the sweep is bound by
 // (two instructions per element and pair against a read of two bytes per element).
 //
-// The dot products of 64 keys with up to 16 (CT = 2: 32) new rows are MFMA tiles, operands fetched as they lie in memory, and
+// The dot products of 32 keys per turn of a wave with up to 16 (CT = 2: 32) new rows are MFMA tiles, operands fetched as they lie in memory, and
 // |k - s|^2 = (|k|^2 - k.s) + (|s|^2 - k.s).  That is as exact as differences where the two rows are far apart, and loses what
 // |k|^2 + |s|^2 exceeds the distance by where they are near: a pair nearer than kNear of it is evaluated by direct differences,
 // eight lanes (16 at d = 128) to a pair, out of a list of the wave.  A wave that finds a tenth of its pairs near (rows that lie

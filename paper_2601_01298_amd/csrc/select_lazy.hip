@@ -19,7 +19,7 @@
 //
 // What bounds it: the chain of a step (median 9 000 cycles with four groups visited, d = 64; queue, rows, update, score, three
 // barriers), and the first steps and those where D_max falls, in which hundreds of groups contend.  A visit is some 800 vector
-// instructions.  384 heads of 32768 keys (d = 64, 655 picks): 32.7 ms with the keys on chip, twelve rounds of 32 heads; 16.9 here, all
+// instructions.  384 heads of 32768 keys (d = 64, 655 picks): 32.8 ms with the keys on chip, twelve rounds of 32 heads; 16.2 here, all
 // heads at once.  Tried: a visit per wave and round to groups of its own (20-25 ms: the slowest wave held the others up), every
 // passing pair evaluated (x 1.3), records in registers, the next group's rows asked for ahead (no gain), visits of four tiles.
 #include "ws_internal.h"
